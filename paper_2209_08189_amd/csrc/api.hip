@@ -390,10 +390,10 @@ const float *reduced_grad(cl_ctx *ctx) { return ctx->opt.beta_w != 0.0 ? ctx->pz
 
 // GN Hessian matvec (incremental state, incremental adjoint, quadrature,
 // beta A vt); needs feet of both directions and the state of the current v.
-// dot_out (device, optional): <vt, Hvt> (weighted by h1 h2 h3), fused into
-// the quadrature that produces Hvt.
+// pcg_sc (device, optional): <vt, Hvt> (weighted by h1 h2 h3), fused into
+// the quadrature that produces Hvt, and PCG's alpha from it.
 // data_only: Hvt = the data term b~ alone (no regularisation term added).
-void matvec(cl_ctx *ctx, const float *vt, float *Hvt, const float *Avt_known = nullptr, double *dot_out = nullptr,
+void matvec(cl_ctx *ctx, const float *vt, float *Hvt, const float *Avt_known = nullptr, double *pcg_sc = nullptr,
             bool data_only = false)
 {
     ensure_feet(ctx, true);
@@ -456,10 +456,10 @@ void matvec(cl_ctx *ctx, const float *vt, float *Hvt, const float *Avt_known = n
         Avt = ctx->tmp3;
     }
     const QuadArgs qa = quad_args(ctx);
-    if (dot_out) {
+    if (pcg_sc) {
         run(ctx, CL_K_QUAD, [&] {
             launch_quadrature_dot(ctx->g, ctx->dta, qa, Avt, Hvt, vt, ctx->qparts, ctx->s);
-            launch_finalize(ctx->qparts, quadrature_blocks(ctx->g, qa), ctx->hv, dot_out, ctx->s);
+            launch_finalize_alpha(ctx->qparts, quadrature_blocks(ctx->g, qa), ctx->hv, pcg_sc, ctx->s);
         });
     } else {
         run(ctx, CL_K_QUAD, [&] { launch_quadrature(ctx->g, ctx->dta, qa, Avt, Hvt, ctx->s); });
@@ -513,16 +513,14 @@ void h0_inner(cl_ctx *ctx, const H0Level &L, const float *r, float *z)
                 launch_h0_apply(L.ip, L.iLp, L.G0, L.ih, N, ctx->partials, nb, ctx->s);
             else
                 launch_h0_direction_apply(L.ip, L.iLp, L.izi, L.ir, L.G0, L.ih, sc, N, ctx->partials, nb, ctx->s);
-            launch_finalize(ctx->partials, nb, L.hv, sc + PCG_PHP, ctx->s);
-            launch_pcg_alpha(sc, ctx->s);
+            launch_finalize_alpha(ctx->partials, nb, L.hv, sc, ctx->s);
             launch_h0_update(z, L.ir, L.ip, L.ih, sc, N, ctx->s);
         });
         if (it == inner - 1) break;
         level_spectral(ctx, L, 1, L.ir, L.izi);
         run(ctx, CL_K_VEC, [&] {
             launch_dot(L.ir, L.izi, n, ctx->partials, nb, ctx->s);
-            launch_finalize(ctx->partials, nb, L.hv, sc + PCG_RZNEW, ctx->s);
-            launch_pcg_beta(sc, ctx->s);
+            launch_finalize_beta(ctx->partials, nb, L.hv, sc, ctx->s);
         });
     }
 }
@@ -623,9 +621,8 @@ int pcg(cl_ctx *ctx, int max_pcg, double eta, int forced, int *iters)
     const int limit = forced >= 0 ? forced : max_pcg;
     int it = 0, neg = 0;
     while (it < limit) {
-        matvec(ctx, ctx->pp, ctx->pHp, pAp, sc + PCG_PHP);
+        matvec(ctx, ctx->pp, ctx->pHp, pAp, sc);
         run(ctx, CL_K_VEC, [&] {
-            launch_pcg_alpha(sc, ctx->s);
             launch_pcg_update3(ctx->px, ctx->pr, ctx->pp, ctx->pHp, sc, ctx->N, ctx->qparts, nbc, ctx->hv, ctx->s);
         });
         HIPCHK(hipMemcpyAsync(ctx->hscal, sc, sizeof(double) * PCG_NSCAL, hipMemcpyDeviceToHost, ctx->s));
@@ -656,8 +653,7 @@ int pcg(cl_ctx *ctx, int max_pcg, double eta, int forced, int *iters)
         precond(ctx, ctx->pr, ctx->pz);
         run(ctx, CL_K_VEC, [&] {
             launch_dot(ctx->pr, ctx->pz, n, ctx->partials, ctx->nparts, ctx->s);
-            launch_finalize(ctx->partials, ctx->nparts, ctx->hv, sc + PCG_RZNEW, ctx->s);
-            launch_pcg_beta(sc, ctx->s);
+            launch_finalize_beta(ctx->partials, ctx->nparts, ctx->hv, sc, ctx->s);
             launch_pcg_direction(ctx->pp, pAp, ctx->pz, ctx->pr, sc, ctx->N, ctx->s);
         });
     }

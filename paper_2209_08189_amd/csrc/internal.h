@@ -223,8 +223,10 @@ void launch_add_sums3(float *y, const double *sums, double scale, size_t n, hipS
 // of p . out in partials[0 .. nblocks)
 void launch_h0_apply(const float *p, const float *Lp, const float *G, float *out, size_t n, double *partials,
                      int nblocks, hipStream_t s);
-void launch_pcg_alpha(double *sc, hipStream_t s);
-void launch_pcg_beta(double *sc, hipStream_t s);
+// sc[PCG_PHP] = scale * (sum of the partials), then alpha and the curvature flag
+void launch_finalize_alpha(const double *partials, int nblocks, double scale, double *sc, hipStream_t s);
+// sc[PCG_RZNEW] = scale * (sum of the partials), then beta, and rz = rz_new
+void launch_finalize_beta(const double *partials, int nblocks, double scale, double *sc, hipStream_t s);
 // x += alpha p, r -= alpha Hp (nothing when alpha = 0); sc[PCG_RR] = rscale
 // ||r||^2, sc[PCG_SUMR + c] = sum of component c; partials needs 6 nblocks
 // entries

@@ -1,0 +1,53 @@
+"""The last stages of the device reductions: the extremes of det grad y against
+the field they are taken from (equal: no arithmetic is involved), with partial
+counts below, at and above one workgroup, and NaN where a value is not finite;
+a dot product against numpy in 64 bits (products of FP32 values are exact in
+FP64; n additions round to n 2^-53 of the sum of magnitudes)."""
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _velocity(shape, amplitude):
+    g = torch.Generator().manual_seed(sum(shape))
+    k = torch.fft.rfftn(torch.randn((3,) + shape, generator=g), dim=(1, 2, 3))
+    low = torch.zeros_like(k)
+    low[:, :3, :3, :3] = k[:, :3, :3, :3]
+    v = torch.fft.irfftn(low, s=shape, dim=(1, 2, 3))
+    return (amplitude * v / v.abs().max()).contiguous().cuda()
+
+
+@pytest.mark.parametrize("shape", [(16, 16, 16), (16, 16, 32), (64, 32, 128), (64, 128, 256)])
+def test_jacobian_extremes_are_those_of_the_field(shape):
+    from paper_2209_08189_amd.claire import Registration
+    r = Registration(shape)
+    r.set_velocity(_velocity(shape, 0.2))
+    jac, lo, hi = r.jacobian_det(want_field=True)
+    assert (lo, hi) == (float(jac.min()), float(jac.max()))
+    # div v near 1e30 overflows the source factor
+    r.set_velocity(_velocity(shape, 1e30))
+    _, lo, hi = r.jacobian_det()
+    assert math.isnan(lo) and math.isnan(hi)
+
+
+@pytest.mark.parametrize("n", [1, 255, 1025, 3 * 32 ** 3])
+def test_dot_against_numpy(n):
+    from paper_2209_08189_amd.claire import Registration
+    shape = (32, 32, 32)
+    r = Registration(shape)
+    g = torch.Generator().manual_seed(n)
+    a, b = torch.randn(n, generator=g), torch.randn(n, generator=g)
+    p = a.numpy().astype(np.float64) * b.numpy().astype(np.float64)
+    hv = (2.0 * math.pi / 32) ** 3
+    got = r.dot(a.cuda(), b.cuda())
+    assert abs(got - hv * p.sum()) <= 2 * n * 2.0 ** -53 * hv * np.abs(p).sum()
