@@ -62,7 +62,6 @@ struct cl_ctx {
     float *df = nullptr, *db = nullptr;     // 3N
     float *c = nullptr, *divv = nullptr;    // N
     float *grad = nullptr, *Av = nullptr, *tmp3 = nullptr;  // 3N
-    float *fscr = nullptr;                  // 3N workspace of the feet computation
     float *px = nullptr, *pr = nullptr, *pz = nullptr, *pp = nullptr, *pHp = nullptr;  // 3N
     double *partials = nullptr, *dscal = nullptr, *hscal = nullptr;
     double *qparts = nullptr;                // partials of the fused PCG reductions
@@ -251,7 +250,7 @@ void ensure_feet(cl_ctx *ctx, bool backward)
         run(ctx, CL_K_FEET, [&] {
             launch_feet(ctx->g, ctx->dt, ctx->v, ctx->df, backward ? ctx->db : nullptr,
                         backward ? ctx->divv : nullptr, backward ? ctx->c : nullptr, ctx->box_f, ctx->box_b,
-                        ctx->fscr, ctx->s);
+                        ctx->s);
         });
         ctx->feet_f = true;
         if (backward) ctx->feet_b = true;
@@ -368,8 +367,7 @@ double gradient(cl_ctx *ctx, double *J, double *mis_out, double *reg_out)
     if (ctx->opt.beta_w == 0.0) {
         run(ctx, CL_K_QUAD, [&] { launch_quadrature(ctx->g, ctx->dta, qa, ctx->Av, ctx->grad, ctx->s); });
     } else {
-        // b into the PCG z vector (free outside PCG; the feet scratch that
-        // may share it is consumed by now), L v + b into ctx->grad, and the
+        // b into the PCG z vector (free outside PCG), L v + b into ctx->grad, and the
         // reduced gradient beta_v A v + K b in z, each term formed directly
         run(ctx, CL_K_QUAD, [&] { launch_quadrature(ctx->g, ctx->dta, qa, nullptr, ctx->pz, ctx->s); });
         run(ctx, CL_K_VEC, [&] { launch_axpy(ctx->grad, ctx->Av, ctx->pz, 1.0f, n3, ctx->s); });
@@ -1163,8 +1161,6 @@ int cl_create(cl_ctx **out, int n1, int n2, int n3, const cl_options *opt)
                 throw Fail{CL_ERR_HIP};
             }
         }
-        // the feet are computed outside PCG, where z is free
-        ctx->fscr = ctx->pz;
         ctx->c = (float *)alloc(N * sizeof(float));
         ctx->divv = (float *)alloc(N * sizeof(float));
         ctx->nparts = reduce_blocks(3 * N);

@@ -104,16 +104,6 @@ __device__ __forceinline__ float gather(const T *__restrict__ u, const Foot &F)
 
 // ------------------------------------------------------------- kernels
 
-// RK2 (Heun) feet of both characteristic directions, as index-unit
-// displacements:  X_f = x - dt/2 [v(x) + v(x - dt v(x))],
-//                 X_b = x + dt/2 [v(x) + v(x + dt v(x))],
-// and the adjoint factor c = 1 + dt/2 (dbar + d + dt dbar d), d = div_h v,
-// dbar = d(X_b).  The velocity at the predictor feet and dbar are tricubic
-// interpolations done by the tiled SL gather (launch_feet below); these
-// kernels are the elementwise steps around them.  Displacements divide by h
-// (correctly rounded), so a velocity that is an exact multiple of h/dt gives
-// an exactly integer foot.
-
 // The solver keeps its displacements interleaved per node (d1 d2 d3 of node
 // p at 3p), so an SL step reads the feet of a node with one 12-byte load;
 // the interpolation entry points take three separate fields from the caller.
@@ -133,29 +123,6 @@ __device__ __forceinline__ void foot_of(const float *__restrict__ d, size_t N, s
     }
 }
 
-// predictor displacement d = (a v) / h, a = -dt (X_f) or +dt (X_b), interleaved
-__global__ __launch_bounds__(TPB) void k_feet_pred(Grid g, float a, const float *__restrict__ v, float *__restrict__ d)
-{
-    const int p = blockIdx.x * TPB + threadIdx.x;
-    if (p >= g.N) return;
-    const size_t N = g.N;
-    *reinterpret_cast<float3 *>(d + 3 * (size_t)p) =
-        make_float3((a * v[p]) / g.h1, (a * v[N + p]) / g.h2, (a * v[2 * N + p]) / g.h3);
-}
-
-// corrector displacement d = (b (v + vi)) / h, b = -dt/2 (X_f) or +dt/2 (X_b),
-// vi = v interpolated at the predictor feet (three fields); d interleaved
-__global__ __launch_bounds__(TPB) void k_feet_corr(Grid g, float b, const float *__restrict__ v,
-                                                   const float *__restrict__ vi, float *__restrict__ d)
-{
-    const int p = blockIdx.x * TPB + threadIdx.x;
-    if (p >= g.N) return;
-    const size_t N = g.N;
-    *reinterpret_cast<float3 *>(d + 3 * (size_t)p) =
-        make_float3((b * (v[p] + vi[p])) / g.h1, (b * (v[N + p] + vi[N + p])) / g.h2,
-                    (b * (v[2 * N + p] + vi[2 * N + p])) / g.h3);
-}
-
 // interleaved feet -> three fields (the feet a caller reads back)
 __global__ __launch_bounds__(TPB) void k_feet_fields(Grid g, const float *__restrict__ d, float *__restrict__ out)
 {
@@ -165,33 +132,6 @@ __global__ __launch_bounds__(TPB) void k_feet_fields(Grid g, const float *__rest
     foot_of<true>(d, N, p, out[p], out[N + p], out[2 * N + p]);
 }
 
-__global__ __launch_bounds__(TPB) void k_adj_factor(Grid g, float dt, const float *__restrict__ divv,
-                                                    const float *__restrict__ dbar, float *__restrict__ c)
-{
-    const int p = blockIdx.x * TPB + threadIdx.x;
-    if (p >= g.N) return;
-    const float d = divv[p], db = dbar[p];
-    c[p] = 1.0f + 0.5f * dt * (db + d + dt * db * d);
-}
-
-// Source factor of the Jacobian determinant transport d_t J + v.grad J =
-// -(div v) J over one step along the forward characteristic (Heun):
-// f = 1 - dt/2 (d_f + d - dt d_f d), d_f = div v at the foot X_f (in place:
-// dfoot holds d_f on entry and f on exit).
-__global__ __launch_bounds__(TPB) void k_jac_factor(Grid g, float dt, const float *__restrict__ divv, float *dfoot)
-{
-    const int p = blockIdx.x * TPB + threadIdx.x;
-    if (p >= g.N) return;
-    const float d = divv[p], df = dfoot[p];
-    dfoot[p] = 1.0f - 0.5f * dt * (df + d - dt * df * d);
-}
-
-__global__ __launch_bounds__(TPB) void k_fill1(float *x, int n)
-{
-    const int p = blockIdx.x * TPB + threadIdx.x;
-    if (p < n) x[p] = 1.0f;
-}
-
 // ------------------------------------------------ semi-Lagrangian steps
 // One SL step gathers u at the feet of every node and applies a mode-specific
 // epilogue with one per-node operand e:
@@ -199,13 +139,19 @@ __global__ __launch_bounds__(TPB) void k_fill1(float *x, int n)
 //   SL_ADJ:    out = e * I[u](X)             (e = c, adjoint divergence factor)
 //   SL_INC:    out = sI * I[u](X) + sS * e   (e = s^{j+1} = -vt . grad_h m^{j+1},
 //                                             incremental source, precomputed)
-enum { SL_STATE = 0, SL_ADJ = 1, SL_INC = 2 };
+// and, with u = e = d = div_h v and I[u](X) = d at the foot, the Heun factors
+// of one step (sI = dt):
+//   SL_CFAC:   out = 1 + dt/2 (dbar + d + dt dbar d)   adjoint, foot X_b
+//   SL_JFAC:   out = 1 - dt/2 (df + d - dt df d)       det grad y, foot X_f
+enum { SL_STATE = 0, SL_ADJ = 1, SL_INC = 2, SL_CFAC = 3, SL_JFAC = 4 };
 
 template <int MODE>
 __device__ __forceinline__ float epilogue(const SLParams &prm, float e, float val)
 {
     if (MODE == SL_ADJ) return e * val;
     if (MODE == SL_INC) return fmaf(prm.sI, val, prm.sS * e);
+    if (MODE == SL_CFAC) return 1.0f + 0.5f * prm.sI * (val + e + prm.sI * val * e);
+    if (MODE == SL_JFAC) return 1.0f - 0.5f * prm.sI * (val + e - prm.sI * val * e);
     return val;
 }
 
@@ -343,51 +289,76 @@ __device__ __forceinline__ TileIdx tile_idx(const Grid &g, int tile, int ntx, in
     return t;
 }
 
-// Bounding box of the 4x4x4 stencils of the feet of every tile, once per
-// velocity and direction: box[8 tile + 0..2] = origin relative to the tile
-// origin (x1, x2, x3), box[8 tile + 3..5] = extents.  The integer parts are
-// the same clamped floors that the SL kernels use, so every stencil lies
-// inside its box for any finite displacement.
-template <bool AOS>
+// Running bounds of the floors of a thread's feet, relative to the tile
+// origin, and their reduction over the NW wavefronts of a workgroup (the
+// result is valid in every thread; red is free again once all have passed a
+// following barrier).
+struct Bounds {
+    int mn1 = 1 << 30, mx1 = -(1 << 30), mn2 = 1 << 30, mx2 = -(1 << 30), mn3 = 1 << 30, mx3 = -(1 << 30);
+    __device__ __forceinline__ void add(int b1, int b2, int b3)
+    {
+        mn1 = min(mn1, b1); mx1 = max(mx1, b1);
+        mn2 = min(mn2, b2); mx2 = max(mx2, b2);
+        mn3 = min(mn3, b3); mx3 = max(mx3, b3);
+    }
+    template <int NW> __device__ __forceinline__ void reduce(int (&red)[NW][6])
+    {
+        mn1 = wave_min(mn1); mx1 = wave_max(mx1);
+        mn2 = wave_min(mn2); mx2 = wave_max(mx2);
+        mn3 = wave_min(mn3); mx3 = wave_max(mx3);
+        const int wv = threadIdx.x >> 6;
+        if ((threadIdx.x & 63) == 0) {
+            red[wv][0] = mn1; red[wv][1] = mx1; red[wv][2] = mn2;
+            red[wv][3] = mx2; red[wv][4] = mn3; red[wv][5] = mx3;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            mn1 = min(mn1, red[w][0]); mx1 = max(mx1, red[w][1]);
+            mn2 = min(mn2, red[w][2]); mx2 = max(mx2, red[w][3]);
+            mn3 = min(mn3, red[w][4]); mx3 = max(mx3, red[w][5]);
+        }
+    }
+    // box of the stencils: they start lo nodes below the floor and span
+    // span nodes (cubic: 1, 4; trilinear: 0, 2)
+    __device__ __forceinline__ void box(int lo, int span, int (&o)[6]) const
+    {
+        o[0] = mn1 - lo; o[1] = mn2 - lo; o[2] = mn3 - lo;
+        o[3] = mx1 - mn1 + span; o[4] = mx2 - mn2 + span; o[5] = mx3 - mn3 + span;
+    }
+};
+
+__device__ __forceinline__ void store_box(int *__restrict__ box, int tile, const int (&o)[6])
+{
+    int *p = box + 8 * tile;
+#pragma unroll
+    for (int a = 0; a < 6; ++a) p[a] = o[a];
+    p[6] = 0;
+    p[7] = 0;
+}
+
+// Bounding box of the 4x4x4 stencils of the feet of every tile (of a caller's
+// displacement; the solver's feet come with their boxes): box[8 tile + 0..2]
+// = origin relative to the tile origin (x1, x2, x3), box[8 tile + 3..5] =
+// extents.  The integer parts are the same clamped floors that the SL kernels
+// use, so every stencil lies inside its box for any finite displacement.
 __global__ __launch_bounds__(TPB) void k_tile_boxes(Grid g, const float *__restrict__ d, int ntx, int nty,
                                                     int *__restrict__ box, int lo, int span)
 {
     __shared__ int red[TPB / 64][6];
     const TileIdx t = tile_idx<1>(g, blockIdx.x, ntx, nty);
     const size_t N = g.N;
-    int mn1 = 1 << 30, mx1 = -(1 << 30), mn2 = 1 << 30, mx2 = -(1 << 30), mn3 = 1 << 30, mx3 = -(1 << 30);
+    Bounds b;
 #pragma unroll
     for (int q = 0; q < TZ; ++q) {
         const int p = t.p0 + q * t.plane;
-        float a1, a2, a3;
-        foot_of<AOS>(d, N, p, a1, a2, a3);
-        const int b1 = q + ifloor(a1), b2 = ifloor(a2), b3 = ifloor(a3);
-        mn1 = min(mn1, b1); mx1 = max(mx1, b1);
-        mn2 = min(mn2, b2); mx2 = max(mx2, b2);
-        mn3 = min(mn3, b3); mx3 = max(mx3, b3);
+        b.add(q + ifloor(d[p]), t.row + ifloor(d[N + p]), t.lane + ifloor(d[2 * N + p]));
     }
-    mn2 += t.row; mx2 += t.row; mn3 += t.lane; mx3 += t.lane;
-    mn1 = wave_min(mn1); mx1 = wave_max(mx1);
-    mn2 = wave_min(mn2); mx2 = wave_max(mx2);
-    mn3 = wave_min(mn3); mx3 = wave_max(mx3);
-    const int wv = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        red[wv][0] = mn1; red[wv][1] = mx1; red[wv][2] = mn2;
-        red[wv][3] = mx2; red[wv][4] = mn3; red[wv][5] = mx3;
-    }
-    __syncthreads();
+    b.reduce(red);
     if (threadIdx.x != 0) return;
-    for (int w = 1; w < TPB / 64; ++w) {
-        mn1 = min(mn1, red[w][0]); mx1 = max(mx1, red[w][1]);
-        mn2 = min(mn2, red[w][2]); mx2 = max(mx2, red[w][3]);
-        mn3 = min(mn3, red[w][4]); mx3 = max(mx3, red[w][5]);
-    }
-    // the stencil starts lo nodes below the floor and spans span nodes
-    // (cubic: 1, 4; trilinear: 0, 2)
-    int *o = box + 8 * blockIdx.x;
-    o[0] = mn1 - lo; o[1] = mn2 - lo; o[2] = mn3 - lo;
-    o[3] = mx1 - mn1 + span; o[4] = mx2 - mn2 + span; o[5] = mx3 - mn3 + span;
-    o[6] = 0; o[7] = 0;
+    int o[6];
+    b.box(lo, span, o);
+    store_box(box, blockIdx.x, o);
 }
 
 // Box of one tile as the SL kernels use it.
@@ -396,11 +367,10 @@ struct TileBox {
     bool fits;
 };
 template <typename Tu>
-__device__ __forceinline__ TileBox tile_box(const int *__restrict__ boxes, int tile, const TileIdx &t)
+__device__ __forceinline__ TileBox tile_box(const int *__restrict__ bx, const TileIdx &t)
 {
     constexpr int PX = box_px<Tu>();
     TileBox B;
-    const int *bx = boxes + 8 * tile;
     B.r1 = bx[0]; B.r2 = bx[1]; B.r3 = bx[2];
     B.E1 = bx[3]; B.E2 = bx[4]; B.E3 = bx[5];
     // global x3 index of box column 0; 16-bit boxes start at the even index
@@ -768,7 +738,7 @@ __global__ __launch_bounds__(TPB_SL, 8) void k_sl_tile(Grid g, const Tu *__restr
     const int b = blockIdx.x;
     const int tile = (nblk & 7) ? b : (b & 7) * (nblk >> 3) + (b >> 3);
     const TileIdx t = tile_idx<SPLIT>(g, tile, ntx, nty);
-    const TileBox B = tile_box<Tu>(boxes, tile, t);
+    const TileBox B = tile_box<Tu>(boxes + 8 * tile, t);
     if (!B.fits) {                 // the whole workgroup takes this branch
         tile_fallback<Tu, To, MODE, ORDER, AOS>(g, u, d, prm, out, t);
         return;
@@ -785,6 +755,159 @@ __global__ __launch_bounds__(TPB_SL, 8) void k_sl_tile(Grid g, const Tu *__restr
     }
     compute_tile<Tu, MODE, ORDER>(box, t, B, d1, d2, d3, e, prm, r);
     store_tile(out, t, r);
+}
+
+// ---------------------------------------------------------------- the feet
+// RK2 (Heun) feet of both characteristic directions, as index-unit
+// displacements:  X_f = x - dt/2 [v(x) + v(x - dt v(x))],
+//                 X_b = x + dt/2 [v(x) + v(x + dt v(x))],
+// and the adjoint factor c = 1 + dt/2 (dbar + d + dt dbar d), d = div_h v,
+// dbar = d(X_b) (SL_CFAC).  Displacements divide by h (correctly rounded), so
+// a velocity that is an exact multiple of h/dt gives an exactly integer foot.
+//
+// One kernel per velocity computes both directions (blockIdx.y): predictor
+// d = (a v) / h with a = -dt or +dt, the velocity interpolated there, the
+// corrector d = (a/2 (v + vi)) / h and the tile boxes of the result.  The
+// velocity of a node is read once; the predictor displacements, their boxes
+// and the interpolated velocity never leave the workgroup.  As separate
+// launches (predictor, boxes, one SL gather per component, corrector, boxes)
+// the intermediate fields made 33 field passes per direction, 560 us at 256^3;
+// in one kernel a direction takes 350 us, bound by the VALU and LDS issue of
+// the three gathers like an SL step.  Trilinear at 128^3: 56 -> 15 us.
+struct FeetArgs {
+    float a[2];          // -dt, +dt
+    float *d[2];         // feet out, interleaved
+    int *box[2];         // tile boxes of the feet out (tiled grids)
+};
+
+__device__ __forceinline__ float3 feet_pred(const Grid &g, float a, float v1, float v2, float v3)
+{
+    return make_float3((a * v1) / g.h1, (a * v2) / g.h2, (a * v3) / g.h3);
+}
+
+// s = v + vi; b = a / 2
+__device__ __forceinline__ float3 feet_corr(const Grid &g, float b, float s1, float s2, float s3)
+{
+    return make_float3((b * s1) / g.h1, (b * s2) / g.h2, (b * s3) / g.h3);
+}
+
+// The feet of one node with the velocity gathered from global memory.
+template <int ORDER>
+__device__ __forceinline__ float3 feet_node(const Grid &g, float a, const float *__restrict__ v, int p, int i, int j,
+                                            int k)
+{
+    const size_t N = g.N;
+    const float v1 = v[p], v2 = v[N + p], v3 = v[2 * N + p];
+    const float3 d = feet_pred(g, a, v1, v2, v3);
+    float s[3];
+    if constexpr (ORDER == 1) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c] = lin_node(g, v + c * N, i, j, k, d.x, d.y, d.z);
+    } else {
+        Foot F;
+        make_foot(g, i, j, k, d.x, d.y, d.z, F);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c] = gather(v + c * N, F);
+    }
+    return feet_corr(g, 0.5f * a, v1 + s[0], v2 + s[1], v3 + s[2]);
+}
+
+// Per-node version (grids too small for tiles).
+template <int ORDER>
+__global__ __launch_bounds__(TPB) void k_feet_node(Grid g, const float *__restrict__ v, FeetArgs fa)
+{
+    const int p = blockIdx.x * TPB + threadIdx.x;
+    if (p >= g.N) return;
+    int i, j, k;
+    node_of(g, p, i, j, k);
+    *reinterpret_cast<float3 *>(fa.d[blockIdx.y] + 3 * (size_t)p) =
+        feet_node<ORDER>(g, fa.a[blockIdx.y], v, p, i, j, k);
+}
+
+// Tiled version, with the thread layout and the box staging of k_sl_tile.  The
+// three components take turns in one box, so the LDS of a workgroup is that of
+// an SL step and four workgroups per CU overlap one another's phases (two
+// boxes with the next component staged ahead: two workgroups per CU and 180
+// spilled registers, 1300 us per direction).
+template <int ORDER>
+__global__ __launch_bounds__(TPB_SL, 8) void k_feet_tile(Grid g, const float *__restrict__ v, FeetArgs fa, int ntx,
+                                                         int nty, int nblk)
+{
+    constexpr int LO = ORDER == 1 ? 0 : 1, SPAN = ORDER == 1 ? 2 : 4;
+    __shared__ __align__(16) float box[PZ * PY * box_px<float>()];
+    __shared__ int red[2][TPB_SL / 64][6];
+    const int b = blockIdx.x;
+    const int tile = (nblk & 7) ? b : (b & 7) * (nblk >> 3) + (b >> 3);
+    const TileIdx t = tile_idx<SPLIT>(g, tile, ntx, nty);
+    const size_t N = g.N;
+    const float a = fa.a[blockIdx.y];
+    float *dout = fa.d[blockIdx.y];
+    Bounds pb, cb;
+    int o[6];
+    float d1[QT], d2[QT], d3[QT], s[3][QT];
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+        const unsigned p = (unsigned)(t.p0 + q * t.plane);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) s[c][q] = at(v + c * N, p);
+    }
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+        const float3 d = feet_pred(g, a, s[0][q], s[1][q], s[2][q]);
+        d1[q] = d.x;
+        d2[q] = d.y;
+        d3[q] = d.z;
+        pb.add(t.q0 + q + ifloor(d.x), t.row + ifloor(d.y), t.lane + ifloor(d.z));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    pb.reduce(red[0]);
+    pb.box(LO, SPAN, o);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) o[c] = __builtin_amdgcn_readfirstlane(o[c]);
+    const TileBox B = tile_box<float>(o, t);
+    if (!B.fits) {                 // the whole workgroup takes this branch
+#pragma unroll 1
+        for (int q = 0; q < QT; ++q) {
+            const int p = t.p0 + q * t.plane;
+            const float3 d = feet_node<ORDER>(g, a, v, p, t.i0 + t.q0 + q, t.j, t.k);
+            *reinterpret_cast<float3 *>(dout + 3 * (size_t)p) = d;
+            cb.add(t.q0 + q + ifloor(d.x), t.row + ifloor(d.y), t.lane + ifloor(d.z));
+        }
+        cb.reduce(red[1]);
+        cb.box(LO, SPAN, o);
+        if (threadIdx.x == 0) store_box(fa.box[blockIdx.y], tile, o);
+        return;
+    }
+    const float e[QT] = {};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        float vi[QT];
+        if (c) __syncthreads();
+        // the weights are formed anew for each component: kept for all
+        // three they would take 48 registers
+#pragma unroll
+        for (int q = 0; q < QT; ++q) asm volatile("" : "+v"(d1[q]), "+v"(d2[q]), "+v"(d3[q]));
+        stage_box(g, v + c * N, box, t, B);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        compute_tile<float, SL_STATE, ORDER>(box, t, B, d1, d2, d3, e, SLParams{}, vi);
+#pragma unroll
+        for (int q = 0; q < QT; ++q) s[c][q] += vi[q];
+    }
+    // interleaved feet from a wave-uniform tile base (as load_feet)
+    const int pt = (((t.i0 << g.l2) + t.ty * TY) << g.l3) + t.tx * TX;
+    char *bd = reinterpret_cast<char *>(dout + 3 * (size_t)pt);
+    const unsigned r0 = (unsigned)(t.p0 - pt) * 12u, rq = (unsigned)t.plane * 12u;
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+        const float3 d = feet_corr(g, 0.5f * a, s[0][q], s[1][q], s[2][q]);
+        *reinterpret_cast<float3 *>(bd + (r0 + q * rq)) = d;
+        cb.add(t.q0 + q + ifloor(d.x), t.row + ifloor(d.y), t.lane + ifloor(d.z));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    cb.reduce(red[1]);
+    cb.box(LO, SPAN, o);
+    if (threadIdx.x == 0) store_box(fa.box[blockIdx.y], tile, o);
 }
 
 inline bool tiled(const Grid &g) { return g.n3 >= TX && g.n2 >= TY && g.n1 >= TZ; }
@@ -812,41 +935,38 @@ void launch_sl(const Grid &g, const Tu *u, const float *d, const SLParams &prm, 
     }
 }
 
-template <bool AOS> void tile_boxes(const Grid &g, const float *d, int *boxes, hipStream_t s)
-{
-    if (!tiled(g)) return;
-    const int ntx = g.n3 / TX, nty = g.n2 / TY, ntz = g.n1 / TZ;
-    const int lo = g.interp == 1 ? 0 : 1, span = g.interp == 1 ? 2 : 4;
-    hipLaunchKernelGGL(k_tile_boxes<AOS>, dim3(ntx * nty * ntz), dim3(TPB), 0, s, g, d, ntx, nty, boxes, lo, span);
-}
-
 } // namespace
 
 void launch_feet(const Grid &g, float dt, const float *v, float *df, float *db, const float *divv, float *c,
-                 int *box_f, int *box_b, float *scratch3, hipStream_t s)
+                 int *box_f, int *box_b, hipStream_t s)
 {
-    const size_t N = g.N;
-    // one direction: predictor, interpolate v there (one SL gather per
-    // component), corrector; the tile boxes follow the displacements
-    auto heun = [&](float a, float b, float *d, int *box) {
-        hipLaunchKernelGGL(k_feet_pred, grid_of(g), dim3(TPB), 0, s, g, a, v, d);
-        launch_tile_boxes(g, d, box, s);
-        for (int k = 0; k < 3; ++k)
-            launch_sl<float, float, SL_STATE>(g, v + k * N, d, SLParams{}, scratch3 + k * N, box, s);
-        hipLaunchKernelGGL(k_feet_corr, grid_of(g), dim3(TPB), 0, s, g, b, v, scratch3, d);
-        launch_tile_boxes(g, d, box, s);
-    };
-    heun(-dt, -0.5f * dt, df, box_f);
-    if (!db) return;
-    heun(dt, 0.5f * dt, db, box_b);
-    if (!c) return;
-    launch_sl<float, float, SL_STATE>(g, divv, db, SLParams{}, scratch3, box_b, s);
-    hipLaunchKernelGGL(k_adj_factor, grid_of(g), dim3(TPB), 0, s, g, dt, divv, scratch3, c);
+    FeetArgs fa{};
+    fa.a[0] = -dt;
+    fa.a[1] = dt;
+    fa.d[0] = df;
+    fa.d[1] = db;
+    fa.box[0] = box_f;
+    fa.box[1] = box_b;
+    const unsigned dirs = db ? 2 : 1;
+    if (tiled(g)) {
+        const int ntx = g.n3 / TX, nty = g.n2 / TY, nblk = ntx * nty * (g.n1 / TZ);
+        if (g.interp == 1)
+            hipLaunchKernelGGL(k_feet_tile<1>, dim3(nblk, dirs), dim3(TPB_SL), 0, s, g, v, fa, ntx, nty, nblk);
+        else
+            hipLaunchKernelGGL(k_feet_tile<3>, dim3(nblk, dirs), dim3(TPB_SL), 0, s, g, v, fa, ntx, nty, nblk);
+    } else if (g.interp == 1) {
+        hipLaunchKernelGGL(k_feet_node<1>, dim3(grid_of(g).x, dirs), dim3(TPB), 0, s, g, v, fa);
+    } else {
+        hipLaunchKernelGGL(k_feet_node<3>, dim3(grid_of(g).x, dirs), dim3(TPB), 0, s, g, v, fa);
+    }
+    if (!db || !c) return;
+    SLParams prm{};
+    prm.e = divv;
+    prm.sI = dt;
+    launch_sl<float, float, SL_CFAC>(g, divv, db, prm, c, box_b, s);
 }
 
 size_t tile_box_ints(const Grid &g) { return tiled(g) ? (size_t)8 * (g.N / (TX * TY * TZ)) : 0; }
-
-void launch_tile_boxes(const Grid &g, const float *d, int *boxes, hipStream_t s) { tile_boxes<true>(g, d, boxes, s); }
 
 void launch_feet_fields(const Grid &g, const float *d, float *out, hipStream_t s)
 {
@@ -896,29 +1016,34 @@ void launch_sl_inc(const Grid &g, int dt_q, const void *q, const float *d, const
 }
 
 // J = det grad y of the map y with m(1) = m0 o y: J^0 = 1, J^{j+1} =
-// f . I[J^j](X_f) with the Heun source factor f; work holds 2N floats (f and
-// one ping-pong half), the result goes to out (N floats).
+// f . I[J^j](X_f) with the Heun source factor f; the weights of I sum to 1,
+// so J^1 = f.  work holds 2N floats (f and one ping-pong half), the result
+// goes to out (N floats).
 void launch_jacobian(const Grid &g, float dt, int nt, const float *divv, const float *df, const int *box_f,
                      float *work, float *out, hipStream_t s)
 {
-    float *f = work, *tmp = work + (size_t)g.N;
-    launch_sl<float, float, SL_STATE>(g, divv, df, SLParams{}, f, box_f, s);
-    hipLaunchKernelGGL(k_jac_factor, grid_of(g), dim3(TPB), 0, s, g, dt, divv, f);
-    // ping-pong so that the last step writes out
-    float *a = (nt & 1) ? tmp : out, *b = (nt & 1) ? out : tmp;
-    hipLaunchKernelGGL(k_fill1, grid_of(g), dim3(TPB), 0, s, a, g.N);
+    float *f = nt == 1 ? out : work, *tmp = work + (size_t)g.N;
     SLParams prm{};
+    prm.e = divv;
+    prm.sI = dt;
+    launch_sl<float, float, SL_JFAC>(g, divv, df, prm, f, box_f, s);
     prm.e = f;
-    for (int j = 0; j < nt; ++j) {
+    const float *a = f;
+    for (int j = 1; j < nt; ++j) {
+        float *b = ((nt - j) & 1) ? out : tmp;   // the last step writes out
         launch_sl<float, float, SL_ADJ>(g, a, df, prm, b, box_f, s);
-        std::swap(a, b);
+        a = b;
     }
 }
 
 // d: three fields from the caller
 void launch_interp_f32(const Grid &g, const float *u, const float *d, int *boxes, float *out, hipStream_t s)
 {
-    tile_boxes<false>(g, d, boxes, s);
+    if (tiled(g)) {
+        const int ntx = g.n3 / TX, nty = g.n2 / TY, ntz = g.n1 / TZ;
+        const int lo = g.interp == 1 ? 0 : 1, span = g.interp == 1 ? 2 : 4;
+        hipLaunchKernelGGL(k_tile_boxes, dim3(ntx * nty * ntz), dim3(TPB), 0, s, g, d, ntx, nty, boxes, lo, span);
+    }
     launch_sl<float, float, SL_STATE, false>(g, u, d, SLParams{}, out, boxes, s);
 }
 
