@@ -5,16 +5,9 @@
 //
 // Activations are channels-last BF16 tensors [D][H][W][C] (C a multiple of
 // 16); arithmetic is FP32.  3x3x3 convolutions run on the matrix cores as an
-// implicit GEMM with v_mfma_f32_16x16x16_bf16:
-//   M = 16 consecutive voxels along x, N = 16 output channels, K = 16 input
-//   channels of one tap; a wavefront owns 16 voxels x all output channels
-//   and loops over the 27 taps and the input-channel chunks.
-// Operand layouts of the 16x16x16 MFMA (lane l, element j = 0..3):
-//   A[m][k]: m = l % 16, k = 4 (l / 16) + j
-//   B[k][n]: n = l % 16, k = 4 (l / 16) + j
-//   D[m][n]: n = l % 16, m = 4 (l / 16) + j
-// Weights are packed once per update into the exact B-fragment order, so a
-// B fragment is one 8-byte load per lane.  The transpose needed by the
+// implicit GEMM with v_mfma_f32_16x16x32_bf16 (K = two taps x 16 input
+// channels, below).  Weights are packed once per update into fragment order, so
+// a fragment is one 16-byte load per lane.  The transpose needed by the
 // backward data pass is the same convolution with flipped taps and swapped
 // channel roles, i.e. the same kernel with a differently packed weight.
 #include "internal.h"
@@ -25,7 +18,10 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+typedef float f2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 
 constexpr int TPB = 256;
 
@@ -36,6 +32,13 @@ __device__ __forceinline__ unsigned short f2bf(float f)
     unsigned u = __float_as_uint(f);
     u += 0x7fffu + ((u >> 16) & 1u);
     return (unsigned short)(u >> 16);
+}
+
+// two values rounded to nearest even and packed, lo in the low half (one
+// v_cvt_pk_bf16_f32)
+__device__ __forceinline__ unsigned pack_bf2(float lo, float hi)
+{
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(f2{lo, hi}, bf2));
 }
 
 // --- weight packing -------------------------------------------------------
@@ -76,101 +79,275 @@ __global__ __launch_bounds__(TPB) void k_pack_w(const float *__restrict__ w, uns
     out[e] = f2bf(val);
 }
 
-// Workgroups are dealt to the 8 XCDs round robin; renumber them so that
-// consecutive logical tiles (which share input halos) run on one XCD and
-// share its L2.
-__device__ __forceinline__ int xcd_tile(int b, int n) { return (n & 7) ? b : (b & 7) * (n >> 3) + (b >> 3); }
-
 __device__ __forceinline__ bf8 as_bf8(u4 v) { return __builtin_bit_cast(bf8, v); }
+
+// four consecutive channels of one voxel; wide: the address is a multiple of
+// their size (a caller's buffer may start at any element)
+__device__ __forceinline__ void store4(unsigned short *o, f4 v, int wide)
+{
+    const u2 r = u2{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+    if (wide) {
+        *(u2 *)o = r;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = (unsigned short)(r[j >> 1] >> (16 * (j & 1)));
+    }
+}
+__device__ __forceinline__ void store4(float *o, f4 v, int wide)
+{
+    if (wide) {
+        *(f4 *)o = v;
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = v[j];
+    }
+}
 
 // --- 3x3x3 convolution (zero padding), LDS-staged MFMA implicit GEMM -------
 // in: BF16 [D][H][W][Ci]; wp: packed (K = Ci); bias FP32 [Co] or NULL;
 // act: 0 none, 1 LeakyReLU(slope).  out: BF16 or FP32 [D][H][W][Co].
-// A workgroup (4 wavefronts) owns a 16 (x) x 4 (y) x MT (z) output brick;
-// wavefront w owns the MT x-runs at y = y0 + w and NTS of the NTT 16-channel
-// output tiles (group blockIdx.y: tiles NTS blockIdx.y ...; small grids split
-// the output channels over several groups to fill the CUs).  Per 16-channel input chunk the 18 x 6 x (MT + 2) input halo is
-// staged in LDS once (two planes of 8 channels, so 16 lanes read 256
-// contiguous bytes) and serves all 27 taps; B fragments stream from the
-// packed weights (L2-resident).
-template <int MT, int NTS, typename To>
-__global__ __launch_bounds__(TPB) void k_conv3(const unsigned short *__restrict__ in, const u4 *__restrict__ wp,
-                                               const float *__restrict__ bias, To *__restrict__ out, int D, int H,
-                                               int W, int Ci, int act, float slope, int nbx, int nby, int nblk,
-                                               int NTT)
+// Work items: a 16 (x) x 8 (y) x MT (z) output brick times NTS of the NTT
+// 16-channel output tiles, times the 16-channel input chunks.  A workgroup (4
+// wavefronts; wavefront w owns the rows y0 + 2w, y0 + 2w + 1) walks its items
+// in a loop: the 18 x 10 x (MT + 2) input halo of the next item is requested
+// into registers before the current one is computed from LDS, so the matrix
+// cores do not wait for memory, and the weight fragments of a chunk (14 NTS,
+// one per tap pair) sit in registers.
+// Fragment reuse: a fragment is the voxels of one tap (lanes 0-31) and of the
+// next tap (lanes 32-63), so there are five kinds per halo row, by the place of
+// the first tap and the step to the second:
+//   P0, P1: x offset 0 or 1, next voxel;  Q: x offset 2, next row;
+//   R: x offset 2, next plane (taps 8, 9);  L: tap 26 and the zero tap.
+// A wavefront streams the halo planes and reads each kind of each of its four
+// halo rows once (15 LDS reads) for the up to 28 products of its two output
+// rows and three output planes; with a read per product the LDS bandwidth
+// bound the 16 -> 16 layers (24 us of a 128^3 launch against 12 us of MFMA).
+// Weights are the A operand, voxels the B operand: a lane then holds four
+// consecutive channels of one voxel and stores them with one instruction.
+// The product order of an output (chunks, then tap pairs) is that of the
+// packing, whatever MT and NTS.
+// Measured (one MI355X, launch): 16 -> 16 at 128^3 91 -> 47 us, 48 -> 16 200 ->
+// 130 us, 32 -> 32 at 64^3 31 -> 24 us; what is left is LDS reads (53 us of the
+// 130) and staging that only the other workgroup of the CU overlaps.  Loads
+// straight to LDS with three or four workgroups per CU and no prefetch: 65 and
+// 167 us; three workgroups per CU with the prefetch: 17-60 spilled registers,
+// 67 and 195 us.
+// Off: unsigned where a brick's halo spans less than 4 GiB of the input (each
+// access is then a wave-uniform base plus a 32-bit offset), else size_t.
+__device__ const u4 conv_zero = {0u, 0u, 0u, 0u};
+
+template <int MT, int NTS, typename To, typename Off>
+__global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restrict__ in, const u4 *__restrict__ wp,
+                                                  const float *__restrict__ bias, To *__restrict__ out, int D, int H,
+                                                  int W, int Ci, int act, float slope, int nbx, int nby, int ntile,
+                                                  int NTT, int wide)
 {
-    constexpr int XS = 18, YS = 6, ZS = MT + 2, NV = XS * YS * ZS;
-    __shared__ u4 tile[2 * NV];
-    int b = xcd_tile(blockIdx.x, nblk);
-    const int bx = b % nbx;
-    b /= nbx;
-    const int by = b % nby, bz = b / nby;
-    const int x0 = bx * 16, y0 = by * 4, z0 = bz * MT;
-    const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
+    constexpr int XS = 18, YS = 10, ZS = MT + 2, NV = XS * YS * ZS, NQ = 2 * NV, NCH = (NQ + TPB - 1) / TPB;
+    // two planes of 8 channels: the 16 lanes of a quarter of a fragment read
+    // read 256 contiguous bytes; a plane pitch of 8 (mod 16) items puts the two
+    // halves that neighbouring lanes stage on different banks
+    constexpr int NP = NV + (24 - NV % 16) % 16;
+    __shared__ u4 tile[2 * NP];
+    const int tid = threadIdx.x, l = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = l & 15, half = (l >> 4) & 1, tsel = l >> 5;
-    const int KC = Ci >> 4, nt0 = blockIdx.y * NTS;
-    f4 acc[MT][NTS];
+    const int KC = Ci >> 4, ngrp = NTT / NTS;
+    // tiles of this workgroup: first, stride, end.  Workgroups are dealt to the 8
+    // XCDs round robin; each XCD takes a contiguous range of tiles, which share
+    // input halos, so that they share its L2
+    int t = blockIdx.x, tstep = gridDim.x, tend = ntile;
+    if (((ntile | gridDim.x) & 7) == 0) {
+        const int per = ntile >> 3;
+        tend = ((t & 7) + 1) * per;
+        t = (t & 7) * per + (t >> 3);
+        tstep >>= 3;
+    }
+    // halo items of this thread (voxel q / 2, half q % 2): byte offset from the
+    // halo origin, and its place: bits 0-5 first / last x, y, z of the halo
+    // (bit 6: past the end)
+    Off rel[NCH];
+    unsigned edge[(NCH + 3) / 4] = {};
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+    for (int ch = 0; ch < NCH; ++ch) {
+        const int q = ch * TPB + tid, v = q >> 1, xt = v % XS, r = v / XS;
+        const int yt = r % YS, zt = r / YS;
+        rel[ch] = ((((Off)zt * H + yt) * W + xt) * Ci + (q & 1) * 8) * 2;
+        const unsigned e = (xt == 0) | (xt == XS - 1) << 1 | (yt == 0) << 2 | (yt == YS - 1) << 3 | (zt == 0) << 4 |
+                           (zt == ZS - 1) << 5 | (q >= NQ) << 6;
+        edge[ch >> 2] |= e << (8 * (ch & 3));
+    }
+    int x0, y0, z0, g;
+    auto origin = [&](int tt) {
+        g = tt % ngrp;
+        tt /= ngrp;
+        x0 = (tt % nbx) * 16;
+        tt /= nbx;
+        y0 = (tt % nby) * 8;
+        z0 = (tt / nby) * MT;
+    };
+    u4 st[NCH];
+    auto request = [&](int kc) {
+        const char *org = (const char *)(in + (((long)(z0 - 1) * H + (y0 - 1)) * W + (x0 - 1)) * Ci + kc * 16);
+        // which faces of the halo lie outside the grid; a ragged brick (more
+        // than its last face outside) compares coordinates.  Items outside
+        // read a zero, so that no load depends on a branch.
+        const bool ragged = x0 + 16 > W || y0 + 8 > H || z0 + MT > D;
+        unsigned ok = 0;
+        if (!ragged) {
+            const unsigned faces = (x0 == 0) | (x0 + 16 == W) << 1 | (y0 == 0) << 2 | (y0 + 8 == H) << 3 |
+                                   (z0 == 0) << 4 | (z0 + MT == D) << 5 | 1u << 6;
 #pragma unroll
-        for (int nt = 0; nt < NTS; ++nt) acc[i][nt] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int kc = 0; kc < KC; ++kc) {
-        if (kc) __syncthreads();
-        for (int q = tid; q < 2 * NV; q += TPB) {
-            const int hq = q & 1, v = q >> 1;
-            const int xt = v % XS, r = v / XS;
-            const int yt = r % YS, zt = r / YS;
-            const int x = x0 - 1 + xt, y = y0 - 1 + yt, z = z0 - 1 + zt;
-            u4 val = u4{0u, 0u, 0u, 0u};
-            if (x >= 0 && x < W && y >= 0 && y < H && z >= 0 && z < D)
-                val = *(const u4 *)(in + (((size_t)z * H + y) * W + x) * Ci + kc * 16 + hq * 8);
-            tile[hq * NV + v] = val;
+            for (int ch = 0; ch < NCH; ++ch)
+                ok |= (((edge[ch >> 2] >> (8 * (ch & 3))) & faces) == 0 ? 1u : 0u) << ch;
+        } else {
+#pragma unroll
+            for (int ch = 0; ch < NCH; ++ch) {
+                const int q = ch * TPB + tid, v = q >> 1, r = v / XS;
+                const int x = x0 - 1 + v % XS, y = y0 - 1 + r % YS, z = z0 - 1 + r / YS;
+                ok |= (q < NQ && (unsigned)x < (unsigned)W && (unsigned)y < (unsigned)H && (unsigned)z < (unsigned)D
+                           ? 1u : 0u) << ch;
+            }
+        }
+#pragma unroll
+        for (int ch = 0; ch < NCH; ++ch)
+            st[ch] = *(const u4 *)((ok >> ch) & 1 ? org + rel[ch] : (const char *)&conv_zero);
+    };
+    f4 acc[MT][2][NTS];
+    u4 bw[NTP][NTS];
+    const u4 *base0 = tile + half * NP + 2 * wv * XS + m;
+    const u4 *baseP = base0 + tsel, *baseQ = base0 + (XS - 2) * tsel + 2,
+             *baseR = base0 + (YS * XS - 2 * XS - 2) * tsel + 2, *baseL = base0 + 2;
+    u4 *put = tile + (tid & 1) * NP + (tid >> 1);
+    if (t >= tend) return;
+    origin(t);
+    request(0);
+    int kc = 0;
+    bool first = true;
+    for (;;) {
+        const int cx = x0, cy = y0, cz = z0, cg = g;
+        // weights first: their latency hides behind the staging (a workgroup
+        // whose every item has the same chunk and group keeps them)
+        if (first || KC > 1 || ngrp > 1) {
+            const u4 *wk = wp + ((size_t)kc * NTP * NTT + cg * NTS) * 64 + l;
+#pragma unroll
+            for (int tp = 0; tp < NTP; ++tp)
+#pragma unroll
+                for (int nt = 0; nt < NTS; ++nt) bw[tp][nt] = wk[(tp * NTT + nt) * 64];
+            first = false;
         }
         __syncthreads();
-        const u4 *wk = wp + ((size_t)kc * NTP * NTT + nt0) * 64 + l;
-        for (int tp = 0; tp < NTP; ++tp) {
-            const int tap = 2 * tp + tsel;
-            const int tt = tap < 27 ? tap : 13;
-            const int dz = tt / 9, dy = (tt / 3) % 3, dx = tt % 3;
-            const int base = half * NV + (dz * YS + wv + dy) * XS + m + dx;
-            bf8 a[MT];
 #pragma unroll
-            for (int i = 0; i < MT; ++i) {
-                u4 raw = tile[base + i * (YS * XS)];
-                if (tap >= 27) raw = u4{0u, 0u, 0u, 0u};
-                a[i] = as_bf8(raw);
+        for (int ch = 0; ch < NCH; ++ch)
+            if ((ch + 1) * TPB <= NQ || ch * TPB + tid < NQ) put[ch * (TPB / 2)] = st[ch];
+        if (kc == 0) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int yi = 0; yi < 2; ++yi)
+#pragma unroll
+                    for (int nt = 0; nt < NTS; ++nt) acc[i][yi][nt] = f4{0.f, 0.f, 0.f, 0.f};
+        }
+        // the next item
+        const bool last_kc = kc + 1 == KC;
+        const bool more = !last_kc || t + tstep < tend;
+        if (more) {
+            if (last_kc) {
+                t += tstep;
+                origin(t);
+                kc = 0;
+            } else {
+                ++kc;
             }
+            request(kc);
+        }
+        __syncthreads();
+        // the fragments of step (plane zz, k) are read one step ahead of its
+        // products, so that LDS latency hides behind them (left to itself the
+        // compiler reads each pair just before its use and waits)
+        bf8 P0[2][4], P1[2][4], Q[2][3], R[2][2], L[2][2];
+        auto row = [&](const u4 *b, int zz, int r, int dx) { return as_bf8(b[(zz * YS + r) * XS + dx]); };
+        auto fetch = [&](int zz, int k) {
+            const bool d0 = zz < MT, d1 = zz >= 1 && zz <= MT, d2 = zz >= 2;
+            const int u = zz & 1;
+            if (k == 0) {
+                if (d0 || d2) P0[u][0] = row(baseP, zz, 0, 0);
+                P0[u][1] = row(baseP, zz, 1, 0);
+                if (d1) P1[u][0] = row(baseP, zz, 0, 1);
+                P1[u][1] = row(baseP, zz, 1, 1);
+            } else if (k == 1) {
+                if (d0 || d2) Q[u][0] = row(baseQ, zz, 0, 0);
+                Q[u][1] = row(baseQ, zz, 1, 0);
+                P0[u][2] = row(baseP, zz, 2, 0);
+            } else if (k == 2) {
+                P1[u][2] = row(baseP, zz, 2, 1);
+                if (d1) Q[u][2] = row(baseQ, zz, 2, 0);
+            } else if (k == 3) {
+                if (d0 || d2) P0[u][3] = row(baseP, zz, 3, 0);
+                if (d1) P1[u][3] = row(baseP, zz, 3, 1);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    if (d0) R[u][r] = row(baseR, zz, 2 + r, 0);
+                    if (d2) L[u][r] = row(baseL, zz, 2 + r, 0);
+                }
+            }
+        };
+        fetch(0, 0);
+#pragma unroll
+        for (int zk = 0; zk < 5 * (MT + 2); ++zk) {
+            const int zz = zk / 5, k = zk % 5, u = zz & 1;
+            const bool d0 = zz < MT, d1 = zz >= 1 && zz <= MT, d2 = zz >= 2;
+            if (zk + 1 < 5 * (MT + 2)) fetch((zk + 1) / 5, (zk + 1) % 5);
+            __builtin_amdgcn_sched_barrier(0);
+            // tap pairs 0-4, 5-8 and 9-13 of the output planes zz, zz - 1 and zz - 2
+#pragma unroll
+            for (int yi = 0; yi < 2; ++yi) {
+                const bf8 a02 = k == 0 ? P0[u][yi] : k == 1 ? Q[u][yi] : k == 2 ? P1[u][yi + 1] : P0[u][yi + 2];
+                const bf8 a1 = k == 0 ? P1[u][yi] : k == 1 ? P0[u][yi + 1] : k == 2 ? Q[u][yi + 1] : P1[u][yi + 2];
+                bf8 al = a02;
+                if (k == 4 && d2) {
+                    u4 raw = __builtin_bit_cast(u4, L[u][yi]);
+                    if (tsel) raw = u4{0u, 0u, 0u, 0u};   // tap 27 does not exist
+                    al = as_bf8(raw);
+                }
+#pragma unroll
+                for (int nt = 0; nt < NTS; ++nt) {
+                    auto mac = [&](int i, int tp, bf8 v) {
+                        acc[i][yi][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(bw[tp][nt]), v,
+                                                                                 acc[i][yi][nt], 0, 0, 0);
+                    };
+                    if (d0) mac(d0 ? zz : 0, k, k == 4 ? R[u][yi] : a02);
+                    if (d1 && k < 4) mac(d1 ? zz - 1 : 0, 5 + (k & 3), a1);
+                    if (d2) mac(d2 ? zz - 2 : 0, 9 + k, al);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (last_kc) {
+            // D[m][n]: n = l % 16 (voxel along x), m = 4 (l / 16) + j (channel);
+            // row bases are wave-uniform
+            const int Co = NTT * 16, cl = 4 * (l >> 4), lo = m * Co + cl;
 #pragma unroll
             for (int nt = 0; nt < NTS; ++nt) {
-                const bf8 bw = as_bf8(wk[(tp * NTT + nt) * 64]);
+                const int co = (cg * NTS + nt) * 16;
+                f4 bb = f4{0.f, 0.f, 0.f, 0.f};
+                if (bias) bb = f4{bias[co + cl], bias[co + cl + 1], bias[co + cl + 2], bias[co + cl + 3]};
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
-                    acc[i][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], bw, acc[i][nt], 0, 0, 0);
+#pragma unroll
+                    for (int yi = 0; yi < 2; ++yi) {
+                        const int z = cz + i, y = cy + 2 * wv + yi;
+                        if (y >= H || z >= D) continue;
+                        f4 v = acc[i][yi][nt] + bb;
+                        if (act) {
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) v[j] = v[j] > 0.f ? v[j] : slope * v[j];
+                        }
+                        To *row = out + (((size_t)z * H + y) * W + cx) * Co + co;
+                        if (cx + m < W) store4(row + lo, v, wide);
+                    }
             }
         }
-    }
-    // D[m][n]: n = l % 16 (channel), m = 4 (l / 16) + j (voxel along x)
-    const int Co = NTT * 16, n = l & 15, xq = x0 + 4 * (l >> 4), y = y0 + wv;
-    if (y >= H) return;
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-        const int z = z0 + i;
-        if (z >= D) continue;
-#pragma unroll
-        for (int nt = 0; nt < NTS; ++nt) {
-            const int co = (nt0 + nt) * 16 + n;
-            const float bb = bias ? bias[co] : 0.f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int x = xq + j;
-                if (x >= W) continue;
-                float v = acc[i][nt][j] + bb;
-                if (act) v = v > 0.f ? v : slope * v;
-                const size_t o = (((size_t)z * H + y) * W + x) * Co + co;
-                if constexpr (sizeof(To) == 2) out[o] = f2bf(v);
-                else out[o] = v;
-            }
-        }
+        if (!more) break;
     }
 }
 
@@ -594,62 +771,38 @@ void nn_pack_weights(const float *w, unsigned short *out, int Ci, int Co, int fl
     hipLaunchKernelGGL(k_pack_w, dim3(nblk(nn_packed_weight_elems(Ci, Co))), dim3(TPB), 0, s, w, out, Ci, Co, flip);
 }
 
-// NTS of the NT output tiles per workgroup, NT / NTS workgroup groups
-template <int MT, int NTS, typename To>
+template <int MT, int NTS, typename To, typename Off = unsigned>
 static void conv3_launch(const unsigned short *in, const void *wp, const float *bias, To *out, int D, int H, int W,
                          int Ci, int NT, int act, float slope, hipStream_t s)
 {
-    const int nbx = (W + 15) / 16, nby = (H + 3) / 4, nbz = (D + MT - 1) / MT;
-    const int nb = nbx * nby * nbz;
-    hipLaunchKernelGGL((k_conv3<MT, NTS, To>), dim3(nb, NT / NTS), dim3(TPB), 0, s, in, (const u4 *)wp, bias, out, D,
-                       H, W, Ci, act, slope, nbx, nby, nb, NT);
+    const int nbx = (W + 15) / 16, nby = (H + 7) / 8, nbz = (D + MT - 1) / MT;
+    const int ntile = nbx * nby * nbz * (NT / NTS);
+    const int wide = ((uintptr_t)out % (4 * sizeof(To))) == 0;
+    // two resident workgroups per CU (of 160-250 VGPRs) walk the tiles
+    const int grid = ntile < 512 ? ntile : 512;
+    hipLaunchKernelGGL((k_conv3<MT, NTS, To, Off>), dim3(grid), dim3(TPB), 0, s, in, (const u4 *)wp, bias, out, D, H, W,
+                       Ci, act, slope, nbx, nby, ntile, NT, wide);
 }
 
-// all NT tiles per workgroup when the bricks alone give 512 workgroups (two
-// per CU); otherwise the output channels are split over groups of 2 or 1
-// tiles (the input halo of a brick is then staged once per group)
-template <int MT, int NT, typename To>
-static void conv3_split(const unsigned short *in, const void *wp, const float *bias, To *out, int D, int H, int W,
-                        int Ci, int act, float slope, hipStream_t s)
-{
-    const int nb = ((W + 15) / 16) * ((H + 3) / 4) * ((D + MT - 1) / MT);
-    if constexpr (MT == 1 && NT == 12) {
-        // one output row per wavefront uses each streamed B fragment once;
-        // two rows of 6 tiles in two groups use it twice for the same
-        // accumulator count
-        if (nb >= 512) {
-            conv3_launch<2, 6, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
-            return;
-        }
-    }
-    if (nb >= 512 || NT == 1) {
-        conv3_launch<MT, NT, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
-        return;
-    }
-    if constexpr (NT % 2 == 0) {
-        if (nb * (NT / 2) >= 512) {
-            conv3_launch<MT, 2, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
-            return;
-        }
-    }
-    conv3_launch<MT, 1, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
-}
-
-// output rows per wavefront (MT) chosen so that MT * NT accumulator tiles stay near 16
+// The largest brick and output split that still give two workgroups per CU;
+// below that, the smallest (the halo of a brick is staged once per output
+// group, so fewer groups where the bricks alone fill the chip).
 template <typename To>
 static void conv3_dispatch(const unsigned short *in, const void *wp, const float *bias, To *out, int D, int H, int W,
                            int Ci, int Co, int act, float slope, hipStream_t s)
 {
-    switch (Co / 16) {
-    case 1: conv3_split<8, 1, To>(in, wp, bias, out, D, H, W, Ci, act, slope, s); break;
-    case 2: conv3_split<8, 2, To>(in, wp, bias, out, D, H, W, Ci, act, slope, s); break;
-    case 3: conv3_split<4, 3, To>(in, wp, bias, out, D, H, W, Ci, act, slope, s); break;
-    case 4: conv3_split<4, 4, To>(in, wp, bias, out, D, H, W, Ci, act, slope, s); break;
-    case 6: conv3_split<2, 6, To>(in, wp, bias, out, D, H, W, Ci, act, slope, s); break;
-    case 8: conv3_split<2, 8, To>(in, wp, bias, out, D, H, W, Ci, act, slope, s); break;
-    case 12: conv3_split<1, 12, To>(in, wp, bias, out, D, H, W, Ci, act, slope, s); break;
-    default: break;
-    }
+    const int NT = Co / 16;
+    auto tiles = [&](int mt, int nts) { return ((W + 15) / 16) * ((H + 7) / 8) * ((D + mt - 1) / mt) * (NT / nts); };
+    if ((6.0 * H + 10.0) * W * Ci * 2.0 >= 4294967296.0)
+        conv3_launch<1, 1, To, size_t>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
+    else if (NT % 2 == 0 && tiles(2, 2) >= 512)
+        conv3_launch<2, 2, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
+    else if (tiles(4, 1) >= 512)
+        conv3_launch<4, 1, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
+    else if (tiles(2, 1) >= 512)
+        conv3_launch<2, 1, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
+    else
+        conv3_launch<1, 1, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
 }
 
 void nn_conv3(const unsigned short *in, const void *wp, const float *bias, void *out, int out_f32, int D, int H, int W,

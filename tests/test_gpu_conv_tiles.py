@@ -1,0 +1,69 @@
+"""The convolution's tilings (brick depth, output tiles per workgroup, walked
+tiles beyond the resident workgroups) at sizes that no brick divides, against
+the FP64 layer oracle fed the same BF16 operands: products of BF16 values are
+exact in FP32, so only the accumulation order differs (1e-5, as for every other
+layer size).  An output that starts at any element holds the same values."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+from oracle.net_oracle import bf16_round
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _bf16(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda().to(torch.bfloat16)
+
+
+def _rel(t, ref):
+    a = t.detach().float().cpu().numpy().astype(np.float64)
+    return float(np.linalg.norm(np.ravel(a - ref)) / np.linalg.norm(np.ravel(ref)))
+
+
+# (36, 70, 130): 729 tiles of depth 4; (33, 60, 70): 680 of depth 2; (22, 50,
+# 100) to 32 channels: 539 of two output tiles; (9, 17, 33) to 48 and 64: depth
+# 1 with output groups; (1, 1, 1), (2, 9, 17): less than a brick
+@pytest.mark.parametrize("shape,ci,co", [((36, 70, 130), 16, 16), ((33, 60, 70), 32, 16), ((22, 50, 100), 16, 32),
+                                         ((9, 17, 33), 16, 48), ((9, 17, 33), 48, 64), ((1, 1, 1), 16, 16),
+                                         ((2, 9, 17), 32, 32)])
+def test_conv3_tilings_against_oracle(shape, ci, co):
+    from paper_2209_08189_amd.claire import nn_conv3
+    r = np.random.default_rng(sum(shape) + ci + co)
+    x = bf16_round(r.standard_normal(shape + (ci,)))
+    w = r.standard_normal((27, ci, co)) / np.sqrt(27 * ci)
+    b = r.standard_normal(co)
+    wt = torch.from_numpy(w.astype(np.float32)).cuda()
+    out = nn_conv3(_bf16(x), wt, torch.from_numpy(b.astype(np.float32)).cuda(), act=0)
+    assert _rel(out, oracle.conv3(x, bf16_round(w), b.astype(np.float32).astype(np.float64))) < 1e-5
+
+
+@pytest.mark.parametrize("f32", [True, False])
+def test_conv3_output_at_any_element(f32):
+    from paper_2209_08189_amd import claire
+    shape, ci, co = (3, 9, 20), 16, 32
+    g = torch.Generator().manual_seed(3)
+    x = torch.randn(shape + (ci,), generator=g).cuda().to(torch.bfloat16)
+    w, b = torch.randn((27, ci, co), generator=g).cuda(), torch.randn(co, generator=g).cuda()
+    ref = claire.nn_conv3(x, w, b, out_f32=f32)
+    n = ref.numel()
+    buf = torch.zeros(n + 8, dtype=ref.dtype, device="cuda")
+    wpack = torch.empty(28 * ci * co * 2, dtype=torch.uint8, device="cuda")
+    for off in (1, 2, 3):
+        buf.zero_()
+        at = ctypes.c_void_p(buf.data_ptr() + off * buf.element_size())
+        st = claire.lib().cl_nn_conv3(claire._ptr(x), claire._ptr(w), claire._ptr(b), at, int(f32), *shape, ci, co, 1,
+                                      0.2, 0, claire._ptr(wpack),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == 0
+        assert torch.equal(buf[off:off + n], ref.reshape(-1))
+        assert not buf[:off].any() and not buf[off + n:].any()
