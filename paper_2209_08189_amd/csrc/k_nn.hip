@@ -11,6 +11,7 @@
 // backward data pass is the same convolution with flipped taps and swapped
 // channel roles, i.e. the same kernel with a differently packed weight.
 #include "internal.h"
+#include "nn.h"
 
 namespace clh {
 
@@ -104,8 +105,10 @@ __device__ __forceinline__ void store4(float *o, f4 v, int wide)
 }
 
 // --- 3x3x3 convolution (zero padding), LDS-staged MFMA implicit GEMM -------
-// in: BF16 [D][H][W][Ci]; wp: packed (K = Ci); bias FP32 [Co] or NULL;
-// act: 0 none, 1 LeakyReLU(slope).  out: BF16 or FP32 [D][H][W][Co].
+// in: BF16, voxels in order vs elements apart and 16-channel chunks cs elements
+// apart (Layout; channels last: Ci and 16); wp: packed (K = Ci); bias FP32 [Co]
+// or NULL; act: 0 none, 1 LeakyReLU(slope).  out: BF16 or FP32, laid out
+// likewise.
 // Work items: a 16 (x) x 8 (y) x MT (z) output brick times NTS of the NTT
 // 16-channel output tiles, times the 16-channel input chunks.  A workgroup (4
 // wavefronts; wavefront w owns the rows y0 + 2w, y0 + 2w + 1) walks its items
@@ -138,9 +141,9 @@ __device__ const u4 conv_zero = {0u, 0u, 0u, 0u};
 
 template <int MT, int NTS, typename To, typename Off>
 __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restrict__ in, const u4 *__restrict__ wp,
-                                                  const float *__restrict__ bias, To *__restrict__ out, int D, int H,
-                                                  int W, int Ci, int act, float slope, int nbx, int nby, int ntile,
-                                                  int NTT, int wide)
+                                                  const float *__restrict__ bias, To *__restrict__ out,
+                                                  NNLayout li, NNLayout lo, int D, int H, int W, int Ci, int act,
+                                                  float slope, int nbx, int nby, int ntile, int NTT, int wide)
 {
     constexpr int XS = 18, YS = 10, ZS = MT + 2, NV = XS * YS * ZS, NQ = 2 * NV, NCH = (NQ + TPB - 1) / TPB;
     // two planes of 8 channels: the 16 lanes of a quarter of a fragment read
@@ -170,7 +173,7 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
     for (int ch = 0; ch < NCH; ++ch) {
         const int q = ch * TPB + tid, v = q >> 1, xt = v % XS, r = v / XS;
         const int yt = r % YS, zt = r / YS;
-        rel[ch] = ((((Off)zt * H + yt) * W + xt) * Ci + (q & 1) * 8) * 2;
+        rel[ch] = ((((Off)zt * H + yt) * W + xt) * li.vs + (q & 1) * 8) * 2;
         const unsigned e = (xt == 0) | (xt == XS - 1) << 1 | (yt == 0) << 2 | (yt == YS - 1) << 3 | (zt == 0) << 4 |
                            (zt == ZS - 1) << 5 | (q >= NQ) << 6;
         edge[ch >> 2] |= e << (8 * (ch & 3));
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
     };
     u4 st[NCH];
     auto request = [&](int kc) {
-        const char *org = (const char *)(in + (((long)(z0 - 1) * H + (y0 - 1)) * W + (x0 - 1)) * Ci + kc * 16);
+        const char *org = (const char *)(in + (((long)(z0 - 1) * H + (y0 - 1)) * W + (x0 - 1)) * li.vs + kc * (long)li.cs);
         // which faces of the halo lie outside the grid; a ragged brick (more
         // than its last face outside) compares coordinates.  Items outside
         // read a zero, so that no load depends on a branch.
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
         if (last_kc) {
             // D[m][n]: n = l % 16 (voxel along x), m = 4 (l / 16) + j (channel);
             // row bases are wave-uniform
-            const int Co = NTT * 16, cl = 4 * (l >> 4), lo = m * Co + cl;
+            const int cl = 4 * (l >> 4), lane_off = m * lo.vs + cl;
 #pragma unroll
             for (int nt = 0; nt < NTS; ++nt) {
                 const int co = (cg * NTS + nt) * 16;
@@ -342,8 +345,8 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
 #pragma unroll
                             for (int j = 0; j < 4; ++j) v[j] = v[j] > 0.f ? v[j] : slope * v[j];
                         }
-                        To *row = out + (((size_t)z * H + y) * W + cx) * Co + co;
-                        if (cx + m < W) store4(row + lo, v, wide);
+                        To *row = out + (((size_t)z * H + y) * W + cx) * lo.vs + (cg * NTS + nt) * lo.cs;
+                        if (cx + m < W) store4(row + lane_off, v, wide);
                     }
             }
         }
@@ -353,150 +356,206 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
 
 // --- weight gradient --------------------------------------------------------
 // part[chunk] = (gw partial [t][Ci][Co], gb partial [Co]): sums over the
-// chunk's voxels p of X[p + t - 1][i] dZ[p][o] and of dZ[p][o].  GEMM with M = 16 input channels
-// (one chunk kc), N = 16 output channels, K = 32 voxels.  A workgroup owns
-// one 16-channel input chunk, NG output tiles and a run of 16 x 4 x 2
-// voxel tiles.  Per tile, X (with a one-voxel halo) is staged in LDS
-// transposed to [channel][z][y][x] in three copies shifted by dx = -1, 0, 1,
-// so each A fragment (8 consecutive x of one channel) is one aligned 16-byte
-// read, and dZ is staged transposed to [channel][row][x]; the dZ fragments
-// are loaded once per tile and serve every tap.  Wavefront w owns the taps
-// t = w (mod 4); the bias sums use an all-ones A operand.
-// K index (lane group g = l / 16, item j): row 2 s + g / 2 of the tile
-// (row = 4 z + y), x = 8 (g % 2) + j, for K step s = 0..3.
-template <int NG>
-__global__ __launch_bounds__(TPB) void k_conv3_dw(const unsigned short *__restrict__ X,
-                                                  const unsigned short *__restrict__ dZ, float *__restrict__ part,
-                                                  int D, int H, int W, int Ci, int Co, int ntx, int nty, int ntiles,
-                                                  int tpc, int ngrp)
+// chunk's voxels p of X[p + t - 1][i] dZ[p][o] and of dZ[p][o].  GEMM with
+// M = 16 input channels (chunk kc), N = 16 output channels (tile ct), K = 32
+// voxels: two rows of 16 x; lane group g = l / 16, item j holds row g / 2,
+// x = 8 (g % 2) + j.
+// A workgroup owns one (kc, ct) pair and a run of 16 (x) x 4 (y) x 4 (z) voxel
+// tiles.  The x shift of a tap is taken on dZ, so X is staged without an x halo
+// (16 x 6 x 6 voxels) and dZ with one (18 x 4 x 4); both go straight to LDS as
+// they lie in memory, and the transposing LDS read (ds_read_b64_tr_b16: lane i
+// of 16 receives channel i of 4 voxels) forms the fragments.  Two buffers: the
+// next tile is in flight while the current one is computed.
+// Wavefront w owns two rows of two planes and all 27 taps (108 accumulators):
+// 12 X fragments and 6 dZ fragments serve 54 products, a third of an LDS read
+// per product.  The wavefronts' sums are added in order at the end; the bias
+// sums use an all-ones X operand.
+// Measured (one MI355X, with the sum of the partials): 16 -> 16 at 128^3 165 ->
+// 48 us, 48 -> 16 359 -> 120 us (channels last).  Before, X was transposed into three shifted
+// copies by 2-byte LDS writes (24 per staged 16 bytes).
+typedef short s4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s4 lds_s4;
+typedef __attribute__((address_space(3))) void lds_void;
+
+// fragment of 8 voxels 32 bytes apart from LDS byte address a (of this lane)
+__device__ __forceinline__ bf8 frag_tr(unsigned a)
 {
-    constexpr int XR = 4 * 6;                 // staged X rows: z in [z0-1, z0+2], y in [y0-1, y0+4]
-    // channel planes padded by 16 bytes: a plane pitch of 4 (mod 8) words puts
-    // the 16-byte A / B fragment reads of the 16 channel lanes on distinct
-    // banks (an unpadded pitch, a multiple of 64 words, sent all 16 to the
-    // same four banks)
-    constexpr int XP = XR * 16 + 8, ZP = 8 * 16 + 8;   // plane pitches in 16-bit elements
-    __shared__ __attribute__((aligned(16))) unsigned short xs[3][16][XP];
-    __shared__ __attribute__((aligned(16))) unsigned short zs[NG * 16][ZP];
-    const int tid = threadIdx.x, l = tid & 63, wv = tid >> 6;
+    struct {
+        s4 lo, hi;
+    } f;
+    f.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)a);
+    f.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4 *)(uintptr_t)(a + 128));
+    return __builtin_bit_cast(bf8, f);
+}
+
+__global__ __launch_bounds__(TPB, 2) void k_conv3_dw(const unsigned short *__restrict__ X,
+                                                     const unsigned short *__restrict__ dZ, float *__restrict__ part,
+                                                     NNLayout lx, NNLayout lz, int D, int H, int W, int Ci, int Co,
+                                                     int ntx, int nty, int ntiles, int tpc)
+{
+    constexpr int XQ = 16 * 6 * 6 * 2, ZQ = 18 * 4 * 4 * 2, NCH = (XQ + ZQ + TPB - 1) / TPB, BUF = NCH * TPB;
+    __shared__ u4 tile[2 * BUF];
+    const int tid = threadIdx.x, l = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = l >> 4, ln = l & 15;
-    const int KC = Ci >> 4;
-    int bq = blockIdx.x;
-    const int grp = bq % ngrp;
-    bq /= ngrp;
-    const int kc = bq % KC, chunk = bq / KC;
-    const int co0 = grp * NG * 16;
+    const int KC = Ci >> 4, npair = KC * (Co >> 4);
+    // the pairs of a run of tiles share its data: consecutive on one XCD
+    int b = blockIdx.x;
+    const int nb = gridDim.x;
+    if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+    const int pair = b % npair, chunk = b / npair;
+    const int kc = pair % KC, ct = pair / KC;
     const int t0 = chunk * tpc, t1 = min(ntiles, t0 + tpc);
-    f4 acc[7][NG], accb[NG];
+    // items of this thread: [voxel][half] of X, then of dZ; byte offset from the
+    // tile's first voxel in its tensor, and place (bits 0-5: first / last x, y,
+    // z of a halo; bit 6: past the end)
+    long rel[NCH];
+    unsigned edge[(NCH + 3) / 4] = {};
 #pragma unroll
-    for (int i = 0; i < 7; ++i)
+    for (int ch = 0; ch < NCH; ++ch) {
+        const int q = ch * TPB + tid;
+        const bool isx = q < XQ;
+        const int v = (isx ? q : q - XQ) >> 1, xt = isx ? v & 15 : v % 18, r = isx ? v >> 4 : v / 18;
+        const int yt = isx ? r % 6 : r & 3, zt = isx ? r / 6 : r >> 2;
+        const int vs = isx ? lx.vs : lz.vs;
+        rel[ch] = ((((long)zt * H + yt) * W + xt) * vs + (q & 1) * 8) * 2;
+        const unsigned e = isx ? (yt == 0) << 2 | (yt == 5) << 3 | (zt == 0) << 4 | (zt == 5) << 5
+                               : (xt == 0) | (xt == 17) << 1 | (q >= XQ + ZQ) << 6;
+        edge[ch >> 2] |= e << (8 * (ch & 3));
+    }
+    auto request = [&](int tI, int buf) {
+        const int x0 = (tI % ntx) * 16, y0 = ((tI / ntx) % nty) * 4, z0 = (tI / (ntx * nty)) * 4;
+        const char *xo = (const char *)(X + (((long)(z0 - 1) * H + (y0 - 1)) * W + x0) * lx.vs + kc * (long)lx.cs);
+        const char *zo = (const char *)(dZ + (((long)z0 * H + y0) * W + (x0 - 1)) * lz.vs + ct * (long)lz.cs);
+        unsigned ok = 0;
+        if (x0 + 16 <= W && y0 + 4 <= H && z0 + 4 <= D) {
+            const unsigned faces = (x0 == 0) | (x0 + 16 == W) << 1 | (y0 == 0) << 2 | (y0 + 4 == H) << 3 |
+                                   (z0 == 0) << 4 | (z0 + 4 == D) << 5 | 1u << 6;
 #pragma unroll
-        for (int nt = 0; nt < NG; ++nt) acc[i][nt] = f4{0.f, 0.f, 0.f, 0.f};
+            for (int ch = 0; ch < NCH; ++ch)
+                ok |= (((edge[ch >> 2] >> (8 * (ch & 3))) & faces) == 0 ? 1u : 0u) << ch;
+        } else {
 #pragma unroll
-    for (int nt = 0; nt < NG; ++nt) accb[nt] = f4{0.f, 0.f, 0.f, 0.f};
-    const bool do_bias = kc == 0 && wv == 3;
-    for (int tI = t0; tI < t1; ++tI) {
-        const int tx = tI % ntx, ty = (tI / ntx) % nty, tz = tI / (ntx * nty);
-        const int x0 = tx * 16, y0 = ty * 4, z0 = tz * 2;
-        __syncthreads();
-        // X halo: 18 x 6 x 4 voxels x 16 channels, two 8-channel halves each
-        for (int q = tid; q < 18 * XR * 2; q += TPB) {
-            const int hq = q & 1, v = q >> 1;
-            const int xt = v % 18, r = v / 18;      // r = zt * 6 + yt
-            const int yt = r % 6, zt = r / 6;
-            const int x = x0 - 1 + xt, y = y0 - 1 + yt, z = z0 - 1 + zt;
-            u4 val = u4{0u, 0u, 0u, 0u};
-            if (x >= 0 && x < W && y >= 0 && y < H && z >= 0 && z < D)
-                val = *(const u4 *)(X + (((size_t)z * H + y) * W + x) * Ci + kc * 16 + hq * 8);
-            const unsigned short *e = (const unsigned short *)&val;
-#pragma unroll
-            for (int sx = 0; sx < 3; ++sx) {
-                const int xc = xt - sx;             // copy sx holds X[x0 + xc + sx - 1]
-                if (xc < 0 || xc >= 16) continue;
-#pragma unroll
-                for (int c = 0; c < 8; ++c) xs[sx][hq * 8 + c][r * 16 + xc] = e[c];
+            for (int ch = 0; ch < NCH; ++ch) {
+                const int q = ch * TPB + tid;
+                const bool isx = q < XQ;
+                const int v = (isx ? q : q - XQ) >> 1, r = isx ? v >> 4 : v / 18;
+                const int x = isx ? x0 + (v & 15) : x0 - 1 + v % 18, y = isx ? y0 - 1 + r % 6 : y0 + (r & 3),
+                          z = isx ? z0 - 1 + r / 6 : z0 + (r >> 2);
+                ok |= (q < XQ + ZQ && (unsigned)x < (unsigned)W && (unsigned)y < (unsigned)H && (unsigned)z < (unsigned)D
+                           ? 1u : 0u) << ch;
             }
         }
-        // dZ tile: 16 x 4 x 2 voxels x NG * 16 channels
-        for (int q = tid; q < 128 * NG * 2; q += TPB) {
-            const int hq = q % (NG * 2), v = q / (NG * 2);
-            const int xt = v & 15, r = v >> 4;      // r = zl * 4 + yl
-            const int x = x0 + xt, y = y0 + (r & 3), z = z0 + (r >> 2);
-            u4 val = u4{0u, 0u, 0u, 0u};
-            if (x < W && y < H && z < D)
-                val = *(const u4 *)(dZ + (((size_t)z * H + y) * W + x) * Co + co0 + hq * 8);
-            const unsigned short *e = (const unsigned short *)&val;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) zs[hq * 8 + c][r * 16 + xt] = e[c];
+        for (int ch = 0; ch < NCH; ++ch) {
+            const char *src = (ch * TPB + tid < XQ ? xo : zo) + rel[ch];
+            __builtin_amdgcn_global_load_lds((const void *)((ok >> ch) & 1 ? src : (const char *)&conv_zero),
+                                             (lds_void *)(tile + buf * BUF + ch * TPB + wv * 64), 16, 0, 0);
         }
+    };
+    f4 acc[27], accb = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 27; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+    const bool do_bias = kc == 0;
+    // rows yp, yp + 1 of planes zb, zb + 1
+    const int yp = (wv & 1) * 2, zb = (wv >> 1) * 2;
+    const unsigned lds0 = (unsigned)(uintptr_t)(lds_void *)tile;
+    const unsigned ax = lds0 + (((zb * 6 + yp + (g >> 1)) * 16 + 8 * (g & 1) + (ln >> 2)) * 32 + (ln & 3) * 8);
+    const unsigned az = lds0 + XQ * 16 + (((zb * 4 + yp + (g >> 1)) * 18 + 8 * (g & 1) + (ln >> 2)) * 32 + (ln & 3) * 8);
+    if (t0 < t1) request(t0, 0);
+    for (int tI = t0; tI < t1; ++tI) {
+        const int buf = (tI - t0) & 1;
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        bf8 bz[NG][4];
+        // every fragment first, then the request: an LDS read after it would
+        // wait for it (the compiler does not tell the two buffers apart)
+        const unsigned bo = buf * BUF * 16;
+        bf8 bz[2][3], a[12];
 #pragma unroll
-        for (int nt = 0; nt < NG; ++nt)
+        for (int zi = 0; zi < 2; ++zi)
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                bz[nt][s] = as_bf8(*(const u4 *)&zs[nt * 16 + ln][(2 * s + (g >> 1)) * 16 + 8 * (g & 1)]);
+            for (int dx = 0; dx < 3; ++dx) bz[zi][dx] = frag_tr(az + bo + ((zi * 4) * 18 + 2 - dx) * 32);
 #pragma unroll
-        for (int ti = 0; ti < 7; ++ti) {
-            const int t = wv + 4 * ti;
-            if (t >= 27) break;
-            const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
+        for (int s = 0; s < 12; ++s) a[s] = frag_tr(ax + bo + ((s / 3) * 6 + s % 3) * 512);
+        __builtin_amdgcn_sched_barrier(0);
+        if (tI + 1 < t1) request(tI + 1, buf ^ 1);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int row = 2 * s + (g >> 1);               // 4 zl + yl
-                const int r = ((row >> 2) + dz) * 6 + (row & 3) + dy;
-                const bf8 a = as_bf8(*(const u4 *)&xs[dx][ln][r * 16 + 8 * (g & 1)]);
+        for (int s = 0; s < 12; ++s) {
+            const int zq = s / 3, dy = s % 3;
 #pragma unroll
-                for (int nt = 0; nt < NG; ++nt)
-                    acc[ti][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bz[nt][s], acc[ti][nt], 0, 0, 0);
+            for (int zi = 0; zi < 2; ++zi) {
+                const int dz = zq - zi;
+                if (dz < 0 || dz > 2) continue;
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    acc[dz * 9 + dy * 3 + dx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], bz[zi][dx],
+                                                                                       acc[dz * 9 + dy * 3 + dx], 0, 0, 0);
             }
         }
         if (do_bias) {
-            const u4 ones4 = u4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
-            const bf8 ones = as_bf8(ones4);
+            const bf8 ones = as_bf8(u4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int nt = 0; nt < NG; ++nt)
-                    accb[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, bz[nt][s], accb[nt], 0, 0, 0);
+            for (int zi = 0; zi < 2; ++zi) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, bz[zi][1], accb, 0, 0, 0);
         }
     }
+    // sum over the wavefronts: 2 and 3 into 0 and 1, then 1 into 0
+    f4 *red = (f4 *)tile;                 // two regions of 28 x 64 values (28 KB each)
+#pragma unroll
+    for (int half = 2; half >= 1; half >>= 1) {
+        __syncthreads();
+        if (wv >= half && wv < 2 * half) {
+#pragma unroll
+            for (int t = 0; t < 27; ++t) red[((wv - half) * 28 + t) * 64 + l] = acc[t];
+            red[((wv - half) * 28 + 27) * 64 + l] = accb;
+        }
+        __syncthreads();
+        if (wv < half) {
+#pragma unroll
+            for (int t = 0; t < 27; ++t) acc[t] += red[(wv * 28 + t) * 64 + l];
+            accb += red[(wv * 28 + 27) * 64 + l];
+        }
+    }
+    if (wv != 0) return;
     // D[m][n]: m = 4 g + j (input channel), n = ln (output channel)
+    float *dst = part + (size_t)chunk * (27 * Ci * Co + Co);
 #pragma unroll
-    for (int ti = 0; ti < 7; ++ti) {
-        const int t = wv + 4 * ti;
-        if (t >= 27) break;
-        float *dst = part + (size_t)chunk * (27 * Ci * Co + Co) + (size_t)t * Ci * Co;
+    for (int t = 0; t < 27; ++t)
 #pragma unroll
-        for (int nt = 0; nt < NG; ++nt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                dst[(size_t)(kc * 16 + 4 * g + j) * Co + co0 + nt * 16 + ln] = acc[ti][nt][j];
-    }
-    if (do_bias && g == 0) {
-#pragma unroll
-        for (int nt = 0; nt < NG; ++nt) part[(size_t)chunk * (27 * Ci * Co + Co) + 27 * Ci * Co + co0 + nt * 16 + ln] = accb[nt][0];
-    }
+        for (int j = 0; j < 4; ++j) dst[((size_t)t * Ci + kc * 16 + 4 * g + j) * Co + ct * 16 + ln] = acc[t][j];
+    if (do_bias && g == 0) dst[27 * (size_t)Ci * Co + ct * 16 + ln] = accb[0];
 }
 
 // Fixed-order sum of the chunk partials: row c of partial holds nw weight
 // values then nb bias values (row stride nw + nb).  A workgroup owns 64
-// consecutive outputs; wave w sums the chunks c = w (mod 4) in order, then
-// the four wave sums are added in order.
-__global__ __launch_bounds__(TPB) void k_sum_partials(const float *__restrict__ partial, int nchunk, int nw, int nb,
-                                                      float *__restrict__ gw, float *__restrict__ gb)
+// consecutive outputs; wave w of 16 sums the chunks c = w (mod 16) in order,
+// eight loads in flight, then the wave sums are added in order.  The 16 -> 16
+// layers have 27 KB rows and 512 chunks: few outputs, so the rows are split
+// over many waves (4 waves with one load in flight: 48 us).
+constexpr int SUM_WAVES = 16;
+__global__ __launch_bounds__(64 * SUM_WAVES) void k_sum_partials(const float *__restrict__ partial, int nchunk, int nw,
+                                                                 int nb, float *__restrict__ gw, float *__restrict__ gb)
 {
-    __shared__ float red[TPB / 64][64];
+    __shared__ float red[SUM_WAVES][64];
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int e = blockIdx.x * 64 + l;
     const int rs = nw + nb;
     float s = 0.f;
-    if (e < rs)
-        for (int c = w; c < nchunk; c += TPB / 64) s += partial[(size_t)c * rs + e];
+    if (e < rs) {
+        int c = w;
+        for (; c + 7 * SUM_WAVES < nchunk; c += 8 * SUM_WAVES) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)(c + u * SUM_WAVES) * rs + e];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; c < nchunk; c += SUM_WAVES) s += partial[(size_t)c * rs + e];
+    }
     red[w][l] = s;
     __syncthreads();
     if (w == 0 && e < rs) {
-        const float t = ((red[0][l] + red[1][l]) + red[2][l]) + red[3][l];
+        float t = red[0][l];
+#pragma unroll
+        for (int u = 1; u < SUM_WAVES; ++u) t += red[u][l];
         if (e < nw) gw[e] = t;
         else if (gb) gb[e - nw] = t;
     }
@@ -772,7 +831,7 @@ void nn_pack_weights(const float *w, unsigned short *out, int Ci, int Co, int fl
 }
 
 template <int MT, int NTS, typename To, typename Off = unsigned>
-static void conv3_launch(const unsigned short *in, const void *wp, const float *bias, To *out, int D, int H, int W,
+static void conv3_launch(const unsigned short *in, const void *wp, const float *bias, To *out, NNLayout li, NNLayout lo, int D, int H, int W,
                          int Ci, int NT, int act, float slope, hipStream_t s)
 {
     const int nbx = (W + 15) / 16, nby = (H + 7) / 8, nbz = (D + MT - 1) / MT;
@@ -780,59 +839,53 @@ static void conv3_launch(const unsigned short *in, const void *wp, const float *
     const int wide = ((uintptr_t)out % (4 * sizeof(To))) == 0;
     // two resident workgroups per CU (of 160-250 VGPRs) walk the tiles
     const int grid = ntile < 512 ? ntile : 512;
-    hipLaunchKernelGGL((k_conv3<MT, NTS, To, Off>), dim3(grid), dim3(TPB), 0, s, in, (const u4 *)wp, bias, out, D, H, W,
-                       Ci, act, slope, nbx, nby, ntile, NT, wide);
+    hipLaunchKernelGGL((k_conv3<MT, NTS, To, Off>), dim3(grid), dim3(TPB), 0, s, in, (const u4 *)wp, bias, out, li, lo,
+                       D, H, W, Ci, act, slope, nbx, nby, ntile, NT, wide);
 }
 
 // The largest brick and output split that still give two workgroups per CU;
 // below that, the smallest (the halo of a brick is staged once per output
 // group, so fewer groups where the bricks alone fill the chip).
 template <typename To>
-static void conv3_dispatch(const unsigned short *in, const void *wp, const float *bias, To *out, int D, int H, int W,
+static void conv3_dispatch(const unsigned short *in, const void *wp, const float *bias, To *out, NNLayout li, NNLayout lo, int D, int H, int W,
                            int Ci, int Co, int act, float slope, hipStream_t s)
 {
     const int NT = Co / 16;
     auto tiles = [&](int mt, int nts) { return ((W + 15) / 16) * ((H + 7) / 8) * ((D + mt - 1) / mt) * (NT / nts); };
-    if ((6.0 * H + 10.0) * W * Ci * 2.0 >= 4294967296.0)
-        conv3_launch<1, 1, To, size_t>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
+    if ((6.0 * H + 10.0) * W * li.vs * 2.0 >= 4294967296.0)
+        conv3_launch<1, 1, To, size_t>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
     else if (NT % 2 == 0 && tiles(2, 2) >= 512)
-        conv3_launch<2, 2, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<2, 2, To>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
     else if (tiles(4, 1) >= 512)
-        conv3_launch<4, 1, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<4, 1, To>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
     else if (tiles(2, 1) >= 512)
-        conv3_launch<2, 1, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<2, 1, To>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
     else
-        conv3_launch<1, 1, To>(in, wp, bias, out, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<1, 1, To>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
 }
 
-void nn_conv3(const unsigned short *in, const void *wp, const float *bias, void *out, int out_f32, int D, int H, int W,
-              int Ci, int Co, int act, float slope, hipStream_t s)
+void nn_conv3(const unsigned short *in, const void *wp, const float *bias, void *out, int out_f32, NNLayout li,
+              NNLayout lo, int D, int H, int W, int Ci, int Co, int act, float slope, hipStream_t s)
 {
-    if (out_f32) conv3_dispatch(in, wp, bias, (float *)out, D, H, W, Ci, Co, act, slope, s);
-    else conv3_dispatch(in, wp, bias, (unsigned short *)out, D, H, W, Ci, Co, act, slope, s);
+    if (out_f32) conv3_dispatch(in, wp, bias, (float *)out, li, lo, D, H, W, Ci, Co, act, slope, s);
+    else conv3_dispatch(in, wp, bias, (unsigned short *)out, li, lo, D, H, W, Ci, Co, act, slope, s);
 }
 
-// weight-gradient work split: NG output tiles per workgroup, ngrp groups,
-// voxel tiles of 16 x 4 x 2 dealt in runs of tpc to nchunk chunks so that
-// about 1024 workgroups are in flight
+// weight-gradient work split: the (input chunk, output tile) pairs times runs
+// of tpc voxel tiles, at most the 512 workgroups that are resident at once (two
+// per CU): 171 runs of three pairs, 513 workgroups, took twice the time of 170
 struct DwPlan {
-    int ng, ngrp, ntx, nty, ntiles, tpc, nchunk;
+    int npair, ntx, nty, ntiles, tpc, nchunk;
 };
 
 static DwPlan dw_plan(int D, int H, int W, int Ci, int Co)
 {
     DwPlan p{};
-    const int nt = Co / 16;
-    p.ng = nt % 4 == 0 ? 4 : nt % 3 == 0 ? 3 : nt;
-    p.ngrp = nt / p.ng;
+    p.npair = (Ci / 16) * (Co / 16);
     p.ntx = (W + 15) / 16;
     p.nty = (H + 3) / 4;
-    p.ntiles = p.ntx * p.nty * ((D + 1) / 2);
-    // one resident wave of workgroups: three per CU (one for NG = 4, whose
-    // accumulators take the whole register file)
-    const int per = (Ci / 16) * p.ngrp;
-    const int resident = (p.ng == 4 ? 1 : 3) * 256;
-    int want = (resident + per - 1) / per;
+    p.ntiles = p.ntx * p.nty * ((D + 3) / 4);
+    int want = 512 / p.npair;
     if (want > p.ntiles) want = p.ntiles;
     if (want < 1) want = 1;
     p.tpc = (p.ntiles + want - 1) / want;
@@ -846,20 +899,15 @@ size_t nn_dw_workspace_floats(int D, int H, int W, int Ci, int Co)
     return (size_t)p.nchunk * (27 * (size_t)Ci * Co + Co);
 }
 
-void nn_conv3_dw(const unsigned short *X, const unsigned short *dZ, float *partial, float *gw, float *gb, int D, int H,
-                 int W, int Ci, int Co, hipStream_t s)
+void nn_conv3_dw(const unsigned short *X, const unsigned short *dZ, float *partial, float *gw, float *gb, NNLayout lx,
+                 NNLayout lz, int D, int H, int W, int Ci, int Co, hipStream_t s)
 {
     const DwPlan p = dw_plan(D, H, W, Ci, Co);
-    const dim3 grid(p.nchunk * (Ci / 16) * p.ngrp), block(TPB);
-    switch (p.ng) {
-    case 1: hipLaunchKernelGGL((k_conv3_dw<1>), grid, block, 0, s, X, dZ, partial, D, H, W, Ci, Co, p.ntx, p.nty, p.ntiles, p.tpc, p.ngrp); break;
-    case 2: hipLaunchKernelGGL((k_conv3_dw<2>), grid, block, 0, s, X, dZ, partial, D, H, W, Ci, Co, p.ntx, p.nty, p.ntiles, p.tpc, p.ngrp); break;
-    case 3: hipLaunchKernelGGL((k_conv3_dw<3>), grid, block, 0, s, X, dZ, partial, D, H, W, Ci, Co, p.ntx, p.nty, p.ntiles, p.tpc, p.ngrp); break;
-    case 4: hipLaunchKernelGGL((k_conv3_dw<4>), grid, block, 0, s, X, dZ, partial, D, H, W, Ci, Co, p.ntx, p.nty, p.ntiles, p.tpc, p.ngrp); break;
-    default: break;
-    }
+    hipLaunchKernelGGL(k_conv3_dw, dim3(p.nchunk * p.npair), dim3(TPB), 0, s, X, dZ, partial, lx, lz, D, H, W, Ci, Co,
+                       p.ntx, p.nty, p.ntiles, p.tpc);
     const int nw = 27 * Ci * Co;
-    hipLaunchKernelGGL(k_sum_partials, dim3((nw + Co + 63) / 64), dim3(TPB), 0, s, partial, p.nchunk, nw, Co, gw, gb);
+    hipLaunchKernelGGL(k_sum_partials, dim3((nw + Co + 63) / 64), dim3(64 * SUM_WAVES), 0, s, partial, p.nchunk, nw, Co,
+                       gw, gb);
 }
 
 void nn_lrelu_bwd(const unsigned short *dY, const unsigned short *Y, float slope, size_t n, unsigned short *dZ,

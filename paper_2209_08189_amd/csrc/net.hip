@@ -15,6 +15,7 @@
 // error on the velocity; optimiser: Adam on FP32 master weights, BF16
 // weight copies packed for the matrix cores after every update.
 #include "internal.h"
+#include "nn.h"
 
 #include <cmath>
 #include <cstring>
@@ -22,33 +23,6 @@
 #include <random>
 #include <string>
 #include <vector>
-
-namespace clh {
-void nn_pack_weights(const float *w, unsigned short *out, int Ci, int Co, int flip, hipStream_t s);
-void nn_conv3(const unsigned short *in, const void *wp, const float *bias, void *out, int out_f32, int D, int H, int W,
-              int Ci, int Co, int act, float slope, hipStream_t s);
-size_t nn_packed_weight_elems(int Ci, int Co);
-size_t nn_dw_workspace_floats(int D, int H, int W, int Ci, int Co);
-void nn_conv3_dw(const unsigned short *X, const unsigned short *dZ, float *partial, float *gw, float *gb, int D, int H,
-                 int W, int Ci, int Co, hipStream_t s);
-void nn_lrelu_bwd(const unsigned short *dY, const unsigned short *Y, float slope, size_t n, unsigned short *dZ,
-                  hipStream_t s);
-void nn_pool2(const unsigned short *in, unsigned short *out, int D, int H, int W, int C, hipStream_t s);
-void nn_pool2_bwd(const unsigned short *gout, unsigned short *gin, int D, int H, int W, int C, int accumulate,
-                  hipStream_t s);
-void nn_up2cat(const unsigned short *a, const unsigned short *b, unsigned short *out, int D, int H, int W, int Ca,
-               int Cb, hipStream_t s);
-void nn_up2cat_bwd(const unsigned short *g, unsigned short *ga, unsigned short *gb, int D, int H, int W, int Ca, int Cb,
-                   int accumulate_b, hipStream_t s);
-void nn_head(const unsigned short *in, const float *w, const float *b, float *out, size_t P, int Ci, hipStream_t s);
-void nn_head_bwd(const unsigned short *in, const float *gout, const float *w, unsigned short *gin, double *partials,
-                 int nparts, double *dst_dev, size_t P, int Ci, hipStream_t s);
-void nn_mse(const float *pred, const float *label, size_t n, float inv, float *grad, double *partials, int nparts,
-            hipStream_t s);
-void nn_adam(float *p, const float *g, float *m, float *v, size_t n, float lr, float b1, float b2, float eps, float c1,
-             float c2, hipStream_t s);
-void nn_pack_input(const float *a, const float *b, unsigned short *out, size_t P, hipStream_t s);
-} // namespace clh
 
 using namespace clh;
 
@@ -147,7 +121,8 @@ Act act(cl_net *net, int lvl, int C)
 void conv_fwd(cl_net *net, const ConvL &c, const Act &in, const Act &out)
 {
     const int d = net->dims[c.lvl];
-    nn_conv3(in.p, c.wpf, net->param + c.bo, out.p, 0, d, d, d, c.Ci, c.Co, 1, net->opt.slope, net->s);
+    nn_conv3(in.p, c.wpf, net->param + c.bo, out.p, 0, nn_channels_last(c.Ci), nn_channels_last(c.Co), d, d, d, c.Ci,
+             c.Co, 1, net->opt.slope, net->s);
 }
 
 // backward of out = lrelu(conv(in)): given gout (w.r.t. out), accumulate the
@@ -157,8 +132,10 @@ void conv_bwd(cl_net *net, const ConvL &c, const Act &in, const Act &out, const 
     const int d = net->dims[c.lvl];
     const size_t n = vox(net, c.lvl) * c.Co;
     nn_lrelu_bwd(gout.p, out.p, net->opt.slope, n, net->dz.p, net->s);
-    nn_conv3_dw(in.p, net->dz.p, net->partial, net->grad + c.wo, net->grad + c.bo, d, d, d, c.Ci, c.Co, net->s);
-    if (gin) nn_conv3(net->dz.p, c.wpb, nullptr, gin->p, 0, d, d, d, c.Co, c.Ci, 0, 0.f, net->s);
+    nn_conv3_dw(in.p, net->dz.p, net->partial, net->grad + c.wo, net->grad + c.bo, nn_channels_last(c.Ci),
+                nn_channels_last(c.Co), d, d, d, c.Ci, c.Co, net->s);
+    if (gin) nn_conv3(net->dz.p, c.wpb, nullptr, gin->p, 0, nn_channels_last(c.Co), nn_channels_last(c.Ci), d, d, d,
+                       c.Co, c.Ci, 0, 0.f, net->s);
 }
 
 void pack_all(cl_net *net)
@@ -584,7 +561,8 @@ int cl_nn_conv3(const void *in, const float *w, const float *b, void *out, int o
     if (!tile_count_ok(Kout / 16)) return CL_ERR_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
     nn_pack_weights(w, (unsigned short *)wpack, Ci, Co, transpose, s);
-    nn_conv3((const unsigned short *)in, wpack, transpose ? nullptr : b, out, out_f32, D, H, W, Kin, Kout, act, slope, s);
+    nn_conv3((const unsigned short *)in, wpack, transpose ? nullptr : b, out, out_f32,
+             nn_channels_last(Kin), nn_channels_last(Kout), D, H, W, Kin, Kout, act, slope, s);
     return hipGetLastError() == hipSuccess ? CL_OK : CL_ERR_HIP;
 }
 
@@ -602,7 +580,8 @@ int cl_nn_conv3_dw(const void *x, const void *dz, float *gw, float *gb, void *wo
     if (!x || !dz || !gw || !workspace) return CL_ERR_ARG;
     if (Ci < 16 || Co < 16 || Ci % 16 || Co % 16 || W < 1 || D < 1 || H < 1) return CL_ERR_SHAPE;
     if (!tile_count_ok(Co / 16)) return CL_ERR_UNSUPPORTED;
-    nn_conv3_dw((const unsigned short *)x, (const unsigned short *)dz, (float *)workspace, gw, gb, D, H, W, Ci, Co,
+    nn_conv3_dw((const unsigned short *)x, (const unsigned short *)dz, (float *)workspace, gw, gb,
+                nn_channels_last(Ci), nn_channels_last(Co), D, H, W, Ci, Co,
                 (hipStream_t)stream);
     return hipGetLastError() == hipSuccess ? CL_OK : CL_ERR_HIP;
 }

@@ -67,3 +67,17 @@ def test_conv3_output_at_any_element(f32):
         assert st == 0
         assert torch.equal(buf[off:off + n], ref.reshape(-1))
         assert not buf[:off].any() and not buf[off + n:].any()
+
+
+# less than a voxel tile of 16 x 4 x 4; ragged in every direction; several tiles
+# per run with a short last run (1458 tiles over 512 workgroups, 96 over 28)
+@pytest.mark.parametrize("shape,ci,co", [((1, 1, 1), 16, 16), ((5, 9, 17), 32, 48), ((2, 3, 40), 16, 64),
+                                         ((36, 70, 130), 16, 16), ((23, 29, 30), 48, 96)])
+def test_conv3_weight_gradient_tilings_against_oracle(shape, ci, co):
+    from paper_2209_08189_amd.claire import nn_conv3_dw
+    r = np.random.default_rng(sum(shape) + ci + co)
+    x, dz = bf16_round(r.standard_normal(shape + (ci,))), bf16_round(r.standard_normal(shape + (co,)))
+    gw, gb = nn_conv3_dw(_bf16(x), _bf16(dz))
+    rw, rb = oracle.conv3_dw(x, dz)
+    assert _rel(gw, rw) < 1e-5
+    assert _rel(gb, rb) < 1e-5
