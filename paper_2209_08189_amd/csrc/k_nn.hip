@@ -82,6 +82,18 @@ __global__ __launch_bounds__(TPB) void k_pack_w(const float *__restrict__ w, uns
 
 __device__ __forceinline__ bf8 as_bf8(u4 v) { return __builtin_bit_cast(bf8, v); }
 
+__device__ __forceinline__ float lo_bf(unsigned v) { return __uint_as_float(v << 16); }
+__device__ __forceinline__ float hi_bf(unsigned v) { return __uint_as_float(v & 0xffff0000u); }
+
+// LeakyReLU backward of a BF16-rounded gradient, from the sign of the output y
+__device__ __forceinline__ float lrelu_bwd1(float g, float y, float slope) { return y > 0.f ? g : slope * g; }
+__device__ __forceinline__ f4 lrelu_bwd4(f4 v, u2 y, float slope)
+{
+    const unsigned a = pack_bf2(v[0], v[1]), b = pack_bf2(v[2], v[3]);
+    return f4{lrelu_bwd1(lo_bf(a), lo_bf(y[0]), slope), lrelu_bwd1(hi_bf(a), hi_bf(y[0]), slope),
+              lrelu_bwd1(lo_bf(b), lo_bf(y[1]), slope), lrelu_bwd1(hi_bf(b), hi_bf(y[1]), slope)};
+}
+
 // four consecutive channels of one voxel; wide: the address is a multiple of
 // their size (a caller's buffer may start at any element)
 __device__ __forceinline__ void store4(unsigned short *o, f4 v, int wide)
@@ -108,7 +120,9 @@ __device__ __forceinline__ void store4(float *o, f4 v, int wide)
 // in: BF16, voxels in order vs elements apart and 16-channel chunks cs elements
 // apart (Layout; channels last: Ci and 16); wp: packed (K = Ci); bias FP32 [Co]
 // or NULL; act: 0 none, 1 LeakyReLU(slope).  out: BF16 or FP32, laid out
-// likewise.
+// likewise.  mask (BF16 output only, laid out as out, or NULL): the activation
+// whose LeakyReLU lies below the output, so that the rounded output v becomes
+// v or slope v (rounded again) by its sign: dZ of the layer below.
 // Work items: a 16 (x) x 8 (y) x MT (z) output brick times NTS of the NTT
 // 16-channel output tiles, times the 16-channel input chunks.  A workgroup (4
 // wavefronts; wavefront w owns the rows y0 + 2w, y0 + 2w + 1) walks its items
@@ -139,11 +153,12 @@ __device__ __forceinline__ void store4(float *o, f4 v, int wide)
 // access is then a wave-uniform base plus a 32-bit offset), else size_t.
 __device__ const u4 conv_zero = {0u, 0u, 0u, 0u};
 
-template <int MT, int NTS, typename To, typename Off>
+template <int MT, int NTS, typename To, typename Off, bool MASK>
 __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restrict__ in, const u4 *__restrict__ wp,
                                                   const float *__restrict__ bias, To *__restrict__ out,
-                                                  NNLayout li, NNLayout lo, int D, int H, int W, int Ci, int act,
-                                                  float slope, int nbx, int nby, int ntile, int NTT, int wide)
+                                                  const unsigned short *__restrict__ mask, NNLayout li, NNLayout lo,
+                                                  int D, int H, int W, int Ci, int act, float slope, int nbx, int nby,
+                                                  int ntile, int NTT, int wide)
 {
     constexpr int XS = 18, YS = 10, ZS = MT + 2, NV = XS * YS * ZS, NQ = 2 * NV, NCH = (NQ + TPB - 1) / TPB;
     // two planes of 8 channels: the 16 lanes of a quarter of a fragment read
@@ -263,6 +278,20 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
             request(kc);
         }
         __syncthreads();
+        // the mask of the item's outputs, in flight while they are computed
+        // (with two output tiles the registers do not allow it)
+        constexpr bool PRE = MASK && NTS == 1;
+        u2 mk[PRE ? MT : 1][2];
+        if (PRE && last_kc) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int yi = 0; yi < 2; ++yi) {
+                    const int z = min(cz + i, D - 1), y = min(cy + 2 * wv + yi, H - 1), x = min(m, W - 1 - cx);
+                    mk[PRE ? i : 0][yi] = *(const u2 *)(mask + (((size_t)z * H + y) * W + cx) * lo.vs + cg * lo.cs +
+                                                        x * lo.vs + 4 * (l >> 4));
+                }
+        }
         // the fragments of step (plane zz, k) are read one step ahead of its
         // products, so that LDS latency hides behind them (left to itself the
         // compiler reads each pair just before its use and waits)
@@ -345,8 +374,11 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
 #pragma unroll
                             for (int j = 0; j < 4; ++j) v[j] = v[j] > 0.f ? v[j] : slope * v[j];
                         }
-                        To *row = out + (((size_t)z * H + y) * W + cx) * lo.vs + (cg * NTS + nt) * lo.cs;
-                        if (cx + m < W) store4(row + lane_off, v, wide);
+                        const size_t row = (((size_t)z * H + y) * W + cx) * lo.vs + (cg * NTS + nt) * lo.cs;
+                        if (cx + m >= W) continue;
+                        if constexpr (MASK)
+                            v = lrelu_bwd4(v, PRE ? mk[PRE ? i : 0][yi] : *(const u2 *)(mask + row + lane_off), slope);
+                        store4(out + row + lane_off, v, wide);
                     }
             }
         }
@@ -561,142 +593,118 @@ __global__ __launch_bounds__(64 * SUM_WAVES) void k_sum_partials(const float *__
     }
 }
 
-// Elementwise layers on channels-last BF16 tensors work on 8-channel
-// groups (one 16-byte load per tensor and thread); channel counts are
-// multiples of 16, so a group never straddles two voxels.
+// The network keeps its activations by 16-channel chunks, [C / 16][D][H][W][16]:
+// a convolution stages one chunk at a time, so each staged row is contiguous
+// (channels last, a 48-channel voxel's 96 bytes were fetched three times, a
+// third of every cache line used: dW of 48 -> 16 at 128^3 115 -> 98 us), a
+// skip connection is written by its convolution into its place in the
+// concatenated tensor, and the elementwise layers see 16-channel tensors with
+// the chunks stacked along z.  They work on 8-channel groups (one 16-byte load
+// per tensor and thread).
 __device__ __forceinline__ void unpack8(u4 v, float (&f)[8])
 {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        f[2 * i] = __uint_as_float(v[i] << 16);
-        f[2 * i + 1] = __uint_as_float(v[i] & 0xffff0000u);
+        f[2 * i] = lo_bf(v[i]);
+        f[2 * i + 1] = hi_bf(v[i]);
     }
 }
 __device__ __forceinline__ u4 pack8(const float (&f)[8])
 {
     u4 v;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = (unsigned)f2bf(f[2 * i]) | ((unsigned)f2bf(f[2 * i + 1]) << 16);
+    for (int i = 0; i < 4; ++i) v[i] = pack_bf2(f[2 * i], f[2 * i + 1]);
     return v;
 }
-
-// dZ = dY * (Y > 0 ? 1 : slope)   (LeakyReLU backward from the output sign)
-__global__ __launch_bounds__(TPB) void k_lrelu_bwd(const u4 *__restrict__ dY, const u4 *__restrict__ Y, float slope,
-                                                   size_t n8, u4 *__restrict__ dZ)
+// LeakyReLU backward of 8 gradients (rounded to BF16 first), from the output y
+__device__ __forceinline__ u4 lrelu_bwd8(const float (&g)[8], u4 y, float slope)
 {
-    const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (e >= n8) return;
-    float g[8], y[8];
-    unpack8(dY[e], g);
-    unpack8(Y[e], y);
+    float f[8], yy[8];
+    unpack8(pack8(g), f);
+    unpack8(y, yy);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) g[i] = y[i] > 0.f ? g[i] : slope * g[i];
-    dZ[e] = pack8(g);
+    for (int i = 0; i < 8; ++i) f[i] = lrelu_bwd1(f[i], yy[i], slope);
+    return pack8(f);
 }
 
-// 2x2x2 average pooling, channels-last (D, H, W of the input)
-__global__ __launch_bounds__(TPB) void k_pool2(const u4 *__restrict__ in, u4 *__restrict__ out, int D, int H, int W,
-                                               int C)
+// sums of the 2 x 2 x 2 children of a coarse voxel (H, W of the fine grid)
+__device__ __forceinline__ void children8(const u4 *__restrict__ in, int x, int y, int z, int H, int W, int c,
+                                          float (&s)[8])
 {
-    const int d = D / 2, h = H / 2, w = W / 2, C8 = C / 8;
-    const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (e >= (size_t)d * h * w * C8) return;
-    const int c = e % C8;
-    const size_t v = e / C8;
-    const int x = v % w, y = (v / w) % h, z = v / ((size_t)w * h);
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s[i] = 0.f;
+#pragma unroll
     for (int a = 0; a < 2; ++a)
+#pragma unroll
         for (int b = 0; b < 2; ++b)
+#pragma unroll
             for (int q = 0; q < 2; ++q) {
                 float f[8];
-                unpack8(in[((((size_t)(2 * z + a)) * H + 2 * y + b) * W + 2 * x + q) * C8 + c], f);
+                unpack8(in[((((size_t)(2 * z + a)) * H + 2 * y + b) * W + 2 * x + q) * 2 + c], f);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) s[i] += f[i];
             }
+}
+
+// 2x2x2 average pooling (D, H, W of the input, D over all chunks)
+__global__ __launch_bounds__(TPB) void k_pool2(const u4 *__restrict__ in, u4 *__restrict__ out, int D, int H, int W)
+{
+    const int d = D / 2, h = H / 2, w = W / 2;
+    const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
+    if (e >= (size_t)d * h * w * 2) return;
+    const int c = e & 1;
+    const size_t v = e >> 1;
+    const int x = v % w, y = (v / w) % h, z = v / ((size_t)w * h);
+    float s[8];
+    children8(in, x, y, z, H, W, c, s);
 #pragma unroll
     for (int i = 0; i < 8; ++i) s[i] *= 0.125f;
     out[e] = pack8(s);
 }
 
-// backward of pool2: gin[fine] (+)= gout[coarse] / 8
-__global__ __launch_bounds__(TPB) void k_pool2_bwd(const u4 *__restrict__ gout, u4 *__restrict__ gin, int D, int H,
-                                                   int W, int C, int accumulate)
+// the gradient of an activation Y that is both pooled and skipped, through its
+// LeakyReLU: g[fine] <- bwd(g[fine] + gpool[coarse] / 8)
+__global__ __launch_bounds__(TPB) void k_pool2_bwd(const u4 *__restrict__ gpool, u4 *__restrict__ g,
+                                                   const u4 *__restrict__ Y, float slope, int D, int H, int W)
 {
-    const int C8 = C / 8;
     const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (e >= (size_t)D * H * W * C8) return;
-    const int c = e % C8;
-    const size_t v = e / C8;
+    if (e >= (size_t)D * H * W * 2) return;
+    const int c = e & 1;
+    const size_t v = e >> 1;
     const int x = v % W, y = (v / W) % H, z = v / ((size_t)W * H);
-    float g[8];
-    unpack8(gout[((((size_t)z / 2) * (H / 2) + y / 2) * (W / 2) + x / 2) * C8 + c], g);
+    float p[8], f[8];
+    unpack8(gpool[((((size_t)z / 2) * (H / 2) + y / 2) * (W / 2) + x / 2) * 2 + c], p);
+    unpack8(g[e], f);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) g[i] *= 0.125f;
-    if (accumulate) {
-        float f[8];
-        unpack8(gin[e], f);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) g[i] = f[i] + g[i];
-    }
-    gin[e] = pack8(g);
+    for (int i = 0; i < 8; ++i) f[i] = f[i] + p[i] * 0.125f;
+    g[e] = lrelu_bwd8(f, Y[e], slope);
 }
 
-// out[p][0:Ca] = a[p / 2], out[p][Ca:Ca+Cb] = b[p]  (D, H, W fine)
-__global__ __launch_bounds__(TPB) void k_up2cat(const u4 *__restrict__ a, const u4 *__restrict__ b, u4 *__restrict__ out,
-                                                int D, int H, int W, int Ca, int Cb)
+// nearest 2x upsampling (D, H, W of the output)
+__global__ __launch_bounds__(TPB) void k_up2(const u4 *__restrict__ a, u4 *__restrict__ out, int D, int H, int W)
 {
-    const int A8 = Ca / 8, B8 = Cb / 8, C8 = A8 + B8;
     const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (e >= (size_t)D * H * W * C8) return;
-    const int c = e % C8;
-    const size_t v = e / C8;
+    if (e >= (size_t)D * H * W * 2) return;
+    const int c = e & 1;
+    const size_t v = e >> 1;
     const int x = v % W, y = (v / W) % H, z = v / ((size_t)W * H);
-    if (c < A8) out[e] = a[((((size_t)z / 2) * (H / 2) + y / 2) * (W / 2) + x / 2) * A8 + c];
-    else out[e] = b[v * B8 + (c - A8)];
+    out[e] = a[((((size_t)z / 2) * (H / 2) + y / 2) * (W / 2) + x / 2) * 2 + c];
 }
 
-// backward of up2cat: ga[coarse] = sum of the 8 children's first Ca
-// channels; gb[fine] (+)= last Cb channels
-__global__ __launch_bounds__(TPB) void k_up2cat_bwd_a(const u4 *__restrict__ g, u4 *__restrict__ ga, int D, int H, int W,
-                                                      int Ca, int Cb)
+// backward of up2, through the LeakyReLU of Y: ga[coarse] <- bwd(sum of its
+// children) (D, H, W of the fine grid)
+__global__ __launch_bounds__(TPB) void k_up2_bwd(const u4 *__restrict__ g, u4 *__restrict__ ga,
+                                                 const u4 *__restrict__ Y, float slope, int D, int H, int W)
 {
-    const int A8 = Ca / 8, C8 = (Ca + Cb) / 8, d = D / 2, h = H / 2, w = W / 2;
+    const int d = D / 2, h = H / 2, w = W / 2;
     const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (e >= (size_t)d * h * w * A8) return;
-    const int c = e % A8;
-    const size_t v = e / A8;
+    if (e >= (size_t)d * h * w * 2) return;
+    const int c = e & 1;
+    const size_t v = e >> 1;
     const int x = v % w, y = (v / w) % h, z = v / ((size_t)w * h);
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int a = 0; a < 2; ++a)
-        for (int b = 0; b < 2; ++b)
-            for (int q = 0; q < 2; ++q) {
-                float f[8];
-                unpack8(g[((((size_t)(2 * z + a)) * H + 2 * y + b) * W + 2 * x + q) * C8 + c], f);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) s[i] += f[i];
-            }
-    ga[e] = pack8(s);
-}
-
-__global__ __launch_bounds__(TPB) void k_up2cat_bwd_b(const u4 *__restrict__ g, u4 *__restrict__ gb, size_t P, int Ca,
-                                                      int Cb, int accumulate)
-{
-    const int A8 = Ca / 8, B8 = Cb / 8;
-    const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (e >= P * B8) return;
-    const size_t p = e / B8;
-    const int c = e % B8;
-    const u4 v = g[p * (A8 + B8) + A8 + c];
-    if (!accumulate) {
-        gb[e] = v;
-        return;
-    }
-    float f[8], h[8];
-    unpack8(v, f);
-    unpack8(gb[e], h);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) h[i] = h[i] + f[i];
-    gb[e] = pack8(h);
+    float s[8];
+    children8(g, x, y, z, H, W, c, s);
+    ga[e] = lrelu_bwd8(s, Y[e], slope);
 }
 
 // head: 1x1x1 convolution Ci -> 3, FP32 output as SoA [3][P]
@@ -723,16 +731,24 @@ __global__ __launch_bounds__(TPB) void k_head(const unsigned short *__restrict__
     out[2 * P + p] = s2;
 }
 
-// head backward: gin[p][i] = sum_o w[i][o] gout[o][p]  (BF16 out)
+// head backward, through the LeakyReLU of its input Y: gin[p][i] =
+// bwd(sum_o w[i][o] gout[o][p]), 8 channels per thread
 __global__ __launch_bounds__(TPB) void k_head_bwd_x(const float *__restrict__ gout, const float *__restrict__ w,
-                                                    unsigned short *__restrict__ gin, size_t P, int Ci)
+                                                    const u4 *__restrict__ Y, float slope, u4 *__restrict__ gin,
+                                                    size_t P)
 {
     const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (e >= P * Ci) return;
-    const size_t p = e / Ci;
-    const int i = e % Ci;
-    const float g = w[i * 3 + 0] * gout[p] + w[i * 3 + 1] * gout[P + p] + w[i * 3 + 2] * gout[2 * P + p];
-    gin[e] = f2bf(g);
+    if (e >= P * 2) return;
+    const size_t p = e >> 1;
+    const int i0 = 8 * (int)(e & 1);
+    const float g0 = gout[p], g1 = gout[P + p], g2 = gout[2 * P + p];
+    float f[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float *wi = w + (i0 + i) * 3;
+        f[i] = wi[0] * g0 + wi[1] * g1 + wi[2] * g2;
+    }
+    gin[e] = lrelu_bwd8(f, Y[e], slope);
 }
 
 // head weight gradient: every workgroup sums, over its voxels, the 16 x 3
@@ -762,10 +778,20 @@ __global__ __launch_bounds__(TPB) void k_head_bwd_w(const unsigned short *__rest
         acc[49] += g1;
         acc[50] += g2;
     }
+    // one barrier for all 51 sums
+    __shared__ double red[TPB / 64][HEAD_NC];
 #pragma unroll
     for (int c = 0; c < HEAD_NC; ++c) {
-        const double v = block_sum(acc[c]);
-        if (threadIdx.x == 0) partials[(size_t)c * gridDim.x + blockIdx.x] = v;
+        double v = acc[c];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][c] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < HEAD_NC) {
+        double v = red[0][threadIdx.x];
+        for (int q = 1; q < TPB / 64; ++q) v += red[q][threadIdx.x];
+        partials[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = v;
     }
 }
 
@@ -831,7 +857,7 @@ void nn_pack_weights(const float *w, unsigned short *out, int Ci, int Co, int fl
 }
 
 template <int MT, int NTS, typename To, typename Off = unsigned>
-static void conv3_launch(const unsigned short *in, const void *wp, const float *bias, To *out, NNLayout li, NNLayout lo, int D, int H, int W,
+static void conv3_launch(const unsigned short *in, const void *wp, const float *bias, To *out, const unsigned short *mask, NNLayout li, NNLayout lo, int D, int H, int W,
                          int Ci, int NT, int act, float slope, hipStream_t s)
 {
     const int nbx = (W + 15) / 16, nby = (H + 7) / 8, nbz = (D + MT - 1) / MT;
@@ -839,36 +865,42 @@ static void conv3_launch(const unsigned short *in, const void *wp, const float *
     const int wide = ((uintptr_t)out % (4 * sizeof(To))) == 0;
     // two resident workgroups per CU (of 160-250 VGPRs) walk the tiles
     const int grid = ntile < 512 ? ntile : 512;
-    hipLaunchKernelGGL((k_conv3<MT, NTS, To, Off>), dim3(grid), dim3(TPB), 0, s, in, (const u4 *)wp, bias, out, li, lo,
-                       D, H, W, Ci, act, slope, nbx, nby, ntile, NT, wide);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(TPB), 0, s, in, (const u4 *)wp, bias, out, mask, li, lo, D, H, W,
+                           Ci, act, slope, nbx, nby, ntile, NT, wide);
+    };
+    if constexpr (sizeof(To) == 2) {
+        if (mask) return go(k_conv3<MT, NTS, To, Off, true>);
+    }
+    go(k_conv3<MT, NTS, To, Off, false>);
 }
 
 // The largest brick and output split that still give two workgroups per CU;
 // below that, the smallest (the halo of a brick is staged once per output
 // group, so fewer groups where the bricks alone fill the chip).
 template <typename To>
-static void conv3_dispatch(const unsigned short *in, const void *wp, const float *bias, To *out, NNLayout li, NNLayout lo, int D, int H, int W,
+static void conv3_dispatch(const unsigned short *in, const void *wp, const float *bias, To *out, const unsigned short *mask, NNLayout li, NNLayout lo, int D, int H, int W,
                            int Ci, int Co, int act, float slope, hipStream_t s)
 {
     const int NT = Co / 16;
     auto tiles = [&](int mt, int nts) { return ((W + 15) / 16) * ((H + 7) / 8) * ((D + mt - 1) / mt) * (NT / nts); };
     if ((6.0 * H + 10.0) * W * li.vs * 2.0 >= 4294967296.0)
-        conv3_launch<1, 1, To, size_t>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<1, 1, To, size_t>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
     else if (NT % 2 == 0 && tiles(2, 2) >= 512)
-        conv3_launch<2, 2, To>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<2, 2, To>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
     else if (tiles(4, 1) >= 512)
-        conv3_launch<4, 1, To>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<4, 1, To>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
     else if (tiles(2, 1) >= 512)
-        conv3_launch<2, 1, To>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<2, 1, To>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
     else
-        conv3_launch<1, 1, To>(in, wp, bias, out, li, lo, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<1, 1, To>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
 }
 
-void nn_conv3(const unsigned short *in, const void *wp, const float *bias, void *out, int out_f32, NNLayout li,
-              NNLayout lo, int D, int H, int W, int Ci, int Co, int act, float slope, hipStream_t s)
+void nn_conv3(const unsigned short *in, const void *wp, const float *bias, void *out, int out_f32,
+              const unsigned short *mask, NNLayout li, NNLayout lo, int D, int H, int W, int Ci, int Co, int act, float slope, hipStream_t s)
 {
-    if (out_f32) conv3_dispatch(in, wp, bias, (float *)out, li, lo, D, H, W, Ci, Co, act, slope, s);
-    else conv3_dispatch(in, wp, bias, (unsigned short *)out, li, lo, D, H, W, Ci, Co, act, slope, s);
+    if (out_f32) conv3_dispatch(in, wp, bias, (float *)out, mask, li, lo, D, H, W, Ci, Co, act, slope, s);
+    else conv3_dispatch(in, wp, bias, (unsigned short *)out, mask, li, lo, D, H, W, Ci, Co, act, slope, s);
 }
 
 // weight-gradient work split: the (input chunk, output tile) pairs times runs
@@ -910,41 +942,28 @@ void nn_conv3_dw(const unsigned short *X, const unsigned short *dZ, float *parti
                        gw, gb);
 }
 
-void nn_lrelu_bwd(const unsigned short *dY, const unsigned short *Y, float slope, size_t n, unsigned short *dZ,
-                  hipStream_t s)
+void nn_pool2(const unsigned short *in, unsigned short *out, int D, int H, int W, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_lrelu_bwd, dim3(nblk(n / 8)), dim3(TPB), 0, s, (const u4 *)dY, (const u4 *)Y, slope, n / 8,
-                       (u4 *)dZ);
+    hipLaunchKernelGGL(k_pool2, dim3(nblk((size_t)D * H * W / 4)), dim3(TPB), 0, s, (const u4 *)in, (u4 *)out, D, H, W);
 }
 
-void nn_pool2(const unsigned short *in, unsigned short *out, int D, int H, int W, int C, hipStream_t s)
+void nn_pool2_bwd(const unsigned short *gpool, unsigned short *g, const unsigned short *Y, float slope, int D, int H,
+                  int W, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_pool2, dim3(nblk((size_t)D * H * W * C / 64)), dim3(TPB), 0, s, (const u4 *)in, (u4 *)out, D,
-                       H, W, C);
+    hipLaunchKernelGGL(k_pool2_bwd, dim3(nblk((size_t)D * H * W * 2)), dim3(TPB), 0, s, (const u4 *)gpool, (u4 *)g,
+                       (const u4 *)Y, slope, D, H, W);
 }
 
-void nn_pool2_bwd(const unsigned short *gout, unsigned short *gin, int D, int H, int W, int C, int accumulate,
-                  hipStream_t s)
+void nn_up2(const unsigned short *a, unsigned short *out, int D, int H, int W, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_pool2_bwd, dim3(nblk((size_t)D * H * W * C / 8)), dim3(TPB), 0, s, (const u4 *)gout, (u4 *)gin,
-                       D, H, W, C, accumulate);
+    hipLaunchKernelGGL(k_up2, dim3(nblk((size_t)D * H * W * 2)), dim3(TPB), 0, s, (const u4 *)a, (u4 *)out, D, H, W);
 }
 
-void nn_up2cat(const unsigned short *a, const unsigned short *b, unsigned short *out, int D, int H, int W, int Ca,
-               int Cb, hipStream_t s)
+void nn_up2_bwd(const unsigned short *g, unsigned short *ga, const unsigned short *Y, float slope, int D, int H, int W,
+                hipStream_t s)
 {
-    hipLaunchKernelGGL(k_up2cat, dim3(nblk((size_t)D * H * W * (Ca + Cb) / 8)), dim3(TPB), 0, s, (const u4 *)a,
-                       (const u4 *)b, (u4 *)out, D, H, W, Ca, Cb);
-}
-
-void nn_up2cat_bwd(const unsigned short *g, unsigned short *ga, unsigned short *gb, int D, int H, int W, int Ca, int Cb,
-                   int accumulate_b, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_up2cat_bwd_a, dim3(nblk((size_t)D * H * W * Ca / 64)), dim3(TPB), 0, s, (const u4 *)g, (u4 *)ga,
-                       D, H, W, Ca, Cb);
-    hipLaunchKernelGGL(k_up2cat_bwd_b, dim3(nblk((size_t)D * H * W * Cb / 8)), dim3(TPB), 0, s, (const u4 *)g, (u4 *)gb,
-                       (size_t)D * H * W,
-                       Ca, Cb, accumulate_b);
+    hipLaunchKernelGGL(k_up2_bwd, dim3(nblk((size_t)D * H * W / 4)), dim3(TPB), 0, s, (const u4 *)g, (u4 *)ga,
+                       (const u4 *)Y, slope, D, H, W);
 }
 
 void nn_head(const unsigned short *in, const float *w, const float *b, float *out, size_t P, int Ci, hipStream_t s)
@@ -952,10 +971,10 @@ void nn_head(const unsigned short *in, const float *w, const float *b, float *ou
     hipLaunchKernelGGL(k_head, dim3(nblk(P)), dim3(TPB), 0, s, in, w, b, out, P, Ci);
 }
 
-void nn_head_bwd(const unsigned short *in, const float *gout, const float *w, unsigned short *gin, double *partials,
-                 int nparts, double *dst_dev, size_t P, int Ci, hipStream_t s)
+void nn_head_bwd(const unsigned short *in, const float *gout, const float *w, float slope, unsigned short *gin,
+                 double *partials, int nparts, double *dst_dev, size_t P, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_head_bwd_x, dim3(nblk(P * Ci)), dim3(TPB), 0, s, gout, w, gin, P, Ci);
+    hipLaunchKernelGGL(k_head_bwd_x, dim3(nblk(P * 2)), dim3(TPB), 0, s, gout, w, (const u4 *)in, slope, (u4 *)gin, P);
     // partials holds HEAD_NC rows of nparts values
     hipLaunchKernelGGL(k_head_bwd_w, dim3(nparts), dim3(TPB), 0, s, in, gout, P, partials);
     hipLaunchKernelGGL(k_finalize_rows, dim3(HEAD_NC), dim3(TPB), 0, s, partials, nparts, dst_dev);

@@ -74,8 +74,9 @@ struct cl_net {
     long step = 0;
     // activations (forward) and their gradients
     Act x0, a1, e1, p1, a2, e2, p2, a3, e3, p3, a4, e4, c3, b3, d3, c2, b2, d2, c1, b1, d1;
-    Act g_a, g_b, g_c, dz;     // per-level scratch (max channels at each level is handled by sizing to level 0)
-    Act ge1, ge2, ge3, ge4, gd2, gd3, gd1;
+    Act g_a, g_c;              // scratch, sized for its largest use
+    Act gc1, gc2, gc3;         // gradients of the concatenated tensors
+    Act ge4, gd2, gd3, gd1;
     float *vout = nullptr, *gv = nullptr;
     // warm-start work space for one registration grid (created on first use)
     cl_resampler *down = nullptr, *up = nullptr;
@@ -109,6 +110,7 @@ void *nalloc(cl_net *net, size_t bytes)
     return p;
 }
 
+// activations lie by 16-channel chunks, [C / 16][voxels][16]
 Act act(cl_net *net, int lvl, int C)
 {
     Act a;
@@ -118,24 +120,49 @@ Act act(cl_net *net, int lvl, int C)
     return a;
 }
 
+// C channels of a from channel c0 on
+Act part(cl_net *net, const Act &a, int c0, int C) { return {a.p + vox(net, a.lvl) * c0, a.lvl, C}; }
+
 void conv_fwd(cl_net *net, const ConvL &c, const Act &in, const Act &out)
 {
     const int d = net->dims[c.lvl];
-    nn_conv3(in.p, c.wpf, net->param + c.bo, out.p, 0, nn_channels_last(c.Ci), nn_channels_last(c.Co), d, d, d, c.Ci,
-             c.Co, 1, net->opt.slope, net->s);
+    const NNLayout lay = nn_chunked(vox(net, c.lvl));
+    nn_conv3(in.p, c.wpf, net->param + c.bo, out.p, 0, nullptr, lay, lay, d, d, d, c.Ci, c.Co, 1, net->opt.slope, net->s);
 }
 
-// backward of out = lrelu(conv(in)): given gout (w.r.t. out), accumulate the
-// weight gradient into net->grad and write gin (w.r.t. in) unless gin is NULL
-void conv_bwd(cl_net *net, const ConvL &c, const Act &in, const Act &out, const Act &gout, const Act *gin)
+// backward of z = conv(in): given dz, write the weight gradient into net->grad
+// and the gradient w.r.t. in into gin (unless NULL); Y: in is the LeakyReLU
+// output Y of the layer below, and gin becomes that layer's dz
+void conv_bwd(cl_net *net, const ConvL &c, const Act &in, const Act &dz, const Act *gin, const Act *Y)
 {
     const int d = net->dims[c.lvl];
-    const size_t n = vox(net, c.lvl) * c.Co;
-    nn_lrelu_bwd(gout.p, out.p, net->opt.slope, n, net->dz.p, net->s);
-    nn_conv3_dw(in.p, net->dz.p, net->partial, net->grad + c.wo, net->grad + c.bo, nn_channels_last(c.Ci),
-                nn_channels_last(c.Co), d, d, d, c.Ci, c.Co, net->s);
-    if (gin) nn_conv3(net->dz.p, c.wpb, nullptr, gin->p, 0, nn_channels_last(c.Co), nn_channels_last(c.Ci), d, d, d,
-                       c.Co, c.Ci, 0, 0.f, net->s);
+    const NNLayout lay = nn_chunked(vox(net, c.lvl));
+    nn_conv3_dw(in.p, dz.p, net->partial, net->grad + c.wo, net->grad + c.bo, lay, lay, d, d, d, c.Ci, c.Co, net->s);
+    if (gin)
+        nn_conv3(dz.p, c.wpb, nullptr, gin->p, 0, Y ? Y->p : nullptr, lay, lay, d, d, d, c.Co, c.Ci, 0, net->opt.slope,
+                 net->s);
+}
+
+// per-level elementwise layers over all chunks (D: the finer grid's extent)
+void pool(cl_net *net, const Act &in, const Act &out)
+{
+    const int d = net->dims[in.lvl];
+    nn_pool2(in.p, out.p, in.C / 16 * d, d, d, net->s);
+}
+void pool_bwd(cl_net *net, const Act &gpool, const Act &g, const Act &Y)
+{
+    const int d = net->dims[g.lvl];
+    nn_pool2_bwd(gpool.p, g.p, Y.p, net->opt.slope, g.C / 16 * d, d, d, net->s);
+}
+void up(cl_net *net, const Act &in, const Act &out)
+{
+    const int d = net->dims[out.lvl];
+    nn_up2(in.p, out.p, in.C / 16 * d, d, d, net->s);
+}
+void up_bwd(cl_net *net, const Act &g, const Act &gin, const Act &Y)
+{
+    const int d = net->dims[g.lvl];
+    nn_up2_bwd(g.p, gin.p, Y.p, net->opt.slope, gin.C / 16 * d, d, d, net->s);
 }
 
 void pack_all(cl_net *net)
@@ -150,26 +177,25 @@ void forward(cl_net *net, const float *m0, const float *m1)
 {
     hipStream_t s = net->s;
     auto &C = net->conv;
-    const int *dm = net->dims;
     nn_pack_input(m0, m1, net->x0.p, vox(net, 0), s);
     conv_fwd(net, C[0], net->x0, net->a1);
     conv_fwd(net, C[1], net->a1, net->e1);
-    nn_pool2(net->e1.p, net->p1.p, dm[0], dm[0], dm[0], 16, s);
+    pool(net, net->e1, net->p1);
     conv_fwd(net, C[2], net->p1, net->a2);
     conv_fwd(net, C[3], net->a2, net->e2);
-    nn_pool2(net->e2.p, net->p2.p, dm[1], dm[1], dm[1], 32, s);
+    pool(net, net->e2, net->p2);
     conv_fwd(net, C[4], net->p2, net->a3);
     conv_fwd(net, C[5], net->a3, net->e3);
-    nn_pool2(net->e3.p, net->p3.p, dm[2], dm[2], dm[2], 64, s);
+    pool(net, net->e3, net->p3);
     conv_fwd(net, C[6], net->p3, net->a4);
     conv_fwd(net, C[7], net->a4, net->e4);
-    nn_up2cat(net->e4.p, net->e3.p, net->c3.p, dm[2], dm[2], dm[2], 128, 64, s);
+    up(net, net->e4, net->c3);
     conv_fwd(net, C[8], net->c3, net->b3);
     conv_fwd(net, C[9], net->b3, net->d3);
-    nn_up2cat(net->d3.p, net->e2.p, net->c2.p, dm[1], dm[1], dm[1], 64, 32, s);
+    up(net, net->d3, net->c2);
     conv_fwd(net, C[10], net->c2, net->b2);
     conv_fwd(net, C[11], net->b2, net->d2);
-    nn_up2cat(net->d2.p, net->e1.p, net->c1.p, dm[0], dm[0], dm[0], 32, 16, s);
+    up(net, net->d2, net->c1);
     conv_fwd(net, C[12], net->c1, net->b1);
     conv_fwd(net, C[13], net->b1, net->d1);
     nn_head(net->d1.p, net->param + net->head_w, net->param + net->head_b, net->vout, vox(net, 0), 16, s);
@@ -177,51 +203,49 @@ void forward(cl_net *net, const float *m0, const float *m1)
 }
 
 // gradient of the loss w.r.t. every parameter into net->grad (overwritten);
-// net->gv must hold dLoss/dv
+// net->gv must hold dLoss/dv.  Every gradient passes through the LeakyReLU
+// below it where it is written, so what a convolution receives is its dz.
 void backward(cl_net *net)
 {
     hipStream_t s = net->s;
     auto &C = net->conv;
-    const int *dm = net->dims;
-    nn_head_bwd(net->d1.p, net->gv, net->param + net->head_w, net->gd1.p, net->dpart, net->nparts, net->dhead,
-                vox(net, 0), 16, s);
+    nn_head_bwd(net->d1.p, net->gv, net->param + net->head_w, net->opt.slope, net->gd1.p, net->dpart, net->nparts,
+                net->dhead, vox(net, 0), s);
     hipLaunchKernelGGL(k_d2f_add, dim3(1), dim3(64), 0, s, net->dhead, net->grad + net->head_w, 51, 0);
     // decoder L1
-    Act gb1{net->g_a.p, 0, 16}, gc1{net->g_b.p, 0, 48};
-    conv_bwd(net, C[13], net->b1, net->d1, net->gd1, &gb1);
-    conv_bwd(net, C[12], net->c1, net->b1, gb1, &gc1);
-    Act gd2{net->gd2.p, 1, 32};
-    nn_up2cat_bwd(gc1.p, gd2.p, net->ge1.p, dm[0], dm[0], dm[0], 32, 16, 0, s);
+    const Act gb1{net->g_a.p, 0, 16}, ge1 = part(net, net->gc1, 32, 16);
+    conv_bwd(net, C[13], net->b1, net->gd1, &gb1, &net->b1);
+    conv_bwd(net, C[12], net->c1, gb1, &net->gc1, nullptr);
+    up_bwd(net, net->gc1, net->gd2, net->d2);
     // decoder L2
-    Act gb2{net->g_a.p, 1, 32}, gc2{net->g_b.p, 1, 96};
-    conv_bwd(net, C[11], net->b2, net->d2, gd2, &gb2);
-    conv_bwd(net, C[10], net->c2, net->b2, gb2, &gc2);
-    Act gd3{net->gd3.p, 2, 64};
-    nn_up2cat_bwd(gc2.p, gd3.p, net->ge2.p, dm[1], dm[1], dm[1], 64, 32, 0, s);
+    const Act gb2{net->g_a.p, 1, 32}, ge2 = part(net, net->gc2, 64, 32);
+    conv_bwd(net, C[11], net->b2, net->gd2, &gb2, &net->b2);
+    conv_bwd(net, C[10], net->c2, gb2, &net->gc2, nullptr);
+    up_bwd(net, net->gc2, net->gd3, net->d3);
     // decoder L3
-    Act gb3{net->g_a.p, 2, 64}, gc3{net->g_b.p, 2, 192};
-    conv_bwd(net, C[9], net->b3, net->d3, gd3, &gb3);
-    conv_bwd(net, C[8], net->c3, net->b3, gb3, &gc3);
-    nn_up2cat_bwd(gc3.p, net->ge4.p, net->ge3.p, dm[2], dm[2], dm[2], 128, 64, 0, s);
+    const Act gb3{net->g_a.p, 2, 64}, ge3 = part(net, net->gc3, 128, 64);
+    conv_bwd(net, C[9], net->b3, net->gd3, &gb3, &net->b3);
+    conv_bwd(net, C[8], net->c3, gb3, &net->gc3, nullptr);
+    up_bwd(net, net->gc3, net->ge4, net->e4);
     // bottleneck
-    Act ga4{net->g_a.p, 3, 128}, gp3{net->g_c.p, 3, 64};
-    conv_bwd(net, C[7], net->a4, net->e4, net->ge4, &ga4);
-    conv_bwd(net, C[6], net->p3, net->a4, ga4, &gp3);
-    nn_pool2_bwd(gp3.p, net->ge3.p, dm[2], dm[2], dm[2], 64, 1, s);
+    const Act ga4{net->g_a.p, 3, 128}, gp3{net->g_c.p, 3, 64};
+    conv_bwd(net, C[7], net->a4, net->ge4, &ga4, &net->a4);
+    conv_bwd(net, C[6], net->p3, ga4, &gp3, nullptr);
+    pool_bwd(net, gp3, ge3, net->e3);
     // encoder L3
-    Act ga3{net->g_a.p, 2, 64}, gp2{net->g_c.p, 2, 32};
-    conv_bwd(net, C[5], net->a3, net->e3, net->ge3, &ga3);
-    conv_bwd(net, C[4], net->p2, net->a3, ga3, &gp2);
-    nn_pool2_bwd(gp2.p, net->ge2.p, dm[1], dm[1], dm[1], 32, 1, s);
+    const Act ga3{net->g_a.p, 2, 64}, gp2{net->g_c.p, 2, 32};
+    conv_bwd(net, C[5], net->a3, ge3, &ga3, &net->a3);
+    conv_bwd(net, C[4], net->p2, ga3, &gp2, nullptr);
+    pool_bwd(net, gp2, ge2, net->e2);
     // encoder L2
-    Act ga2{net->g_a.p, 1, 32}, gp1{net->g_c.p, 1, 16};
-    conv_bwd(net, C[3], net->a2, net->e2, net->ge2, &ga2);
-    conv_bwd(net, C[2], net->p1, net->a2, ga2, &gp1);
-    nn_pool2_bwd(gp1.p, net->ge1.p, dm[0], dm[0], dm[0], 16, 1, s);
+    const Act ga2{net->g_a.p, 1, 32}, gp1{net->g_c.p, 1, 16};
+    conv_bwd(net, C[3], net->a2, ge2, &ga2, &net->a2);
+    conv_bwd(net, C[2], net->p1, ga2, &gp1, nullptr);
+    pool_bwd(net, gp1, ge1, net->e1);
     // encoder L1
-    Act ga1{net->g_a.p, 0, 16};
-    conv_bwd(net, C[1], net->a1, net->e1, net->ge1, &ga1);
-    conv_bwd(net, C[0], net->x0, net->a1, ga1, nullptr);
+    const Act ga1{net->g_a.p, 0, 16};
+    conv_bwd(net, C[1], net->a1, ge1, &ga1, &net->a1);
+    conv_bwd(net, C[0], net->x0, ga1, nullptr, nullptr);
     NCHK(hipGetLastError());
 }
 
@@ -319,17 +343,21 @@ int cl_net_create(cl_net **out, const cl_net_options *opt)
         net->dhead = (double *)nalloc(net, 64 * sizeof(double));
         if (hipHostMalloc((void **)&net->hscal, 4 * sizeof(double), hipHostMallocDefault) != hipSuccess)
             throw NFail{CL_ERR_OOM};
-        net->x0 = act(net, 0, 16); net->a1 = act(net, 0, 16); net->e1 = act(net, 0, 16);
-        net->p1 = act(net, 1, 16); net->a2 = act(net, 1, 32); net->e2 = act(net, 1, 32);
-        net->p2 = act(net, 2, 32); net->a3 = act(net, 2, 64); net->e3 = act(net, 2, 64);
+        net->x0 = act(net, 0, 16); net->a1 = act(net, 0, 16);
+        net->p1 = act(net, 1, 16); net->a2 = act(net, 1, 32);
+        net->p2 = act(net, 2, 32); net->a3 = act(net, 2, 64);
         net->p3 = act(net, 3, 64); net->a4 = act(net, 3, 128); net->e4 = act(net, 3, 128);
         net->c3 = act(net, 2, 192); net->b3 = act(net, 2, 64); net->d3 = act(net, 2, 64);
         net->c2 = act(net, 1, 96); net->b2 = act(net, 1, 32); net->d2 = act(net, 1, 32);
         net->c1 = act(net, 0, 48); net->b1 = act(net, 0, 16); net->d1 = act(net, 0, 16);
-        // gradient scratch: sized for the largest use at level 0 (48 channels)
-        net->g_a = act(net, 0, 16); net->g_b = act(net, 0, 48); net->g_c = act(net, 1, 32);
-        net->dz = act(net, 0, 48);
-        net->ge1 = act(net, 0, 16); net->ge2 = act(net, 1, 32); net->ge3 = act(net, 2, 64); net->ge4 = act(net, 3, 128);
+        // the encoder outputs that are skipped lie in the concatenated tensors,
+        // after the upsampled channels
+        net->e1 = part(net, net->c1, 32, 16);
+        net->e2 = part(net, net->c2, 64, 32);
+        net->e3 = part(net, net->c3, 128, 64);
+        net->g_a = act(net, 0, 16); net->g_c = act(net, 1, 32);
+        net->gc1 = act(net, 0, 48); net->gc2 = act(net, 1, 96); net->gc3 = act(net, 2, 192);
+        net->ge4 = act(net, 3, 128);
         net->gd1 = act(net, 0, 16); net->gd2 = act(net, 1, 32); net->gd3 = act(net, 2, 64);
         net->vout = (float *)nalloc(net, 3 * vox(net, 0) * sizeof(float));
         net->gv = (float *)nalloc(net, 3 * vox(net, 0) * sizeof(float));
@@ -561,7 +589,7 @@ int cl_nn_conv3(const void *in, const float *w, const float *b, void *out, int o
     if (!tile_count_ok(Kout / 16)) return CL_ERR_UNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
     nn_pack_weights(w, (unsigned short *)wpack, Ci, Co, transpose, s);
-    nn_conv3((const unsigned short *)in, wpack, transpose ? nullptr : b, out, out_f32,
+    nn_conv3((const unsigned short *)in, wpack, transpose ? nullptr : b, out, out_f32, nullptr,
              nn_channels_last(Kin), nn_channels_last(Kout), D, H, W, Kin, Kout, act, slope, s);
     return hipGetLastError() == hipSuccess ? CL_OK : CL_ERR_HIP;
 }

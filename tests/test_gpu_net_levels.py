@@ -1,0 +1,129 @@
+"""The network's passes against the same network put together from single layers
+(nn_conv3, nn_conv3_dw on channels-last tensors) and torch, with BF16 rounding at
+the same places.  The two lay their tensors out differently and the network
+passes gradients through the LeakyReLU where they are written, but every value is
+the same sum in the same order: the results are equal.  Only the head's 16
+products per voxel may be contracted otherwise (17 roundings of 2^-24)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+SLOPE = 0.2
+LAYERS = [(16, 16), (16, 16), (16, 32), (32, 32), (32, 64), (64, 64), (64, 128), (128, 128), (192, 64), (64, 64),
+          (96, 32), (32, 32), (48, 16), (16, 16)]
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _children(x):
+    """Sum over the 2 x 2 x 2 children of a coarse voxel, in FP32, z then y then x."""
+    x, s = x.float(), 0.0
+    for a in range(2):
+        for b in range(2):
+            for c in range(2):
+                s = s + x[a::2, b::2, c::2]
+    return s
+
+
+def _up(x):
+    for a in range(3):
+        x = x.repeat_interleave(2, a)
+    return x
+
+
+def _through(g, y):
+    """LeakyReLU backward of a BF16 gradient from the output y."""
+    return torch.where(y.float() > 0, g.float(), SLOPE * g.float()).to(torch.bfloat16)
+
+
+# 32: every convolution on single-plane bricks; 128: all tilings, walked
+@pytest.mark.parametrize("n", [32, 128])
+def test_network_equals_its_layers(n):
+    from paper_2209_08189_amd.claire import Net, nn_conv3, nn_conv3_dw
+    g = torch.Generator().manual_seed(n)
+    wb, parts = [], []
+    for ci, co in LAYERS:
+        w = (2 * torch.rand((27, ci, co), generator=g) - 1) * (6.0 / (27 * ci)) ** 0.5
+        b = 0.01 * torch.randn(co, generator=g)
+        wb.append((w.cuda(), b.cuda()))
+        parts += [w.reshape(-1), b]
+    head = torch.zeros(16, 3)          # one component: its gradient is a single product
+    head[:, 0] = 0.3 * torch.randn(16, generator=g)
+    params = torch.cat(parts + [head.reshape(-1), torch.zeros(3)])
+    m0, m1 = (torch.rand((n, n, n), generator=g).cuda() for _ in range(2))
+    label = 0.1 * torch.randn((3, n, n, n), generator=g).cuda()
+    net = Net(in_n=n)
+    net.set_params(params.cuda())
+    v = net.forward(m0, m1)
+    _, grad = net.loss_grad(m0, m1, label)
+
+    def conv(i, x):
+        return nn_conv3(x.contiguous(), wb[i][0], wb[i][1], act=1, slope=SLOPE, out_f32=False)
+
+    def pool(x):
+        return (_children(x) * 0.125).to(torch.bfloat16)
+
+    x0 = torch.zeros((n, n, n, 16), dtype=torch.bfloat16, device="cuda")
+    x0[..., 0], x0[..., 1] = m0, m1
+    t = {}                             # inputs of every layer
+    t[0] = x0
+    t[1] = conv(0, t[0])
+    e1 = conv(1, t[1])
+    t[2] = pool(e1)
+    t[3] = conv(2, t[2])
+    e2 = conv(3, t[3])
+    t[4] = pool(e2)
+    t[5] = conv(4, t[4])
+    e3 = conv(5, t[5])
+    t[6] = pool(e3)
+    t[7] = conv(6, t[6])
+    e4 = conv(7, t[7])
+    t[8] = torch.cat([_up(e4), e3], -1)
+    t[9] = conv(8, t[8])
+    d3 = conv(9, t[9])
+    t[10] = torch.cat([_up(d3), e2], -1)
+    t[11] = conv(10, t[10])
+    d2 = conv(11, t[11])
+    t[12] = torch.cat([_up(d2), e1], -1)
+    t[13] = conv(12, t[12])
+    d1 = conv(13, t[13])
+    w0 = head[:, 0].cuda()
+    ref = (d1.double() * w0.double()).sum(-1)
+    mag = (d1.double() * w0.double()).abs().sum(-1)
+    assert ((v[0].double() - ref).abs() <= 17 * 2.0 ** -24 * mag).all()
+    assert not v[1:].any()
+
+    gw = {}
+
+    def back(i, dz, below=None):
+        """Weight gradient of layer i from its dz; the gradient of its input, through the activation `below`."""
+        gw[i] = nn_conv3_dw(t[i].contiguous(), dz.contiguous())
+        gx = nn_conv3(dz.contiguous(), wb[i][0], None, act=0, transpose=True, out_f32=False)
+        return gx if below is None else _through(gx, below)
+
+    def pooled(gpool, gskip, y):
+        return _through((gskip.float() + _up(gpool).float() * 0.125).to(torch.bfloat16), y)
+
+    gv = (v[0] - label[0]) * torch.tensor(1.0 / (3.0 * n ** 3), dtype=torch.float32, device="cuda")
+    dz = _through((w0 * gv[..., None]).to(torch.bfloat16), d1)
+    gc1 = back(12, back(13, dz, t[13]))
+    dz = _through(_children(gc1[..., :32]).to(torch.bfloat16), d2)
+    gc2 = back(10, back(11, dz, t[11]))
+    dz = _through(_children(gc2[..., :64]).to(torch.bfloat16), d3)
+    gc3 = back(8, back(9, dz, t[9]))
+    dz = _through(_children(gc3[..., :128]).to(torch.bfloat16), e4)
+    dz = pooled(back(6, back(7, dz, t[7])), gc3[..., 128:], e3)
+    dz = pooled(back(4, back(5, dz, t[5])), gc2[..., 64:], e2)
+    dz = pooled(back(2, back(3, dz, t[3])), gc1[..., 32:], e1)
+    back(0, back(1, dz, t[1]))
+    off = 0
+    for i, (ci, co) in enumerate(LAYERS):
+        k = 27 * ci * co
+        assert torch.equal(grad[off:off + k], gw[i][0].reshape(-1)), i
+        assert torch.equal(grad[off + k:off + k + co], gw[i][1]), i
+        off += k + co
