@@ -422,7 +422,7 @@ void matvec(cl_ctx *ctx, const float *vt, float *Hvt, const float *Avt_known = n
             launch_inc_source_fd(ctx->g, ctx->dts, slot(ctx, ctx->m, ctx->dts, 0), vt, 0.5f * dt, ctx->dta,
                                  ctx->q[0], ctx->s);
         });
-    } else if (sources_march(ctx->g, nt)) {
+    } else if (sources_march(ctx->g)) {
         const QuadArgs qa = quad_args(ctx);
         run(ctx, CL_K_VEC, [&] {
             launch_inc_sources_march(ctx->g, ctx->dts, qa, vt, nt, 0.5f * dt, ctx->dta, ctx->q[0], ctx->S, ctx->s);
@@ -748,8 +748,7 @@ int solve(cl_ctx *ctx, const int *forced_pcg, const double *forced_alpha, int fo
 }
 
 // Levels of grad_h m^j a context stores: every level where a kernel reads
-// them (grids the marching FD8 kernels do not cover, or more time steps than
-// the all-level source pass takes), level 0 for the full-resolution
+// them (grids the marching FD8 kernels do not cover), level 0 for the full-resolution
 // zero-velocity preconditioner (the two-level one takes the gradient of its
 // coarse template), none otherwise (and none in the lean layout)
 int grad_levels(int n1, int n2, int n3, const cl_options &o, bool lean)
@@ -758,7 +757,7 @@ int grad_levels(int n1, int n2, int n3, const cl_options &o, bool lean)
     const Grid g = make_grid(n1, n2, n3, o.interp_order);
     QuadArgs qa{};
     qa.count = o.nt + 1;
-    if (!quadrature_marches(g, qa) || !sources_march(g, o.nt)) return o.nt + 1;
+    if (!quadrature_marches(g, qa) || !sources_march(g)) return o.nt + 1;
     return o.precond == CL_PRECOND_H0 ? 1 : 0;
 }
 

@@ -171,8 +171,8 @@ struct QuadArgs {
     int lean;                 // 1: use m[] (storage dtype dt_m), 0: use G[]
     int dt_m;
 };
-// all-level sources by the marching FD8 kernel when sources_march(g, nt)
-bool sources_march(const Grid &g, int nt);
+// all-level sources by the marching FD8 kernel when sources_march(g)
+bool sources_march(const Grid &g);
 void launch_inc_sources_march(const Grid &g, int dt_m, const QuadArgs &qa, const float *vt, int nt, float scale,
                               int dt_q, void *q0, float *S, hipStream_t s);
 // out3 = addend3 (may be NULL) + sum_j w_j lam^j G^j

@@ -246,6 +246,7 @@ __device__ __forceinline__ float fd8_lds(const float *c, int st, float ih)   // 
 // MODE 1: out1 = scale * (-vt . grad_h m^0) (NL = 1).
 // MODE 2: the incremental sources of every level at once, s^t = -vt .
 //         grad_h m^t: out1 = scale * s^0, out3[(t - 1) N ..] = s^t, t >= 1.
+// MODE 3: a later group of levels of the same: out3[t N ..] = s^t, t >= 0.
 template <typename Tm, typename Tl, typename To, int NL, int MODE>
 __global__ __launch_bounds__(TPB_M) void k_fd_march(Grid g, MarchGeom mg, QuadArgs qa, const float *__restrict__ add,
                                                     float *__restrict__ out3, const float *__restrict__ dp,
@@ -368,17 +369,17 @@ __global__ __launch_bounds__(TPB_M) void k_fd_march(Grid g, MarchGeom mg, QuadAr
                 b0 = fmaf(lw[t], d0, b0);
                 b1 = fmaf(lw[t], d1, b1);
                 b2 = fmaf(lw[t], d2, b2);
-            } else if (MODE == 2) {
+            } else if (MODE >= 2) {
                 const float sv = -(e0 * d0 + e1 * d1 + e2 * d2);
-                if (t == 0) stf(&at(out1, p), scale * sv);
-                else at(out3 + (size_t)(t - 1) * N, p) = sv;
+                if (MODE == 2 && t == 0) stf(&at(out1, p), scale * sv);
+                else at(out3 + (size_t)(MODE == 2 ? t - 1 : t) * N, p) = sv;
             } else {
                 b0 = d0;
                 b1 = d1;
                 b2 = d2;
             }
         }
-        if (MODE == 2) {
+        if (MODE >= 2) {
         } else if (MODE == 0) {
             if (add) {
                 b0 += e0;
@@ -439,11 +440,6 @@ void launch_state_grad(const Grid &g, int dt_m, const StateGradArgs &a, int coun
     });
 }
 
-bool sources_march(const Grid &g, int nt) { return g.n3 >= 64 && g.n2 >= 8 && nt + 1 <= 5; }
-
-void launch_inc_sources_march(const Grid &g, int dt_m, const QuadArgs &qa, const float *vt, int nt, float scale,
-                              int dt_q, void *q0, float *S, hipStream_t s);
-
 void launch_inc_sources(const Grid &g, const float *G, const float *vt, int nt, float scale, int dt_q, void *q0,
                         float *S, hipStream_t s)
 {
@@ -464,10 +460,14 @@ namespace {
 // The marching kernels need whole 64 x 8 tiles in (x3, x2).  Each tile
 // column along x1 is cut into nch chunks, and a chunk reads 8 halo planes of
 // m beside its own.  nch minimises (rounds of resident blocks) x (longest
-// chunk + halo), with two resident 512-thread blocks per CU (the register
-// use of five time levels): at 256^3 four chunks of 64 planes, 512 blocks
-// that all run at once (12.5 % halo reads), where 16-plane chunks took 2048
-// blocks in four rounds (50 % halo reads).
+// chunk + start), with two resident 512-thread blocks per CU (the register
+// use of five time levels).  The start, the 8 planes of the ring requested
+// together and the first wait, costs about as much as four steps.  At 256^3
+// this gives four chunks of 64 planes, 512 blocks that all run at once (12.5 %
+// halo reads), where 16-plane chunks took 2048 blocks in four rounds (50 %
+// halo reads).  On small grids the chip is filled by short chunks, down to
+// single planes at 64^3, whose halo comes from L2: quadrature 20 -> 9 us,
+// sources 16 -> 7 us against chunks of 8 planes on 64 blocks.
 bool march_ok(const Grid &g) { return g.n3 >= MX && g.n2 >= MY; }
 
 int device_cus()
@@ -490,8 +490,8 @@ MarchGeom march_geom(const Grid &g)
     const long tiles = (long)mg.ntx * mg.nty, resident = 2L * device_cus();
     double best = 1e300;
     mg.nch = 1;
-    for (int n = 1; n <= std::max(1, g.n1 / 8); ++n) {
-        const double cost = (double)((tiles * n + resident - 1) / resident) * ((g.n1 + n - 1) / n + 2 * MH);
+    for (int n = 1; n <= g.n1; ++n) {
+        const double cost = (double)((tiles * n + resident - 1) / resident) * ((g.n1 + n - 1) / n + 4);
         if (cost < best) {
             best = cost;
             mg.nch = n;
@@ -577,27 +577,52 @@ void launch_quadrature_dot(const Grid &g, int dt_lam, const QuadArgs &qa, const 
     });
 }
 
+bool sources_march(const Grid &g) { return march_ok(g); }
+
 // sources of every level from m^0 .. m^nt by the marching kernel (the
-// same FD8 and products as from stored gradients, bit for bit)
+// same FD8 and products as from stored gradients, bit for bit), in groups of
+// MAX_NL levels.  With nt = 8 at 512^3 (FP16) two groups read m and vt twice,
+// 3.9 -> 2.6 ms against 27 fields of stored gradients (which nothing stores
+// then: 14.5 GB and 7.2 ms per velocity).
 void launch_inc_sources_march(const Grid &g, int dt_m, const QuadArgs &qa, const float *vt, int nt, float scale,
                               int dt_q, void *q0, float *S, hipStream_t s)
 {
     with_dtype(dt_m, [&](auto tm) {
         using Tm = decltype(tm);
-        with_dtype(dt_q, [&](auto tq) {
-            using Tq = decltype(tq);
-            const dim3 grid(march_blocks(g));
-            switch (nt + 1) {
+        const dim3 grid(march_blocks(g));
+        for (int t0 = 0; t0 <= nt; t0 += MAX_NL) {
+            QuadArgs sub{};
+            const int count = std::min(MAX_NL, nt + 1 - t0);
+            for (int t = 0; t < count; ++t) sub.m[t] = qa.m[t0 + t];
+            if (t0 == 0) {
+                with_dtype(dt_q, [&](auto tq) {
+                    using Tq = decltype(tq);
+                    switch (count) {
 #define CLH_SM(NL)                                                                                                   \
     case NL:                                                                                                         \
-        hipLaunchKernelGGL((k_fd_march<Tm, float, Tq, NL, 2>), grid, dim3(TPB_M), 0, s, g, march_geom(g), qa,        \
+        hipLaunchKernelGGL((k_fd_march<Tm, float, Tq, NL, 2>), grid, dim3(TPB_M), 0, s, g, march_geom(g), sub,       \
                            (const float *)nullptr, S, (const float *)nullptr, (double *)nullptr, vt, scale, (Tq *)q0); \
         break;
-                CLH_SM(2) CLH_SM(3) CLH_SM(4) CLH_SM(5)
+                        CLH_SM(2) CLH_SM(3) CLH_SM(4) CLH_SM(5)
 #undef CLH_SM
-            default: break;
+                    default: break;
+                    }
+                });
+            } else {
+                float *out = S + (size_t)(t0 - 1) * g.N;
+                switch (count) {
+#define CLH_SM(NL)                                                                                                   \
+    case NL:                                                                                                         \
+        hipLaunchKernelGGL((k_fd_march<Tm, float, float, NL, 3>), grid, dim3(TPB_M), 0, s, g, march_geom(g), sub,    \
+                           (const float *)nullptr, out, (const float *)nullptr, (double *)nullptr, vt, 1.0f,         \
+                           (float *)nullptr);                                                                        \
+        break;
+                    CLH_SM(1) CLH_SM(2) CLH_SM(3) CLH_SM(4) CLH_SM(5)
+#undef CLH_SM
+                default: break;
+                }
             }
-        });
+        }
     });
 }
 
