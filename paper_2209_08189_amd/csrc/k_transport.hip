@@ -381,11 +381,15 @@ __device__ __forceinline__ TileBox tile_box(const int *__restrict__ bx, const Ti
     return B;
 }
 
-// SL tile kernel: 512 threads, each owning QT = 4 nodes along x1.
-constexpr int SPLIT = 2, QT = TZ / SPLIT, TPB_SL = 256 * SPLIT;
+// SL tile kernels: SP x 256 threads, each owning TZ / SP nodes along x1.  SP =
+// 2 (512 threads) where the tiles fill the chip; SP = 4 on grids of at most two
+// tiles per CU (tile_split), where a step takes one tile's own time and half the
+// nodes per thread and half the box rows per wavefront shorten it: 64^3 7.1 -> 6.3
+// us per step, 32^3 6.5 -> 6.0 us, 128x128x64 matvec 183 -> 177 us.
+constexpr int tile_threads(int sp) { return 256 * sp; }
 
 // Feet and epilogue operand of the QT nodes of this thread.
-template <int MODE, bool AOS>
+template <int MODE, bool AOS, int QT>
 __device__ __forceinline__ void load_feet(const Grid &g, const float *__restrict__ d, const SLParams &prm,
                                           const TileIdx &t, float (&d1)[QT], float (&d2)[QT], float (&d3)[QT],
                                           float (&e)[QT])
@@ -428,14 +432,14 @@ __device__ __forceinline__ void load_feet(const Grid &g, const float *__restrict
 // bb = wv, wv + NW, ... (NW waves); lane l loads column l (FP32) or the column pair 2l,
 // 2l+1 (16-bit) into LDS at row start + 4 l bytes; lanes past the row are
 // switched off.  A row wider than one wave's load takes several chunks.
-template <typename Tu>
+template <typename Tu, int SP>
 __device__ __forceinline__ void stage_box(const Grid &g, const Tu *__restrict__ u, Tu *box, const TileIdx &t,
                                           const TileBox &B)
 {
     constexpr int PX = box_px<Tu>();
     constexpr int EPL = sizeof(Tu) == 2 ? 2 : 1;       // elements per lane
     constexpr int NCH = (PX + 64 * EPL - 1) / (64 * EPL);
-    constexpr int NW = TPB_SL / 64;
+    constexpr int NW = tile_threads(SP) / 64;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l64 = threadIdx.x & 63;
     const int gi0 = t.i0 + B.r1, gj0 = t.ty * TY + B.r2;
@@ -564,7 +568,7 @@ __device__ __forceinline__ unsigned stencil_addr(const BoxAddr &A, int q, float 
 // Trilinear gather of the QT nodes of this thread from a staged box (box
 // origin at the lowest floor of the tile's feet), with the operations of
 // lin_node.
-template <typename Tu, int MODE>
+template <typename Tu, int MODE, int QT>
 __device__ __forceinline__ void compute_tile_lin(const Tu *box, const TileIdx &t, const TileBox &B,
                                                  const float (&d1)[QT], const float (&d2)[QT], const float (&d3)[QT],
                                                  const float (&e)[QT], const SLParams &prm, float (&res)[QT])
@@ -594,7 +598,7 @@ __device__ __forceinline__ void compute_tile_lin(const Tu *box, const TileIdx &t
 
 // Gather of the QT nodes of this thread from a staged box and the epilogue,
 // into res.  ORDER 1: trilinear, 3: tricubic.
-template <typename Tu, int MODE, int ORDER>
+template <typename Tu, int MODE, int ORDER, int QT>
 __device__ __forceinline__ void compute_tile(const Tu *box, const TileIdx &t, const TileBox &B, const float (&d1)[QT], const float (&d2)[QT],
                                              const float (&d3)[QT], const float (&e)[QT], const SLParams &prm,
                                              float (&res)[QT])
@@ -665,7 +669,7 @@ __device__ __forceinline__ void compute_tile(const Tu *box, const TileIdx &t, co
     }
 }
 
-template <typename To>
+template <typename To, int QT>
 __device__ __forceinline__ void store_tile(To *__restrict__ out, const TileIdx &t, const float (&res)[QT])
 {
     char *b = reinterpret_cast<char *>(out);
@@ -676,7 +680,7 @@ __device__ __forceinline__ void store_tile(To *__restrict__ out, const TileIdx &
 
 // 16-bit boxes: copy B (words after copy A) holds the elements shifted by
 // one, B word j = elements 2j+1, 2j+2 of copy A, built from copy A in LDS.
-template <typename Tu>
+template <typename Tu, int SP>
 __device__ __forceinline__ void shift_copy(const Tu *box, const TileBox &B)
 {
     constexpr int PX = box_px<Tu>();
@@ -684,7 +688,7 @@ __device__ __forceinline__ void shift_copy(const Tu *box, const TileBox &B)
     const unsigned A0 = lds_addr(box), B0 = A0 + PZ * PY * PX * 2;
     const int nw = (B.E3 + B.sh + 1) >> 1;             // words of copy A in use per row
     const int tot = B.E1 * PY * WPR;
-    for (int e = threadIdx.x; e < tot; e += TPB_SL) {
+    for (int e = threadIdx.x; e < tot; e += tile_threads(SP)) {
         const int r = e / WPR, j = e - r * WPR;
         const int bb = r - (r / PY) * PY;
         if (bb < B.E2 && j < nw) {
@@ -697,7 +701,7 @@ __device__ __forceinline__ void shift_copy(const Tu *box, const TileBox &B)
 // A tile whose box exceeds the pitches: each node gathers straight from
 // global memory, with the weights and contraction order of the tiled path
 // (same results), one node at a time so that the path needs few registers.
-template <typename Tu, typename To, int MODE, int ORDER, bool AOS>
+template <typename Tu, typename To, int MODE, int ORDER, bool AOS, int QT>
 __device__ __forceinline__ void tile_fallback(const Grid &g, const Tu *__restrict__ u, const float *__restrict__ d,
                                               const SLParams &prm, To *__restrict__ out, const TileIdx &t)
 {
@@ -725,8 +729,8 @@ __device__ __forceinline__ void tile_fallback(const Grid &g, const Tu *__restric
 // needs about 50 VGPRs (the global-memory fallback runs one node at a time
 // and adds none), so the 39.9 KB box sets the occupancy: four 512-thread
 // workgroups per CU, whose phases (waiting for memory, gathering) overlap.
-template <typename Tu, typename To, int MODE, int ORDER, bool AOS>
-__global__ __launch_bounds__(TPB_SL, 8) void k_sl_tile(Grid g, const Tu *__restrict__ u, const float *__restrict__ d,
+template <typename Tu, typename To, int MODE, int ORDER, bool AOS, int SP>
+__global__ __launch_bounds__(tile_threads(SP), 8) void k_sl_tile(Grid g, const Tu *__restrict__ u, const float *__restrict__ d,
                                                   SLParams prm, To *__restrict__ out, const int *__restrict__ boxes,
                                                   int ntx, int nty, int nblk)
 {
@@ -737,20 +741,21 @@ __global__ __launch_bounds__(TPB_SL, 8) void k_sl_tile(Grid g, const Tu *__restr
     // XCD-contiguous tile order (workgroups go round-robin to the 8 XCDs)
     const int b = blockIdx.x;
     const int tile = (nblk & 7) ? b : (b & 7) * (nblk >> 3) + (b >> 3);
-    const TileIdx t = tile_idx<SPLIT>(g, tile, ntx, nty);
+    constexpr int QT = TZ / SP;
+    const TileIdx t = tile_idx<SP>(g, tile, ntx, nty);
     const TileBox B = tile_box<Tu>(boxes + 8 * tile, t);
     if (!B.fits) {                 // the whole workgroup takes this branch
-        tile_fallback<Tu, To, MODE, ORDER, AOS>(g, u, d, prm, out, t);
+        tile_fallback<Tu, To, MODE, ORDER, AOS, QT>(g, u, d, prm, out, t);
         return;
     }
     float d1[QT], d2[QT], d3[QT], e[QT], r[QT];
-    load_feet<MODE, AOS>(g, d, prm, t, d1, d2, d3, e);
+    load_feet<MODE, AOS, QT>(g, d, prm, t, d1, d2, d3, e);
     __builtin_amdgcn_sched_barrier(0);
-    stage_box(g, u, box, t, B);
+    stage_box<Tu, SP>(g, u, box, t, B);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (sizeof(Tu) == 2) {
-        shift_copy(box, B);
+        shift_copy<Tu, SP>(box, B);
         __syncthreads();
     }
     compute_tile<Tu, MODE, ORDER>(box, t, B, d1, d2, d3, e, prm, r);
@@ -829,16 +834,16 @@ __global__ __launch_bounds__(TPB) void k_feet_node(Grid g, const float *__restri
 // an SL step and four workgroups per CU overlap one another's phases (two
 // boxes with the next component staged ahead: two workgroups per CU and 180
 // spilled registers, 1300 us per direction).
-template <int ORDER>
-__global__ __launch_bounds__(TPB_SL, 8) void k_feet_tile(Grid g, const float *__restrict__ v, FeetArgs fa, int ntx,
+template <int ORDER, int SP>
+__global__ __launch_bounds__(tile_threads(SP), 8) void k_feet_tile(Grid g, const float *__restrict__ v, FeetArgs fa, int ntx,
                                                          int nty, int nblk)
 {
-    constexpr int LO = ORDER == 1 ? 0 : 1, SPAN = ORDER == 1 ? 2 : 4;
+    constexpr int LO = ORDER == 1 ? 0 : 1, SPAN = ORDER == 1 ? 2 : 4, QT = TZ / SP;
     __shared__ __align__(16) float box[PZ * PY * box_px<float>()];
-    __shared__ int red[2][TPB_SL / 64][6];
+    __shared__ int red[2][tile_threads(SP) / 64][6];
     const int b = blockIdx.x;
     const int tile = (nblk & 7) ? b : (b & 7) * (nblk >> 3) + (b >> 3);
-    const TileIdx t = tile_idx<SPLIT>(g, tile, ntx, nty);
+    const TileIdx t = tile_idx<SP>(g, tile, ntx, nty);
     const size_t N = g.N;
     const float a = fa.a[blockIdx.y];
     float *dout = fa.d[blockIdx.y];
@@ -887,7 +892,7 @@ __global__ __launch_bounds__(TPB_SL, 8) void k_feet_tile(Grid g, const float *__
         // three they would take 48 registers
 #pragma unroll
         for (int q = 0; q < QT; ++q) asm volatile("" : "+v"(d1[q]), "+v"(d2[q]), "+v"(d3[q]));
-        stage_box(g, v + c * N, box, t, B);
+        stage_box<float, SP>(g, v + c * N, box, t, B);
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         compute_tile<float, SL_STATE, ORDER>(box, t, B, d1, d2, d3, e, SLParams{}, vi);
@@ -912,6 +917,9 @@ __global__ __launch_bounds__(TPB_SL, 8) void k_feet_tile(Grid g, const float *__
 
 inline bool tiled(const Grid &g) { return g.n3 >= TX && g.n2 >= TY && g.n1 >= TZ; }
 
+// threads per tile (in units of 256): see k_sl_tile
+inline int tile_split(int nblk) { return nblk <= 512 ? 4 : 2; }
+
 inline dim3 grid_of(const Grid &g) { return dim3((g.N + TPB - 1) / TPB); }
 
 // AOS: interleaved feet (the solver's own); otherwise three fields
@@ -922,12 +930,17 @@ void launch_sl(const Grid &g, const Tu *u, const float *d, const SLParams &prm, 
     if (tiled(g)) {
         const int ntx = g.n3 / TX, nty = g.n2 / TY, ntz = g.n1 / TZ;
         const int nblk = ntx * nty * ntz;
-        if (g.interp == 1)
-            hipLaunchKernelGGL((k_sl_tile<Tu, To, MODE, 1, AOS>), dim3(nblk), dim3(TPB_SL), 0, s, g, u, d, prm, out,
-                               boxes, ntx, nty, nblk);
-        else
-            hipLaunchKernelGGL((k_sl_tile<Tu, To, MODE, 3, AOS>), dim3(nblk), dim3(TPB_SL), 0, s, g, u, d, prm, out,
-                               boxes, ntx, nty, nblk);
+        auto go = [&](auto kernel, int sp) {
+            hipLaunchKernelGGL(kernel, dim3(nblk), dim3(tile_threads(sp)), 0, s, g, u, d, prm, out, boxes, ntx, nty,
+                               nblk);
+        };
+        if (tile_split(nblk) == 4) {
+            if (g.interp == 1) go(k_sl_tile<Tu, To, MODE, 1, AOS, 4>, 4);
+            else go(k_sl_tile<Tu, To, MODE, 3, AOS, 4>, 4);
+        } else {
+            if (g.interp == 1) go(k_sl_tile<Tu, To, MODE, 1, AOS, 2>, 2);
+            else go(k_sl_tile<Tu, To, MODE, 3, AOS, 2>, 2);
+        }
     } else if (g.interp == 1) {
         hipLaunchKernelGGL((k_sl_lin<Tu, To, MODE, AOS>), grid_of(g), dim3(TPB), 0, s, g, u, d, prm, out);
     } else {
@@ -950,10 +963,16 @@ void launch_feet(const Grid &g, float dt, const float *v, float *df, float *db, 
     const unsigned dirs = db ? 2 : 1;
     if (tiled(g)) {
         const int ntx = g.n3 / TX, nty = g.n2 / TY, nblk = ntx * nty * (g.n1 / TZ);
-        if (g.interp == 1)
-            hipLaunchKernelGGL(k_feet_tile<1>, dim3(nblk, dirs), dim3(TPB_SL), 0, s, g, v, fa, ntx, nty, nblk);
-        else
-            hipLaunchKernelGGL(k_feet_tile<3>, dim3(nblk, dirs), dim3(TPB_SL), 0, s, g, v, fa, ntx, nty, nblk);
+        auto go = [&](auto kernel, int sp) {
+            hipLaunchKernelGGL(kernel, dim3(nblk, dirs), dim3(tile_threads(sp)), 0, s, g, v, fa, ntx, nty, nblk);
+        };
+        if (tile_split(nblk) == 4) {
+            if (g.interp == 1) go(k_feet_tile<1, 4>, 4);
+            else go(k_feet_tile<3, 4>, 4);
+        } else {
+            if (g.interp == 1) go(k_feet_tile<1, 2>, 2);
+            else go(k_feet_tile<3, 2>, 2);
+        }
     } else if (g.interp == 1) {
         hipLaunchKernelGGL(k_feet_node<1>, dim3(grid_of(g).x, dirs), dim3(TPB), 0, s, g, v, fa);
     } else {

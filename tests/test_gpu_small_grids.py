@@ -1,0 +1,51 @@
+"""Dispatches that depend on the grid's size, each against the path of the other
+size.  The operations of a node do not depend on the path: results are equal."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+# one period on at most 512 tiles of 8 x 8 x 32 nodes (1024 threads each), and
+# repeated on more (512 threads each)
+@pytest.mark.parametrize("order", [3, 1])
+@pytest.mark.parametrize("shape,times", [((64, 64, 64), (2, 2, 2)), ((16, 128, 32), (4, 1, 8))])
+def test_interpolation_repeats_with_its_period(shape, times, order):
+    from paper_2209_08189_amd.claire import interp_noalloc
+    g = torch.Generator().manual_seed(sum(shape) + order)
+    u = torch.randn(shape, generator=g).cuda()
+    x = [2 * torch.pi * torch.arange(n, dtype=torch.float32) / n for n in shape]
+    d = torch.sin(x[0])[:, None, None] + torch.cos(x[1])[None, :, None] * torch.sin(x[2])[None, None, :]
+    d = (torch.stack([d, d.flip(0), d.flip(2)]) * 0.9).contiguous().cuda()
+    d[:, 3, 5, 7] += 20.0                # one tile takes the global-memory path
+    one = interp_noalloc(u, d, torch.empty_like(u), order)
+    big = u.repeat(times)
+    many = interp_noalloc(big, d.repeat((1,) + times), torch.empty_like(big), order)
+    assert torch.equal(many, one.repeat(times))
+
+
+# sources of all levels in groups of five (full layout) against one level at a
+# time (lean layout); short chunks of the marching kernels on small grids
+@pytest.mark.parametrize("nt", [4, 5, 8, 10])
+@pytest.mark.parametrize("shape", [(16, 16, 64), (64, 64, 64), (128, 16, 64)])
+def test_grouped_sources_equal_single_levels(shape, nt):
+    from paper_2209_08189_amd.claire import Registration, query_workspace
+    g = torch.Generator().manual_seed(nt)
+    m0, m1 = (torch.rand(shape, generator=g).cuda() for _ in range(2))
+    v, vt = (0.1 * torch.randn((3,) + shape, generator=g).cuda() for _ in range(2))
+    out = []
+    for cap in (0, query_workspace(shape, nt=nt, workspace_cap=1)):
+        r = Registration(shape, nt=nt, workspace_cap=cap)
+        assert r.layout() == (1 if cap else 0)
+        r.set_images(m0, m1)
+        r.set_velocity(v)
+        grad, _, _ = r.gradient()
+        out.append((grad, r.hessian_matvec(vt)))
+    assert torch.equal(out[0][0], out[1][0])
+    assert torch.equal(out[0][1], out[1][1])
