@@ -16,13 +16,19 @@
 //             optional fused add.
 // Lines of 128 ... 1024 points take register-resident passes (below); the
 // generic passes for shorter lines work on LDS tiles: a workgroup owns a
-// tile of nl lines x L points (nl L = 4096 complex, 32 KB), coalesced
-// batched loads into LDS, then Stockham stages of radix 16 (and one of
-// radix 2/4/8 for the remainder) with every group's R values in registers,
-// twiddles from FP64-computed tables staged in LDS, and a coalesced store.  The LDS tile is stored as [q][l] with pitch nl + 1 so
-// that both row-wise and column-wise accesses are conflict-free.
+// tile of nl lines x L points (nl L <= 2048 complex, 16 KB), coalesced
+// batched loads into LDS, then Stockham stages of radix 8 (and one of
+// radix 2/4 for the remainder) with every group's R values in registers,
+// twiddles from FP64-computed tables staged in LDS, and a coalesced store.
+// The LDS tile is stored as [q][l] with pitch nl + 1 so that both row-wise and
+// column-wise accesses are conflict-free.  Grids of such lines are small and
+// a pass lasts as long as one tile: radix 16 on tiles of 4096 values left half
+// the threads of a stage idle behind the other half's longer chains.  Planes of
+// at most 64 x 64 points do their x3 and x2 passes in one kernel (k_fft_plane),
+// three passes in all: a 64^3 vector 49 -> 29 us, 32^3 35 -> 18 us.
 #include "internal.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace clh {
@@ -30,7 +36,7 @@ namespace clh {
 namespace {
 
 constexpr int TPB = 256;
-constexpr int TILE = 4096;   // complex values per LDS tile
+constexpr int TILE = 2048;   // complex values per LDS tile of the Stockham passes
 constexpr int EPT = TILE / TPB;
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
@@ -106,7 +112,7 @@ template <int R, bool INV> __device__ __forceinline__ void dft_reg(float2 *v)
 template <int R, bool INV, int NT>
 __device__ __forceinline__ void stage(float2 *lds, int P, int lognl, int logL, int logNs, const float2 *tw)
 {
-    constexpr int LOGR = R == 2 ? 1 : R == 4 ? 2 : R == 8 ? 3 : 4;
+    constexpr int LOGR = R == 2 ? 1 : R == 4 ? 2 : 3;
     constexpr int G = EPT / R;          // groups per thread (the tile holds EPT values per thread)
     const int nl = 1 << lognl, L = 1 << logL, Ns = 1 << logNs;
     const int ngroups = nl << (logL - LOGR);
@@ -146,18 +152,17 @@ __device__ __forceinline__ void stage(float2 *lds, int P, int lognl, int logL, i
     __syncthreads();
 }
 
-// Full FFT of the tile's lines: radix-16 stages, then one radix-2/4/8 stage.
+// Full FFT of the tile's lines: radix-8 stages, then one radix-2/4 stage.
 // NT threads per workgroup, EPT values per thread.
 template <bool INV, int NT = TPB> __device__ void fft_lines(float2 *lds, int P, int lognl, int logL, const float2 *tw)
 {
     int logNs = 0;
-    while (logL - logNs >= 4) {
-        stage<16, INV, NT>(lds, P, lognl, logL, logNs, tw);
-        logNs += 4;
+    while (logL - logNs >= 3) {
+        stage<8, INV, NT>(lds, P, lognl, logL, logNs, tw);
+        logNs += 3;
     }
     const int rem = logL - logNs;
-    if (rem == 3) stage<8, INV, NT>(lds, P, lognl, logL, logNs, tw);
-    else if (rem == 2) stage<4, INV, NT>(lds, P, lognl, logL, logNs, tw);
+    if (rem == 2) stage<4, INV, NT>(lds, P, lognl, logL, logNs, tw);
     else if (rem == 1) stage<2, INV, NT>(lds, P, lognl, logL, logNs, tw);
 }
 
@@ -288,6 +293,127 @@ __global__ __launch_bounds__(TPB) void k_fft_x3_c2r(const float2 *__restrict__ s
                 v.y += a.y;
             }
             dst[o] = v;
+        }
+    }
+}
+
+// --- x3 and x2 passes of one x1 plane in one workgroup (planes of at most 64 x
+// 64 points), forward: real rows -> half spectrum -> columns; inverse the other
+// way, with the optional add.  Same line transforms as the separate passes; the
+// plane stays in LDS between them, as rows [q][row] (pitch n2 + 1) and as
+// columns [row][k] (pitch NL + 1, NL >= n3 / 2 + 1 a power of two).
+// Separate passes at 64^3: 11 + 7 us forward, 7 + 12 us inverse; one kernel 10
+// and 9 us, bound by the latency of its stages.
+constexpr int NTP = 512;            // threads, EPT = 8 values each: 64 x 64
+
+template <bool INV>
+__global__ __launch_bounds__(NTP) void k_fft_plane(const float *__restrict__ in, float *__restrict__ out,
+                                                   const float *__restrict__ add, float2 *__restrict__ spec,
+                                                   const float2 *__restrict__ twM, const float2 *__restrict__ tw3,
+                                                   const float2 *__restrict__ tw2, int logM, int logn2, int logNL,
+                                                   size_t cs, size_t spec_cs, int np)
+{
+    extern __shared__ float2 sm[];
+    const int M = 1 << logM, n2 = 1 << logn2, NL = 1 << logNL, PR = n2 + 1, PC = NL + 1;
+    float2 *twm = sm;                 // M: e^{-2 pi i t / M}
+    float2 *tws = twm + M;            // M + 1: e^{-2 pi i k / n3}
+    float2 *twc = tws + M + 1;        // n2
+    float2 *lds = twc + n2;
+    const int comp = blockIdx.y;
+    const size_t row0 = (size_t)blockIdx.x << logn2;
+    float2 *sp = spec + comp * spec_cs + row0 * np;
+    load_table<NTP>(twm, twM, M);
+    load_table<NTP>(tws, tw3, M + 1);
+    load_table<NTP>(twc, tw2, n2);
+    const int rows = n2 << logM, cols = n2 << logNL;   // values as rows, as columns
+    float2 v[EPT];
+    if (!INV) {
+        const float2 *src = (const float2 *)(in + comp * cs) + row0 * M;
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x;
+            if (e < rows) v[it] = src[e];
+        }
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x;
+            if (e < rows) lds[(e & (M - 1)) * PR + (e >> logM)] = v[it];
+        }
+        __syncthreads();
+        fft_lines<false, NTP>(lds, PR, logn2, logM, twm);
+        // X[k] = E[k] + w^k O[k] (see k_fft_x3_r2c), k <= M
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x, k = e & (NL - 1), r = e >> logNL;
+            v[it] = make_float2(0.f, 0.f);
+            if (e < cols && k <= M) {
+                const float2 zk = lds[(k & (M - 1)) * PR + r];
+                const float2 zc = cconj(lds[((M - k) & (M - 1)) * PR + r]);
+                const float2 E = make_float2(0.5f * (zk.x + zc.x), 0.5f * (zk.y + zc.y));
+                const float2 O = make_float2(0.5f * (zk.y - zc.y), -0.5f * (zk.x - zc.x));
+                v[it] = cadd(E, cmul(tws[k], O));
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x;
+            if (e < cols) lds[(e >> logNL) * PC + (e & (NL - 1))] = v[it];
+        }
+        __syncthreads();
+        fft_lines<false, NTP>(lds, PC, logNL, logn2, twc);
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x, k = e & (NL - 1), r = e >> logNL;
+            if (e < cols && k <= M) sp[(size_t)r * np + k] = lds[r * PC + k];
+        }
+    } else {
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x, k = e & (NL - 1), r = e >> logNL;
+            v[it] = e < cols && k <= M ? sp[(size_t)r * np + k] : make_float2(0.f, 0.f);
+        }
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x;
+            if (e < cols) lds[(e >> logNL) * PC + (e & (NL - 1))] = v[it];
+        }
+        __syncthreads();
+        fft_lines<true, NTP>(lds, PC, logNL, logn2, twc);
+        // Z[k] (see k_fft_x3_c2r), k < M
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x;
+            if (e < rows) {
+                const int k = e & (M - 1), r = e >> logM;
+                const float2 a = lds[r * PC + k], b = cconj(lds[r * PC + M - k]);
+                const float2 sum = cadd(a, b), dif = csub(a, b);
+                const float2 wd = cmul(cconj(tws[k]), dif);
+                v[it] = make_float2(sum.x - wd.y, sum.y + wd.x);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x;
+            if (e < rows) lds[(e & (M - 1)) * PR + (e >> logM)] = v[it];
+        }
+        __syncthreads();
+        fft_lines<true, NTP>(lds, PR, logn2, logM, twm);
+        float2 *dst = (float2 *)(out + comp * cs) + row0 * M;
+        const float2 *ad = add ? (const float2 *)(add + comp * cs) + row0 * M : nullptr;
+#pragma unroll
+        for (int it = 0; it < EPT; ++it) {
+            const int e = it * NTP + threadIdx.x;
+            if (e < rows) {
+                float2 x = lds[(e & (M - 1)) * PR + (e >> logM)];
+                if (ad) {
+                    const float2 a = ad[e];
+                    x.x += a.x;
+                    x.y += a.y;
+                }
+                dst[e] = x;
+            }
         }
     }
 }
@@ -1047,9 +1173,22 @@ void pass_c2r(const FFTPlan &P, float *out, const float *add, int nc, int logM, 
                        logM, lognl3, nrows, N, spec_cs, P.np);
 }
 
+// x3 and x2 passes of small planes in one kernel
+bool planes_ok(const FFTPlan &P) { return P.n2 <= 64 && P.n3 <= 64; }
+
+template <bool INV>
+void launch_planes(const FFTPlan &P, const float *in, float *out, const float *add, int nc, size_t spec_cs,
+                   hipStream_t s)
+{
+    const int M = P.n3 / 2, NL = 2 * M;   // NL >= nh = M + 1; n2 NL <= 64 x 64 values
+    const size_t lds = (size_t)(2 * M + 1 + P.n2 + std::max(M * (P.n2 + 1), P.n2 * (NL + 1))) * sizeof(float2);
+    hipLaunchKernelGGL((k_fft_plane<INV>), dim3(P.n1, nc), dim3(NTP), lds, s, in, out, add, P.spec, P.twM, P.twS, P.tw2,
+                       ilog2(M), ilog2(P.n2), ilog2(NL), (size_t)P.n1 * P.n2 * P.n3, spec_cs, P.np);
+}
+
 // Stockham column passes (lines of 16 ... 64 points; 128 ... 1024 take the
-// register-resident passes): a 256-thread tile of 4096 values holds C =
-// 4096 / L columns (at most 32).
+// register-resident passes): a 256-thread tile of at most 2048 values holds 32
+// columns.
 struct ColGeom {
     int logC;
     size_t lds;   // twiddle table + tile at pitch C + 1
@@ -1134,6 +1273,12 @@ void spectral_apply(const FFTPlan &P, int kind, float beta, float beta_w, int nc
         const float *inc = in + c0 * N;
         float *outc = out + c0 * N;
         const float *addc = add ? add + c0 * N : nullptr;
+        if (planes_ok(P)) {
+            launch_planes<false>(P, inc, nullptr, nullptr, nc, spec_cs, s);
+            pass_x1(P, 0, kind, beta, scale, nc, spec_cs, s);
+            launch_planes<true>(P, nullptr, outc, addc, nc, spec_cs, s);
+            continue;
+        }
         pass_r2c(P, inc, nc, logM, lognl3, lds3, spec_cs, s);
         pass_x2(P, false, nc, spec_cs, s);
         pass_x1(P, 0, kind, beta, scale, nc, spec_cs, s);
@@ -1166,14 +1311,22 @@ PassGeom geom(const FFTPlan &P)
 
 void forward3(const FFTPlan &P, const PassGeom &G, int nc, const float *in, hipStream_t s)
 {
-    pass_r2c(P, in, nc, G.logM, G.lognl3, G.lds3, G.spec_cs, s);
-    pass_x2(P, false, nc, G.spec_cs, s);
+    if (planes_ok(P)) {
+        launch_planes<false>(P, in, nullptr, nullptr, nc, G.spec_cs, s);
+    } else {
+        pass_r2c(P, in, nc, G.logM, G.lognl3, G.lds3, G.spec_cs, s);
+        pass_x2(P, false, nc, G.spec_cs, s);
+    }
     pass_x1(P, 1, 2, 0.f, 1.f, nc, G.spec_cs, s);
 }
 
 void inverse3(const FFTPlan &P, const PassGeom &G, int nc, float *out, hipStream_t s)
 {
     pass_x1(P, 2, 2, 0.f, 1.f, nc, G.spec_cs, s);
+    if (planes_ok(P)) {
+        launch_planes<true>(P, nullptr, out, nullptr, nc, G.spec_cs, s);
+        return;
+    }
     pass_x2(P, true, nc, G.spec_cs, s);
     pass_c2r(P, out, nullptr, nc, G.logM, G.lognl3, G.lds3, G.spec_cs, s);
 }
