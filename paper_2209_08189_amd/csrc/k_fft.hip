@@ -30,6 +30,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace clh {
 
@@ -214,11 +215,12 @@ __global__ __launch_bounds__(TPB) void k_fft_x3_r2c(const float *__restrict__ in
     }
 }
 
-// --- x3 inverse: half spectrum -> real rows (unnormalised), optional add.
+// --- x3 inverse: half spectrum -> real rows (unnormalised), optional add; the
+// values k >= kmax are zero and not read.
 __global__ __launch_bounds__(TPB) void k_fft_x3_c2r(const float2 *__restrict__ spec, float *__restrict__ out,
                                                     const float *__restrict__ add, const float2 *__restrict__ twM,
                                                     const float2 *__restrict__ tw3, int logM, int lognl, int nrows,
-                                                    size_t out_cs, size_t spec_cs, int np)
+                                                    size_t out_cs, size_t spec_cs, int np, int kmax)
 {
     extern __shared__ float2 sm[];
     const int M = 1 << logM, nl = 1 << lognl, P = nl + 1, nh = M + 1;
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(TPB) void k_fft_x3_c2r(const float2 *__restrict__ s
             const int e = it * TPB + threadIdx.x;
             if (e < totk) {
                 const int r = e / nh, k = e - r * nh;
-                buf[it] = src[(size_t)(row0 + r) * np + k];
+                buf[it] = k < kmax ? src[(size_t)(row0 + r) * np + k] : make_float2(0.f, 0.f);
             }
         }
 #pragma unroll
@@ -299,7 +301,8 @@ __global__ __launch_bounds__(TPB) void k_fft_x3_c2r(const float2 *__restrict__ s
 
 // --- x3 and x2 passes of one x1 plane in one workgroup (planes of at most 64 x
 // 64 points), forward: real rows -> half spectrum -> columns; inverse the other
-// way, with the optional add.  Same line transforms as the separate passes; the
+// way, with the optional add, from the values k < kmax of the rows |k2| < m2
+// (the others are zero and not read).  Same line transforms as the separate passes; the
 // plane stays in LDS between them, as rows [q][row] (pitch n2 + 1) and as
 // columns [row][k] (pitch NL + 1, NL >= n3 / 2 + 1 a power of two).
 // Separate passes at 64^3: 11 + 7 us forward, 7 + 12 us inverse; one kernel 10
@@ -311,7 +314,7 @@ __global__ __launch_bounds__(NTP) void k_fft_plane(const float *__restrict__ in,
                                                    const float *__restrict__ add, float2 *__restrict__ spec,
                                                    const float2 *__restrict__ twM, const float2 *__restrict__ tw3,
                                                    const float2 *__restrict__ tw2, int logM, int logn2, int logNL,
-                                                   size_t cs, size_t spec_cs, int np)
+                                                   size_t cs, size_t spec_cs, int np, int kmax, int m2)
 {
     extern __shared__ float2 sm[];
     const int M = 1 << logM, n2 = 1 << logn2, NL = 1 << logNL, PR = n2 + 1, PC = NL + 1;
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(NTP) void k_fft_plane(const float *__restrict__ in,
 #pragma unroll
         for (int it = 0; it < EPT; ++it) {
             const int e = it * NTP + threadIdx.x, k = e & (NL - 1), r = e >> logNL;
-            v[it] = e < cols && k <= M ? sp[(size_t)r * np + k] : make_float2(0.f, 0.f);
+            v[it] = e < cols && k < kmax && (r < m2 || r > n2 - m2) ? sp[(size_t)r * np + k] : make_float2(0.f, 0.f);
         }
 #pragma unroll
         for (int it = 0; it < EPT; ++it) {
@@ -418,6 +421,33 @@ __global__ __launch_bounds__(NTP) void k_fft_plane(const float *__restrict__ in,
     }
 }
 
+// Pruned column passes (spectral resampling): of the La-point lines of a source
+// spectrum only the rows |k| < m are read, as the rows |k| < m of lines of L
+// points, the others are zero; and only the planes |k| < mp are visited.  A
+// pass with m = mp = L and dplane = 0 is the plain one.
+struct ColSrc {
+    const float2 *src;   // spectrum read, components cs apart, planes ps, rows rs
+    size_t cs, ps, rs;
+    int La, m;           // points of a source line, kept rows
+    int mp, skip;        // kept planes, planes left out (N - (2 mp - 1), or 0)
+    int dplane;          // source planes minus planes (for negative k)
+    float scale;         // of every value read
+};
+
+// plane of the j-th kept one, and its source plane
+__device__ __forceinline__ int kept_plane(const ColSrc &c, int j) { return j < c.mp ? j : j + c.skip; }
+__device__ __forceinline__ const float2 *src_plane(const ColSrc &c, int comp, int j, int c0)
+{
+    return c.src + comp * c.cs + (size_t)(j < c.mp ? j : j + c.skip + c.dplane) * c.ps + c0;
+}
+// row q of an L-point line
+__device__ __forceinline__ float2 src_row(const ColSrc &c, const float2 *__restrict__ base, int q, int L, int l, bool ok)
+{
+    if (!ok || (q >= c.m && q <= L - c.m)) return make_float2(0.f, 0.f);
+    const float2 v = base[(size_t)(q < c.m ? q : q + c.La - L) * c.rs + l];
+    return make_float2(v.x * c.scale, v.y * c.scale);
+}
+
 // --- column tile load/store for the x2 and x1 passes: element (l, q) of
 // the tile is base[q * rs + l], l < cw valid columns; NT threads.  A thread
 // keeps its column l and steps through the rows q0, q0 + NT / C, ...: the
@@ -442,6 +472,25 @@ __device__ __forceinline__ void load_cols(float2 *lds, const float2 *__restrict_
     __syncthreads();
 }
 
+// the same through a ColSrc
+template <int NT>
+__device__ __forceinline__ void load_cols_src(float2 *lds, const ColSrc &c, const float2 *__restrict__ base, int logC,
+                                              int logL, int cw, int P)
+{
+    const int C = 1 << logC, L = 1 << logL;
+    const int l = threadIdx.x & (C - 1), q0 = threadIdx.x >> logC, QS = NT >> logC;
+    float2 buf[EPT];
+#pragma unroll
+    for (int it = 0; it < EPT; ++it) {
+        const int q = q0 + it * QS;
+        if (q < L) buf[it] = src_row(c, base, q, L, l, l < cw);
+    }
+#pragma unroll
+    for (int it = 0; it < EPT; ++it)
+        if (q0 + it * QS < L) lds[(q0 + it * QS) * P + l] = buf[it];
+    __syncthreads();
+}
+
 template <int NT>
 __device__ __forceinline__ void store_cols(const float2 *lds, float2 *__restrict__ base, size_t rs, int logC, int logL,
                                            int cw, int P)
@@ -458,9 +507,9 @@ __device__ __forceinline__ void store_cols(const float2 *lds, float2 *__restrict
 
 // --- x2 C2C in place on the half spectrum: plane i1 = blockIdx.y, columns
 // [c0, c0 + C) of the nh per row; NT threads hold the tile of NT EPT values.
-template <bool INV, int NT>
-__global__ __launch_bounds__(NT) void k_fft_x2(float2 *__restrict__ spec, const float2 *__restrict__ tw2, int logn2,
-                                                int n2, int nh, int np, int logC, size_t spec_cs)
+template <bool INV, int NT, bool PR>
+__global__ __launch_bounds__(NT) void k_fft_x2(float2 *spec, const float2 *__restrict__ tw2, int logn2,
+                                                int n2, int nh, int np, int logC, size_t spec_cs, ColSrc from)
 {
     extern __shared__ float2 sm[];
     const int C = 1 << logC, P = C + 1;
@@ -470,7 +519,8 @@ __global__ __launch_bounds__(NT) void k_fft_x2(float2 *__restrict__ spec, const 
     const int cw = min(C, nh - c0);
     float2 *base = spec + comp * spec_cs + (size_t)i1 * n2 * np + c0;
     load_table<NT>(tw, tw2, n2);
-    load_cols<NT>(lds, base, np, logC, logn2, cw, P);
+    if (PR) load_cols_src<NT>(lds, from, src_plane(from, comp, i1, c0), logC, logn2, cw, P);
+    else load_cols<NT>(lds, base, np, logC, logn2, cw, P);
     fft_lines<INV, NT>(lds, P, logC, logn2, tw);
     store_cols<NT>(lds, base, np, logC, logn2, cw, P);
 }
@@ -478,21 +528,22 @@ __global__ __launch_bounds__(NT) void k_fft_x2(float2 *__restrict__ spec, const 
 // --- x1 fused: forward FFT along x1, symbol multiply, inverse FFT.
 // plane i2 = blockIdx.y, columns [c0, c0 + C).
 // mode 0: forward, multiply, inverse; 1: forward only; 2: inverse only
-template <int NT>
-__global__ __launch_bounds__(NT) void k_fft_x1_mult(float2 *__restrict__ spec, const float2 *__restrict__ tw1,
+template <int NT, bool PR>
+__global__ __launch_bounds__(NT) void k_fft_x1_mult(float2 *spec, const float2 *__restrict__ tw1,
                                                      int logn1, int n1, int n2, int nh, int np, int logC, int kind,
-                                                     float beta, float scale, size_t spec_cs, int mode)
+                                                     float beta, float scale, size_t spec_cs, int mode, ColSrc from)
 {
     extern __shared__ float2 sm[];
     const int C = 1 << logC, P = C + 1;
     float2 *tw = sm;
     float2 *lds = sm + n1;
-    const int comp = blockIdx.z, i2 = blockIdx.y, c0 = blockIdx.x * C;
+    const int comp = blockIdx.z, i2 = PR ? kept_plane(from, blockIdx.y) : blockIdx.y, c0 = blockIdx.x * C;
     const int cw = min(C, nh - c0);
     float2 *base = spec + comp * spec_cs + (size_t)i2 * np + c0;
     const size_t rs = (size_t)n2 * np;
     load_table<NT>(tw, tw1, n1);
-    load_cols<NT>(lds, base, rs, logC, logn1, cw, P);
+    if (PR) load_cols_src<NT>(lds, from, src_plane(from, comp, blockIdx.y, c0), logC, logn1, cw, P);
+    else load_cols<NT>(lds, base, rs, logC, logn1, cw, P);
     if (mode == 2) {
         fft_lines<true, NT>(lds, P, logC, logn1, tw);
         store_cols<NT>(lds, base, rs, logC, logn1, cw, P);
@@ -548,24 +599,30 @@ __device__ __forceinline__ void cols_load_b(float2 (&v)[16], const float2 *__res
     for (int a = 0; a < 16; ++a) v[a] = ok ? base[(size_t)(R2 * a + b) * rs + l] : make_float2(0.f, 0.f);
 }
 
-template <int R2, int MODE>
-__global__ __launch_bounds__(TPB) void k_fft_cols(float2 *__restrict__ spec, const float2 *__restrict__ twL,
+template <int R2, int MODE, bool PR>
+__global__ __launch_bounds__(TPB) void k_fft_cols(float2 *spec, const float2 *__restrict__ twL,
                                                   int nh, size_t plane_stride, size_t rs, size_t spec_cs, int kind,
-                                                  float beta, float scale, int n1, int n2)
+                                                  float beta, float scale, int n1, int n2, ColSrc from)
 {
     constexpr int L = 16 * R2, C = 256 / R2, P2 = C / 16;   // P2: (l, c) pairs per thread
     __shared__ float2 tw[L];
     __shared__ float2 ex[16 * CSC];
-    const int comp = blockIdx.z, pl = blockIdx.y, c0 = blockIdx.x * C;
+    const int comp = blockIdx.z, pl = PR ? kept_plane(from, blockIdx.y) : blockIdx.y, c0 = blockIdx.x * C;
     const int cw = min(C, nh - c0);
     float2 *base = spec + comp * spec_cs + pl * plane_stride + c0;
+    const float2 *sb = PR ? src_plane(from, comp, blockIdx.y, c0) : base;
     for (int t = threadIdx.x; t < L; t += TPB) tw[t] = twL[t];
     const int l = threadIdx.x % C, r = threadIdx.x / C;     // r: b (b layout) or the first c (c layout)
     const bool ok = l < cw;
     float2 v[16];
     if (MODE != 2) {
         // forward: b layout, DFT-16 over a, twiddle W_L^{bc}, exchange
-        cols_load_b<R2>(v, base, rs, l, r, ok);
+        if (PR) {
+#pragma unroll
+            for (int a = 0; a < 16; ++a) v[a] = src_row(from, sb, R2 * a + r, L, l, ok);
+        } else {
+            cols_load_b<R2>(v, base, rs, l, r, ok);
+        }
         __syncthreads();                                      // twiddle table
         dft_reg<16, false>(v);
 #pragma unroll
@@ -621,7 +678,8 @@ __global__ __launch_bounds__(TPB) void k_fft_cols(float2 *__restrict__ spec, con
             const int c = r + (256 / C) * u;
 #pragma unroll
             for (int d = 0; d < R2; ++d)
-                v[u * R2 + d] = ok ? base[(size_t)(c + 16 * d) * rs + l] : make_float2(0.f, 0.f);
+                v[u * R2 + d] = PR ? src_row(from, sb, c + 16 * d, L, l, ok)
+                                   : ok ? base[(size_t)(c + 16 * d) * rs + l] : make_float2(0.f, 0.f);
         }
         __syncthreads();                                      // twiddle table
     }
@@ -687,18 +745,19 @@ template <int E, bool INV, int S = 1> __device__ __forceinline__ void cross_dft(
     bfly(INV ? 2 : 1);
 }
 
-template <int E, int MODE>
-__global__ __launch_bounds__(NTX, 4) void k_fft_colsx(float2 *__restrict__ spec, const float2 *__restrict__ twL,
+template <int E, int MODE, bool PR>
+__global__ __launch_bounds__(NTX, 4) void k_fft_colsx(float2 *spec, const float2 *__restrict__ twL,
                                                       int nh, size_t plane_stride, size_t rs, size_t spec_cs, int kind,
-                                                      float beta, float scale, int n1, int n2)
+                                                      float beta, float scale, int n1, int n2, ColSrc from)
 {
     constexpr int R2 = 16 * E, L = 16 * R2, C = NTX / R2, LOGC = C == 16 ? 4 : 3, LOGE = E == 2 ? 1 : 2;
     constexpr int CS = R2 * C + 16;   // exchange pitch per c
     __shared__ float2 tw[L];
     __shared__ float2 ex[16 * CS];
-    const int comp = blockIdx.z, pl = blockIdx.y, c0 = blockIdx.x * C;
+    const int comp = blockIdx.z, pl = PR ? kept_plane(from, blockIdx.y) : blockIdx.y, c0 = blockIdx.x * C;
     const int cw = min(C, nh - c0);
     float2 *base = spec + comp * spec_cs + pl * plane_stride + c0;
+    const float2 *sb = PR ? src_plane(from, comp, blockIdx.y, c0) : base;
     for (int t = threadIdx.x; t < L; t += NTX) tw[t] = twL[t];
     // b layout: thread (column lb, b); c layout: thread (eps, column lc, c), eps fastest
     const int lb = threadIdx.x & (C - 1), b = threadIdx.x >> LOGC;
@@ -707,7 +766,12 @@ __global__ __launch_bounds__(NTX, 4) void k_fft_colsx(float2 *__restrict__ spec,
     const bool okb = lb < cw, okc = lc < cw;
     float2 v[16];
     if (MODE != 2) {
-        cols_load_b<R2>(v, base, rs, lb, b, okb);            // v[a] = x[R2 a + b]
+        if (PR) {
+#pragma unroll
+            for (int a = 0; a < 16; ++a) v[a] = src_row(from, sb, R2 * a + b, L, lb, okb);
+        } else {
+            cols_load_b<R2>(v, base, rs, lb, b, okb);        // v[a] = x[R2 a + b]
+        }
         __syncthreads();                                      // twiddle table
         dft_reg<16, false>(v);
 #pragma unroll
@@ -749,7 +813,8 @@ __global__ __launch_bounds__(NTX, 4) void k_fft_colsx(float2 *__restrict__ spec,
     } else {
 #pragma unroll
         for (int k = 0; k < 16; ++k)
-            v[k] = okc ? base[(size_t)(c + 16 * k + 256 * m) * rs + lc] : make_float2(0.f, 0.f);
+            v[k] = PR ? src_row(from, sb, c + 16 * k + 256 * m, L, lc, okc)
+                      : okc ? base[(size_t)(c + 16 * k + 256 * m) * rs + lc] : make_float2(0.f, 0.f);
         __syncthreads();                                      // twiddle table
     }
     // inverse: lanes, twiddle W_R2^{-eps d'}, DFT-16 over d', exchange,
@@ -912,16 +977,19 @@ __global__ __launch_bounds__(TPB) void k_fft_rows_r2c(const float *__restrict__ 
 }
 
 // x3 inverse: half spectrum -> real rows (unnormalised), optional add
-template <int R2>
+template <int R2, bool PR>
 __global__ __launch_bounds__(TPB) void k_fft_rows_c2r(const float2 *__restrict__ spec, float *__restrict__ out,
                                                       const float *__restrict__ add, const float2 *__restrict__ twM,
-                                                      const float2 *__restrict__ tw3, size_t out_cs, size_t spec_cs)
+                                                      const float2 *__restrict__ tw3, size_t out_cs, size_t spec_cs,
+                                                      int kmax)
 {
     constexpr int M = 16 * R2, NR = 256 / R2, PP = 16 / R2, NP = M + 16;   // NP: spectrum row pitch
     __shared__ float2 twm[M], tws[M + 1];
     __shared__ float2 ex[NR * rows_pitch<R2>()];
     const int comp = blockIdx.y;
     const size_t row0 = (size_t)blockIdx.x * NR;
+    // value k of a row (PR: zero from kmax on, not read)
+    auto val = [&](const float2 *row, int k) { return !PR || k < kmax ? row[k] : make_float2(0.f, 0.f); };
     const float2 *src = spec + comp * spec_cs + row0 * NP;
     float2 *dst = (float2 *)(out + comp * out_cs) + row0 * M;
     const float2 *ad = add ? (const float2 *)(add + comp * out_cs) + row0 * M : nullptr;
@@ -938,8 +1006,8 @@ __global__ __launch_bounds__(TPB) void k_fft_rows_c2r(const float2 *__restrict__
 #pragma unroll
         for (int dl = 0; dl < 16; ++dl) {
             const int k = c + 16 * eps + 32 * dl;
-            xa[dl] = srow[k];
-            xb[dl] = srow[M - k];
+            xa[dl] = val(srow, k);
+            xb[dl] = val(srow, M - k);
         }
         __syncthreads();                                      // twiddle tables
 #pragma unroll
@@ -957,8 +1025,8 @@ __global__ __launch_bounds__(TPB) void k_fft_rows_c2r(const float2 *__restrict__
         for (int u = 0; u < PP; ++u) {
             const float2 *srow = src + (size_t)(r0 + 16 * u) * NP;
 #pragma unroll
-            for (int d = 0; d < R2; ++d) xa[u * R2 + d] = srow[c + 16 * d];
-            nyq[u] = c == 0 ? srow[M] : make_float2(0.f, 0.f);
+            for (int d = 0; d < R2; ++d) xa[u * R2 + d] = val(srow, c + 16 * d);
+            nyq[u] = c == 0 ? val(srow, M) : make_float2(0.f, 0.f);
         }
         // X[M - k] for k = c + 16 d: for c > 0 it is X[(16 - c) + 16 (R2 - 1 - d)],
         // held by lane 16 - c of the same 16-lane row (a row reflection by DPP);
@@ -997,28 +1065,6 @@ __global__ __launch_bounds__(TPB) void k_fft_rows_c2r(const float2 *__restrict__
         }
         dst[o] = val;
     }
-}
-
-// Copy the half-spectrum modes with |k_d| < min(na_d, nb_d)/2 from grid a
-// to grid b (the coarse Nyquist planes are dropped), zero elsewhere.
-__global__ __launch_bounds__(TPB) void k_mode_copy(const float2 *__restrict__ sa, float2 *__restrict__ sb, int a1, int a2,
-                                                   int a3, int b1, int b2, int b3, int ncomp)
-{
-    const int bh = b3 / 2 + 1, ap = fft_row_pitch(a3), bp = fft_row_pitch(b3);
-    const size_t nb = (size_t)b1 * b2 * bh;
-    const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (e >= nb * ncomp) return;
-    const int comp = (int)(e / nb);
-    const size_t r = e - comp * nb;
-    const int q3 = (int)(r % bh), q2 = (int)((r / bh) % b2), q1 = (int)(r / ((size_t)bh * b2));
-    const int k1 = q1 < b1 / 2 ? q1 : q1 - b1, k2 = q2 < b2 / 2 ? q2 : q2 - b2, k3 = q3;
-    const int c1 = min(a1, b1), c2 = min(a2, b2), c3 = min(a3, b3);
-    float2 v = make_float2(0.f, 0.f);
-    if (2 * abs(k1) < c1 && 2 * abs(k2) < c2 && 2 * k3 < c3) {
-        const int p1 = k1 < 0 ? k1 + a1 : k1, p2 = k2 < 0 ? k2 + a2 : k2;
-        v = sa[(size_t)comp * a1 * a2 * ap + ((size_t)p1 * a2 + p2) * ap + k3];
-    }
-    sb[(size_t)comp * b1 * b2 * bp + ((size_t)q1 * b2 + q2) * bp + q3] = v;
 }
 
 // Per-mode 3x3 operators of the near-incompressible regularisation on the
@@ -1104,22 +1150,26 @@ bool cols_ok(int L) { return L == 128 || L == 256 || L == 512 || L == 1024; }
 // columns per tile of the register-resident column passes
 int cols_width(int L) { return L <= 256 ? 4096 / L : 8192 / L; }
 
+// from: pruned source (NULL: the spectrum itself, in full)
 template <int MODE>
 void launch_cols(int L, dim3 grid, float2 *spec, const float2 *tw, int nh, size_t plane_stride, size_t rs,
-                 size_t spec_cs, int kind, float beta, float scale, int n1, int n2, hipStream_t s)
+                 size_t spec_cs, int kind, float beta, float scale, int n1, int n2, const ColSrc *from, hipStream_t s)
 {
-    if (L == 1024)
-        hipLaunchKernelGGL((k_fft_colsx<4, MODE>), grid, dim3(NTX), 0, s, spec, tw, nh, plane_stride, rs, spec_cs, kind,
-                           beta, scale, n1, n2);
-    else if (L == 512)
-        hipLaunchKernelGGL((k_fft_colsx<2, MODE>), grid, dim3(NTX), 0, s, spec, tw, nh, plane_stride, rs, spec_cs, kind,
-                           beta, scale, n1, n2);
-    else if (L == 256)
-        hipLaunchKernelGGL((k_fft_cols<16, MODE>), grid, dim3(TPB), 0, s, spec, tw, nh, plane_stride, rs, spec_cs, kind,
-                           beta, scale, n1, n2);
-    else
-        hipLaunchKernelGGL((k_fft_cols<8, MODE>), grid, dim3(TPB), 0, s, spec, tw, nh, plane_stride, rs, spec_cs, kind,
-                           beta, scale, n1, n2);
+    auto go = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, spec, tw, nh, plane_stride, rs, spec_cs, kind, beta,
+                           scale, n1, n2, from ? *from : ColSrc{});
+    };
+    auto size = [&](auto pruned) {
+        constexpr bool PR = decltype(pruned)::value;
+        if (L == 1024) go(k_fft_colsx<4, MODE, PR>, NTX);
+        else if (L == 512) go(k_fft_colsx<2, MODE, PR>, NTX);
+        else if (L == 256) go(k_fft_cols<16, MODE, PR>, TPB);
+        else go(k_fft_cols<8, MODE, PR>, TPB);
+    };
+    if constexpr (MODE != 0) {
+        if (from) return size(std::true_type{});
+    }
+    size(std::false_type{});
 }
 
 bool rows_ok(int n3) { return n3 == 128 || n3 == 256 || n3 == 512 || n3 == 1024; }
@@ -1133,10 +1183,15 @@ void launch_rows_r2c(const FFTPlan &P, const float *in, int nc, size_t N, size_t
 }
 
 template <int R2>
-void launch_rows_c2r(const FFTPlan &P, float *out, const float *add, int nc, size_t N, size_t spec_cs, hipStream_t s)
+void launch_rows_c2r(const FFTPlan &P, float *out, const float *add, int nc, size_t N, size_t spec_cs, int kmax,
+                     hipStream_t s)
 {
-    hipLaunchKernelGGL((k_fft_rows_c2r<R2>), dim3(P.n1 * P.n2 / (256 / R2), nc), dim3(TPB), 0, s, P.spec, out, add,
-                       P.twM, P.twS, N, spec_cs);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(P.n1 * P.n2 / (256 / R2), nc), dim3(TPB), 0, s, P.spec, out, add, P.twM, P.twS,
+                           N, spec_cs, kmax);
+    };
+    if (kmax < P.nh) go(k_fft_rows_c2r<R2, true>);
+    else go(k_fft_rows_c2r<R2, false>);
 }
 
 // x3 forward pass (real rows -> half spectrum), nc components
@@ -1156,34 +1211,36 @@ void pass_r2c(const FFTPlan &P, const float *in, int nc, int logM, int lognl3, s
                        lognl3, nrows, N, spec_cs, P.np);
 }
 
-// x3 inverse pass (half spectrum -> real rows, optional add), nc components
+// x3 inverse pass (half spectrum -> real rows, optional add), nc components;
+// values k >= kmax are taken as zero
 void pass_c2r(const FFTPlan &P, float *out, const float *add, int nc, int logM, int lognl3, size_t lds3,
-              size_t spec_cs, hipStream_t s)
+              size_t spec_cs, int kmax, hipStream_t s)
 {
     const size_t N = (size_t)P.n1 * P.n2 * P.n3;
     const int nrows = P.n1 * P.n2;
     if (rows_ok(P.n3) && nrows % (256 / (P.n3 / 32)) == 0) {
-        if (P.n3 == 1024) launch_rows_c2r<32>(P, out, add, nc, N, spec_cs, s);
-        else if (P.n3 == 512) launch_rows_c2r<16>(P, out, add, nc, N, spec_cs, s);
-        else if (P.n3 == 256) launch_rows_c2r<8>(P, out, add, nc, N, spec_cs, s);
-        else launch_rows_c2r<4>(P, out, add, nc, N, spec_cs, s);
+        if (P.n3 == 1024) launch_rows_c2r<32>(P, out, add, nc, N, spec_cs, kmax, s);
+        else if (P.n3 == 512) launch_rows_c2r<16>(P, out, add, nc, N, spec_cs, kmax, s);
+        else if (P.n3 == 256) launch_rows_c2r<8>(P, out, add, nc, N, spec_cs, kmax, s);
+        else launch_rows_c2r<4>(P, out, add, nc, N, spec_cs, kmax, s);
         return;
     }
     hipLaunchKernelGGL(k_fft_x3_c2r, dim3(nrows >> lognl3, nc), dim3(TPB), lds3, s, P.spec, out, add, P.twM, P.twS,
-                       logM, lognl3, nrows, N, spec_cs, P.np);
+                       logM, lognl3, nrows, N, spec_cs, P.np, kmax);
 }
 
 // x3 and x2 passes of small planes in one kernel
 bool planes_ok(const FFTPlan &P) { return P.n2 <= 64 && P.n3 <= 64; }
 
 template <bool INV>
-void launch_planes(const FFTPlan &P, const float *in, float *out, const float *add, int nc, size_t spec_cs,
-                   hipStream_t s)
+void launch_planes(const FFTPlan &P, const float *in, float *out, const float *add, int nc, size_t spec_cs, int kmax,
+                   int m2, hipStream_t s)
 {
     const int M = P.n3 / 2, NL = 2 * M;   // NL >= nh = M + 1; n2 NL <= 64 x 64 values
     const size_t lds = (size_t)(2 * M + 1 + P.n2 + std::max(M * (P.n2 + 1), P.n2 * (NL + 1))) * sizeof(float2);
     hipLaunchKernelGGL((k_fft_plane<INV>), dim3(P.n1, nc), dim3(NTP), lds, s, in, out, add, P.spec, P.twM, P.twS, P.tw2,
-                       ilog2(M), ilog2(P.n2), ilog2(NL), (size_t)P.n1 * P.n2 * P.n3, spec_cs, P.np);
+                       ilog2(M), ilog2(P.n2), ilog2(NL), (size_t)P.n1 * P.n2 * P.n3, spec_cs, P.np,
+                       kmax, m2);
 }
 
 // Stockham column passes (lines of 16 ... 64 points; 128 ... 1024 take the
@@ -1204,44 +1261,55 @@ ColGeom col_geom(int L)
 }
 
 
-// x2 pass over every x1 plane (forward or inverse), nc components
-void pass_x2(const FFTPlan &P, bool inv, int nc, size_t spec_cs, hipStream_t s)
+// x2 pass over every x1 plane (forward or inverse), nc components: the columns
+// k3 < kmax; from: pruned rows of an inverse pass
+void pass_x2(const FFTPlan &P, bool inv, int nc, size_t spec_cs, int kmax, const ColSrc *from, hipStream_t s)
 {
+    const size_t ps = (size_t)P.n2 * P.np;
     if (cols_ok(P.n2)) {
         const int C = cols_width(P.n2);
-        const dim3 grid((P.nh + C - 1) / C, P.n1, nc);
-        if (inv) launch_cols<2>(P.n2, grid, P.spec, P.tw2, P.nh, (size_t)P.n2 * P.np, P.np, spec_cs, 2, 0.f, 1.f, P.n1, P.n2, s);
-        else launch_cols<1>(P.n2, grid, P.spec, P.tw2, P.nh, (size_t)P.n2 * P.np, P.np, spec_cs, 2, 0.f, 1.f, P.n1, P.n2, s);
+        const dim3 grid((kmax + C - 1) / C, P.n1, nc);
+        if (inv) launch_cols<2>(P.n2, grid, P.spec, P.tw2, kmax, ps, P.np, spec_cs, 2, 0.f, 1.f, P.n1, P.n2, from, s);
+        else launch_cols<1>(P.n2, grid, P.spec, P.tw2, kmax, ps, P.np, spec_cs, 2, 0.f, 1.f, P.n1, P.n2, nullptr, s);
         return;
     }
     const ColGeom cg = col_geom(P.n2);
     const int C2 = 1 << cg.logC;
-    const dim3 grid((P.nh + C2 - 1) / C2, P.n1, nc);
-    if (inv)
-        hipLaunchKernelGGL((k_fft_x2<true, TPB>), grid, dim3(TPB), cg.lds, s, P.spec, P.tw2, ilog2(P.n2), P.n2, P.nh,
-                           P.np, cg.logC, spec_cs);
-    else
-        hipLaunchKernelGGL((k_fft_x2<false, TPB>), grid, dim3(TPB), cg.lds, s, P.spec, P.tw2, ilog2(P.n2), P.n2, P.nh,
-                           P.np, cg.logC, spec_cs);
+    const dim3 grid((kmax + C2 - 1) / C2, P.n1, nc);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(TPB), cg.lds, s, P.spec, P.tw2, ilog2(P.n2), P.n2, kmax, P.np, cg.logC,
+                           spec_cs, from ? *from : ColSrc{});
+    };
+    if (!inv) go(k_fft_x2<false, TPB, false>);
+    else if (from) go(k_fft_x2<true, TPB, true>);
+    else go(k_fft_x2<true, TPB, false>);
 }
 
-// x1 pass over every x2 plane: mode 0 forward, symbol, inverse; 1 forward; 2 inverse
-void pass_x1(const FFTPlan &P, int mode, int kind, float beta, float scale, int nc, size_t spec_cs, hipStream_t s)
+// x1 pass over every x2 plane: mode 0 forward, symbol, inverse; 1 forward; 2
+// inverse.  kmax, from: the columns k3 < kmax of the planes that from keeps
+// (modes 1 and 2), read through it.
+void pass_x1(const FFTPlan &P, int mode, int kind, float beta, float scale, int nc, size_t spec_cs, int kmax,
+             const ColSrc *from, hipStream_t s)
 {
+    const int planes = from ? P.n2 - from->skip : P.n2;
     if (cols_ok(P.n1)) {
         const int C = cols_width(P.n1);
-        const dim3 grid((P.nh + C - 1) / C, P.n2, nc);
+        const dim3 grid((kmax + C - 1) / C, planes, nc);
         const size_t rs = (size_t)P.n2 * P.np;
-        if (mode == 0) launch_cols<0>(P.n1, grid, P.spec, P.tw1, P.nh, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, s);
-        else if (mode == 1) launch_cols<1>(P.n1, grid, P.spec, P.tw1, P.nh, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, s);
-        else launch_cols<2>(P.n1, grid, P.spec, P.tw1, P.nh, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, s);
+        if (mode == 0) launch_cols<0>(P.n1, grid, P.spec, P.tw1, kmax, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, nullptr, s);
+        else if (mode == 1) launch_cols<1>(P.n1, grid, P.spec, P.tw1, kmax, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, from, s);
+        else launch_cols<2>(P.n1, grid, P.spec, P.tw1, kmax, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, from, s);
         return;
     }
     const ColGeom cg = col_geom(P.n1);
     const int C1 = 1 << cg.logC;
-    const dim3 grid((P.nh + C1 - 1) / C1, P.n2, nc);
-    hipLaunchKernelGGL((k_fft_x1_mult<TPB>), grid, dim3(TPB), cg.lds, s, P.spec, P.tw1, ilog2(P.n1), P.n1, P.n2, P.nh,
-                       P.np, cg.logC, kind, beta, scale, spec_cs, mode);
+    const dim3 grid((kmax + C1 - 1) / C1, planes, nc);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(TPB), cg.lds, s, P.spec, P.tw1, ilog2(P.n1), P.n1, P.n2, kmax, P.np,
+                           cg.logC, kind, beta, scale, spec_cs, mode, from ? *from : ColSrc{});
+    };
+    if (from) go(k_fft_x1_mult<TPB, true>);
+    else go(k_fft_x1_mult<TPB, false>);
 }
 
 } // namespace
@@ -1274,16 +1342,16 @@ void spectral_apply(const FFTPlan &P, int kind, float beta, float beta_w, int nc
         float *outc = out + c0 * N;
         const float *addc = add ? add + c0 * N : nullptr;
         if (planes_ok(P)) {
-            launch_planes<false>(P, inc, nullptr, nullptr, nc, spec_cs, s);
-            pass_x1(P, 0, kind, beta, scale, nc, spec_cs, s);
-            launch_planes<true>(P, nullptr, outc, addc, nc, spec_cs, s);
+            launch_planes<false>(P, inc, nullptr, nullptr, nc, spec_cs, P.nh, P.n2, s);
+            pass_x1(P, 0, kind, beta, scale, nc, spec_cs, P.nh, nullptr, s);
+            launch_planes<true>(P, nullptr, outc, addc, nc, spec_cs, P.nh, P.n2, s);
             continue;
         }
         pass_r2c(P, inc, nc, logM, lognl3, lds3, spec_cs, s);
-        pass_x2(P, false, nc, spec_cs, s);
-        pass_x1(P, 0, kind, beta, scale, nc, spec_cs, s);
-        pass_x2(P, true, nc, spec_cs, s);
-        pass_c2r(P, outc, addc, nc, logM, lognl3, lds3, spec_cs, s);
+        pass_x2(P, false, nc, spec_cs, P.nh, nullptr, s);
+        pass_x1(P, 0, kind, beta, scale, nc, spec_cs, P.nh, nullptr, s);
+        pass_x2(P, true, nc, spec_cs, P.nh, nullptr, s);
+        pass_c2r(P, outc, addc, nc, logM, lognl3, lds3, spec_cs, P.nh, s);
     }
 }
 
@@ -1309,60 +1377,84 @@ PassGeom geom(const FFTPlan &P)
     return G;
 }
 
-void forward3(const FFTPlan &P, const PassGeom &G, int nc, const float *in, hipStream_t s)
+// Forward and inverse transforms of nc components, in full or for the modes
+// |k_d| < m_d alone (full: m_d = n_d and kmax = nh): a forward pass visits the
+// columns and planes that are kept, an inverse pass reads the others as zero.
+struct Keep {
+    int m1, m2, kmax;
+};
+
+ColSrc whole(const FFTPlan &P, const PassGeom &G, const float2 *src, size_t ps, size_t rs)
 {
-    if (planes_ok(P)) {
-        launch_planes<false>(P, in, nullptr, nullptr, nc, G.spec_cs, s);
-    } else {
-        pass_r2c(P, in, nc, G.logM, G.lognl3, G.lds3, G.spec_cs, s);
-        pass_x2(P, false, nc, G.spec_cs, s);
-    }
-    pass_x1(P, 1, 2, 0.f, 1.f, nc, G.spec_cs, s);
+    return ColSrc{src, G.spec_cs, ps, rs, 0, 1 << 30, 1 << 30, 0, 0, 1.0f};
 }
 
-void inverse3(const FFTPlan &P, const PassGeom &G, int nc, float *out, hipStream_t s)
+void forward3(const FFTPlan &P, const PassGeom &G, int nc, const float *in, const Keep &k, hipStream_t s)
 {
-    pass_x1(P, 2, 2, 0.f, 1.f, nc, G.spec_cs, s);
     if (planes_ok(P)) {
-        launch_planes<true>(P, nullptr, out, nullptr, nc, G.spec_cs, s);
+        launch_planes<false>(P, in, nullptr, nullptr, nc, G.spec_cs, P.nh, P.n2, s);
+    } else {
+        pass_r2c(P, in, nc, G.logM, G.lognl3, G.lds3, G.spec_cs, s);
+        pass_x2(P, false, nc, G.spec_cs, k.kmax, nullptr, s);
+    }
+    if (k.m2 >= P.n2) {
+        pass_x1(P, 1, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, nullptr, s);
+    } else {
+        ColSrc c = whole(P, G, P.spec, P.np, (size_t)P.n2 * P.np);
+        c.mp = k.m2;
+        c.skip = P.n2 - (2 * k.m2 - 1);
+        pass_x1(P, 1, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, &c, s);
+    }
+}
+
+// from: source of the x1 pass (NULL: this plan's spectrum, in full)
+void inverse3(const FFTPlan &P, const PassGeom &G, int nc, float *out, const Keep &k, const ColSrc *from, hipStream_t s)
+{
+    pass_x1(P, 2, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, from, s);
+    if (planes_ok(P)) {
+        launch_planes<true>(P, nullptr, out, nullptr, nc, G.spec_cs, k.kmax, k.m2, s);
         return;
     }
-    pass_x2(P, true, nc, G.spec_cs, s);
-    pass_c2r(P, out, nullptr, nc, G.logM, G.lognl3, G.lds3, G.spec_cs, s);
+    if (k.m2 >= P.n2) {
+        pass_x2(P, true, nc, G.spec_cs, k.kmax, nullptr, s);
+    } else {
+        ColSrc c = whole(P, G, P.spec, (size_t)P.n2 * P.np, P.np);
+        c.La = P.n2;
+        c.m = k.m2;
+        pass_x2(P, true, nc, G.spec_cs, k.kmax, &c, s);
+    }
+    pass_c2r(P, out, nullptr, nc, G.logM, G.lognl3, G.lds3, G.spec_cs, k.kmax, s);
 }
 
 void coupled3(const FFTPlan &P, int kind, float beta_v, float beta_w, const float *in, float *out, hipStream_t s)
 {
     // every plan of the library holds three components of spectrum
     const PassGeom G = geom(P);
-    forward3(P, G, 3, in, s);
+    const Keep all{P.n1, P.n2, P.nh};
+    forward3(P, G, 3, in, all, s);
     const size_t modes = (size_t)P.n1 * P.n2 * P.nh;
     hipLaunchKernelGGL(k_spec_mult3, dim3((unsigned)((modes + TPB - 1) / TPB)), dim3(TPB), 0, s, P.spec, P.n1, P.n2,
                        P.nh, P.np, kind, beta_v, beta_w, (float)(1.0 / (double)G.N), G.spec_cs);
-    inverse3(P, G, 3, out, s);
-}
-
-__global__ __launch_bounds__(TPB) void k_scale_f(float *x, float a, size_t n)
-{
-    const size_t e = (size_t)blockIdx.x * TPB + threadIdx.x;
-    if (e < n) x[e] *= a;
+    inverse3(P, G, 3, out, all, nullptr, s);
 }
 
 } // namespace
 
+// The modes |k_d| < m_d = min(a_d, b_d) / 2 go straight from A's spectrum into
+// B's x1 pass, scaled by 1 / N_A (a power of two); every pass visits only the
+// columns and planes that hold them.  128^3 -> 256^3 (3 fields): with a copy
+// into a zero-filled spectrum, full inverse passes and a scaling pass 434 us,
+// 155 us so; the real rows written (201 MB) bound the last pass (60 us).
 void spectral_resample(const FFTPlan &A, const FFTPlan &B, int ncomp, const float *in, float *out, hipStream_t s)
 {
     const PassGeom GA = geom(A), GB = geom(B);
     for (int c0 = 0; c0 < ncomp; c0 += min(A.ncomp_max, B.ncomp_max)) {
         const int nc = min(ncomp - c0, min(A.ncomp_max, B.ncomp_max));
-        forward3(A, GA, nc, in + c0 * GA.N, s);
-        const size_t nb = (size_t)B.n1 * B.n2 * B.nh * nc;
-        hipLaunchKernelGGL(k_mode_copy, dim3((unsigned)((nb + TPB - 1) / TPB)), dim3(TPB), 0, s, A.spec, B.spec, A.n1,
-                           A.n2, A.n3, B.n1, B.n2, B.n3, nc);
-        inverse3(B, GB, nc, out + c0 * GB.N, s);
-        const size_t n = GB.N * nc;
-        hipLaunchKernelGGL(k_scale_f, dim3((unsigned)((n + TPB - 1) / TPB)), dim3(TPB), 0, s, out + c0 * GB.N,
-                           (float)(1.0 / (double)GA.N), n);
+        const Keep k{min(A.n1, B.n1) / 2, min(A.n2, B.n2) / 2, min(A.n3, B.n3) / 2};
+        forward3(A, GA, nc, in + c0 * GA.N, k, s);
+        const ColSrc from{A.spec, GA.spec_cs, (size_t)A.np, (size_t)A.n2 * A.np, A.n1, k.m1, k.m2,
+                          B.n2 - (2 * k.m2 - 1), A.n2 - B.n2, (float)(1.0 / (double)GA.N)};
+        inverse3(B, GB, nc, out + c0 * GB.N, k, &from, s);
     }
 }
 

@@ -72,3 +72,22 @@ def test_spectral_operators_on_short_lines(shape, kind):
     for c in (1, 3):
         out = r.spectral(kind, x[:c].contiguous()).cpu().double()
         assert float((out - ref[:c]).norm() / ref[:c].norm()) < 1e-5
+
+
+# resampling through pruned passes: up, down and mixed, every kind of line
+@pytest.mark.parametrize("ncomp", [1, 3])
+@pytest.mark.parametrize("a,b", [((16, 16, 16), (32, 64, 16)), ((64, 32, 128), (64, 32, 128)),
+                                 ((128, 64, 32), (16, 256, 256)), ((16, 32, 1024), (512, 16, 64)),
+                                 ((1024, 16, 32), (32, 64, 512)), ((32, 512, 64), (128, 1024, 16))])
+def test_resampling_keeps_the_common_modes(a, b, ncomp):
+    from paper_2209_08189_amd.claire import Resampler
+    x = torch.randn((ncomp,) + a, generator=torch.Generator().manual_seed(sum(a) + sum(b)))
+    A = torch.fft.rfftn(x.double(), dim=(1, 2, 3))
+    B = torch.zeros((ncomp,) + b[:2] + (b[2] // 2 + 1,), dtype=A.dtype)
+    m = [min(p, q) // 2 for p, q in zip(a, b)]
+    k = [torch.arange(-(s - 1), s) for s in m[:2]]
+    B[:, (k[0] % b[0])[:, None], (k[1] % b[1])[None, :], :m[2]] = \
+        A[:, (k[0] % a[0])[:, None], (k[1] % a[1])[None, :], :m[2]]
+    ref = torch.fft.irfftn(B, s=b, dim=(1, 2, 3)) * (b[0] * b[1] * b[2] / (a[0] * a[1] * a[2]))
+    out = Resampler(a, b)(x.cuda()).cpu().double().reshape(ref.shape)
+    assert float((out - ref).norm() / ref.norm()) < 1e-5
