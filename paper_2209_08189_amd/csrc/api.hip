@@ -3,7 +3,7 @@
 //
 // Every field operation is a HIP kernel on the context stream; the host only
 // sequences launches and reads FP64 scalars (dot products, norms, objective
-// parts) back, one synchronisation per scalar.
+// parts) back, all those of an evaluation in one synchronisation.
 #include "internal.h"
 
 #include <algorithm>
@@ -199,30 +199,25 @@ template <typename F> void run(cl_ctx *ctx, int kclass, F &&f) { run_on(ctx, ctx
 // ---- helpers
 void *slot(cl_ctx *ctx, void *base, int dt, int j) { return (char *)base + (size_t)j * ctx->N * dtype_size(dt); }
 
-double read_scalar(cl_ctx *ctx)
+// scalars of an evaluation on the device (dscal), read together
+enum { SC_MIS = 0, SC_REG = 1, SC_GN2 = 2, SC_GVT = 3, SC_COUNT = 4 };
+
+// the first n scalars (host)
+const double *read_scalars(cl_ctx *ctx, int n)
 {
-    HIPCHK(hipMemcpyAsync(ctx->hscal, ctx->dscal, sizeof(double), hipMemcpyDeviceToHost, ctx->s));
+    HIPCHK(hipMemcpyAsync(ctx->hscal, ctx->dscal, n * sizeof(double), hipMemcpyDeviceToHost, ctx->s));
     HIPCHK(hipStreamSynchronize(ctx->s));
-    return *ctx->hscal;
+    return ctx->hscal;
 }
 
-// h-weighted FP64 inner product of two FP32 vectors of n values
-double dotw(cl_ctx *ctx, const float *a, const float *b, size_t n)
+// scale x inner product of two FP32 vectors of n values (FP64) into *out (device)
+void dot_to(cl_ctx *ctx, const float *a, const float *b, size_t n, double scale, double *out)
 {
+    const int nb = std::min(ctx->nparts, reduce_blocks(n));
     run(ctx, CL_K_VEC, [&] {
-        launch_dot(a, b, n, ctx->partials, ctx->nparts, ctx->s);
-        launch_finalize(ctx->partials, ctx->nparts, ctx->hv, ctx->dscal, ctx->s);
+        launch_dot(a, b, n, ctx->partials, nb, ctx->s);
+        launch_finalize(ctx->partials, nb, scale, out, ctx->s);
     });
-    return read_scalar(ctx);
-}
-
-double count_nonfinite(cl_ctx *ctx, const float *a, size_t n)
-{
-    run(ctx, CL_K_VEC, [&] {
-        launch_count_nonfinite(a, n, ctx->partials, ctx->nparts, ctx->s);
-        launch_finalize(ctx->partials, ctx->nparts, 1.0, ctx->dscal, ctx->s);
-    });
-    return read_scalar(ctx);
 }
 
 void spectral(cl_ctx *ctx, int kind, int ncomp, const float *in, float *out, const float *add)
@@ -288,33 +283,31 @@ void ensure_sgrad(cl_ctx *ctx)
     ctx->sgrad = true;
 }
 
-double mismatch_only(cl_ctx *ctx)
-{
-    run(ctx, CL_K_VEC, [&] {
-        launch_sq_diff(ctx->g, ctx->dts, ctx->m1, slot(ctx, ctx->m, ctx->dts, ctx->nt), ctx->partials, ctx->nparts,
-                       ctx->s);
-        launch_finalize(ctx->partials, ctx->nparts, 0.5 * ctx->hv, ctx->dscal, ctx->s);
-    });
-    return read_scalar(ctx);
-}
-
-double regulariser(cl_ctx *ctx)
+// beta_v/2 <A v, v> (+ the divergence term) at the current v, into dscal
+void regulariser(cl_ctx *ctx)
 {
     if (!ctx->av) {
         spectral(ctx, 0, 3, ctx->v, ctx->Av, nullptr);
         ctx->av = true;
     }
-    return 0.5 * dotw(ctx, ctx->Av, ctx->v, 3 * ctx->N);
+    dot_to(ctx, ctx->Av, ctx->v, 3 * ctx->N, 0.5 * ctx->hv, ctx->dscal + SC_REG);
 }
 
-void objective(cl_ctx *ctx, double *J, double *mis, double *reg)
+// gvt (optional): receives SC_GVT, whose dot product the caller has enqueued
+void objective(cl_ctx *ctx, double *J, double *mis, double *reg, double *gvt = nullptr)
 {
     ensure_state(ctx);
-    const double a = mismatch_only(ctx);
-    const double r = regulariser(ctx);
-    if (mis) *mis = a;
-    if (reg) *reg = r;
-    if (J) *J = a + r;
+    run(ctx, CL_K_VEC, [&] {
+        launch_sq_diff(ctx->g, ctx->dts, ctx->m1, slot(ctx, ctx->m, ctx->dts, ctx->nt), ctx->partials, ctx->nparts,
+                       ctx->s);
+        launch_finalize(ctx->partials, ctx->nparts, 0.5 * ctx->hv, ctx->dscal + SC_MIS, ctx->s);
+    });
+    regulariser(ctx);
+    const double *sc = read_scalars(ctx, SC_COUNT);
+    if (mis) *mis = sc[SC_MIS];
+    if (reg) *reg = sc[SC_REG];
+    if (J) *J = sc[SC_MIS] + sc[SC_REG];
+    if (gvt) *gvt = sc[SC_GVT];
 }
 
 QuadArgs quad_args(cl_ctx *ctx)
@@ -354,14 +347,10 @@ double gradient(cl_ctx *ctx, double *J, double *mis_out, double *reg_out)
     run(ctx, CL_K_VEC, [&] {
         launch_residual(ctx->g, ctx->dts, ctx->m1, slot(ctx, ctx->m, ctx->dts, ctx->nt), ctx->dta,
                         slot(ctx, ctx->lam, ctx->dta, ctx->nt), ctx->partials, ctx->nparts, ctx->s);
-        launch_finalize(ctx->partials, ctx->nparts, 0.5 * ctx->hv, ctx->dscal, ctx->s);
+        launch_finalize(ctx->partials, ctx->nparts, 0.5 * ctx->hv, ctx->dscal + SC_MIS, ctx->s);
     });
-    const double mis = read_scalar(ctx);
     adjoint_sweep(ctx);
-    if (!ctx->av) {
-        spectral(ctx, 0, 3, ctx->v, ctx->Av, nullptr);
-        ctx->av = true;
-    }
+    regulariser(ctx);
     const QuadArgs qa = quad_args(ctx);
     const size_t n3 = 3 * ctx->N;
     if (ctx->opt.beta_w == 0.0) {
@@ -375,12 +364,13 @@ double gradient(cl_ctx *ctx, double *J, double *mis_out, double *reg_out)
         spectral_scalar(ctx, 0, 3, ctx->v, ctx->tmp3);
         run(ctx, CL_K_VEC, [&] { launch_axpy(ctx->pz, ctx->pz, ctx->tmp3, 1.0f, n3, ctx->s); });
     }
-    const double reg = 0.5 * dotw(ctx, ctx->Av, ctx->v, 3 * ctx->N);
-    if (mis_out) *mis_out = mis;
-    if (reg_out) *reg_out = reg;
-    if (J) *J = mis + reg;
     const float *g = ctx->opt.beta_w != 0.0 ? ctx->pz : ctx->grad;
-    return std::sqrt(dotw(ctx, g, g, 3 * ctx->N));
+    dot_to(ctx, g, g, n3, ctx->hv, ctx->dscal + SC_GN2);
+    const double *sc = read_scalars(ctx, SC_GN2 + 1);
+    if (mis_out) *mis_out = sc[SC_MIS];
+    if (reg_out) *reg_out = sc[SC_REG];
+    if (J) *J = sc[SC_MIS] + sc[SC_REG];
+    return std::sqrt(sc[SC_GN2]);
 }
 
 // the reduced gradient after gradient(): beta_v A v + K b, or ctx->grad
@@ -577,13 +567,6 @@ void precond(cl_ctx *ctx, const float *r, float *z)
         spectral(ctx, 1, 3, r, z, nullptr);
 }
 
-void load_velocity(cl_ctx *ctx, const float *src_dev)
-{
-    HIPCHK(hipMemcpyAsync(ctx->v, src_dev, 3 * ctx->N * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
-    ctx->vel = true;
-    ctx->feet_f = ctx->feet_b = ctx->state = ctx->av = false;
-}
-
 // PCG on H x = rhs (rhs in ctx->pr on entry); solution in ctx->px.
 int pcg(cl_ctx *ctx, int max_pcg, double eta, int forced, int *iters)
 {
@@ -596,11 +579,8 @@ int pcg(cl_ctx *ctx, int max_pcg, double eta, int forced, int *iters)
     run(ctx, CL_K_VEC, [&] { launch_fill_f32(ctx->px, 0.0f, n, ctx->s); });
     precond(ctx, ctx->pr, ctx->pz);
     HIPCHK(hipMemcpyAsync(ctx->pp, ctx->pz, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
-    run(ctx, CL_K_VEC, [&] {
-        launch_dot(ctx->pr, ctx->pz, n, ctx->partials, ctx->nparts, ctx->s);
-        launch_finalize(ctx->partials, ctx->nparts, ctx->hv, sc + PCG_RZ, ctx->s);
-    });
-    const double r0 = std::sqrt(dotw(ctx, ctx->pr, ctx->pr, n));
+    dot_to(ctx, ctx->pr, ctx->pz, n, ctx->hv, sc + PCG_RZ);
+    dot_to(ctx, ctx->pr, ctx->pr, n, ctx->hv, sc + PCG_R0);   // read with the first iteration's scalars
     // beta A p by recurrence: p = z + b p and beta A z = r - mean(r) (A has
     // no k = 0 mode, the preconditioner maps it by 1/beta), so the matvecs
     // inside PCG need no FFT pair of their own.  With the zero-velocity
@@ -630,7 +610,7 @@ int pcg(cl_ctx *ctx, int max_pcg, double eta, int forced, int *iters)
             if (it == 0) HIPCHK(hipMemcpyAsync(ctx->px, ctx->pz, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
             break;
         }
-        const double rn = std::sqrt(ctx->hscal[PCG_RR]);
+        const double rn = std::sqrt(ctx->hscal[PCG_RR]), r0 = std::sqrt(ctx->hscal[PCG_R0]);
         ++it;
         if (forced < 0 && rn <= eta * r0) break;
         if (it >= limit) break;
@@ -698,7 +678,7 @@ int solve(cl_ctx *ctx, const int *forced_pcg, const double *forced_alpha, int fo
         R.pcg_iters_total += its;
         if (ctx->opt.fault_flip_direction)   // failure injection: an ascent direction
             run(ctx, CL_K_VEC, [&] { launch_scale(ctx->px, ctx->px, -1.0f, n, ctx->s); });
-        const double gvt = dotw(ctx, ctx->grad, ctx->px, n);
+        if (!forced) dot_to(ctx, ctx->grad, ctx->px, n, ctx->hv, ctx->dscal + SC_GVT);
         double alpha = 1.0;
         int trials = 0;
         bool ok = false;
@@ -713,8 +693,8 @@ int solve(cl_ctx *ctx, const int *forced_pcg, const double *forced_alpha, int fo
                 run(ctx, CL_K_VEC, [&] { launch_axpy(ctx->vtrial, ctx->v, ctx->px, (float)alpha, n, ctx->s); });
                 std::swap(ctx->v, ctx->vtrial);
                 ctx->feet_f = ctx->feet_b = ctx->state = ctx->av = false;
-                double Jt;
-                objective(ctx, &Jt, nullptr, nullptr);
+                double Jt, gvt;
+                objective(ctx, &Jt, nullptr, nullptr, &gvt);
                 R.linesearch_trials++;
                 if (Jt <= J + 1e-4 * alpha * gvt) { ok = true; break; }
                 std::swap(ctx->v, ctx->vtrial);   // back to the accepted v
@@ -1164,7 +1144,7 @@ int cl_create(cl_ctx **out, int n1, int n2, int n3, const cl_options *opt)
         ctx->divv = (float *)alloc(N * sizeof(float));
         ctx->nparts = reduce_blocks(3 * N);
         ctx->partials = (double *)alloc(ctx->nparts * sizeof(double));
-        ctx->dscal = (double *)alloc(sizeof(double) * 4);
+        ctx->dscal = (double *)alloc(sizeof(double) * SC_COUNT);
         ctx->nqparts = std::max(quadrature_blocks_max(ctx->g), 6 * reduce_blocks(ctx->N));
         ctx->qparts = (double *)alloc(sizeof(double) * ctx->nqparts);
         ctx->pscal = (double *)alloc(sizeof(double) * PCG_NSCAL);
@@ -1227,11 +1207,19 @@ int cl_set_images(cl_ctx *ctx, const void *m0, const void *m1, int dt)
     if (dt != CL_F32) return fail(ctx, CL_ERR_DTYPE, "images must be passed as CL_F32");
     API_BEGIN
     const size_t N = ctx->N;
-    if (count_nonfinite(ctx, (const float *)m0, N) > 0 || count_nonfinite(ctx, (const float *)m1, N) > 0)
-        return fail(ctx, CL_ERR_NONFINITE, "image contains NaN or Inf");
+    const int nb = std::min(ctx->nparts, reduce_blocks(N));
+    const float *src[2] = {(const float *)m0, (const float *)m1};
+    void *dst[2] = {ctx->m0, ctx->m1};
     run(ctx, CL_K_VEC, [&] {
-        launch_convert(ctx->dts, ctx->m0, (const float *)m0, N, ctx->s);
-        launch_convert(ctx->dts, ctx->m1, (const float *)m1, N, ctx->s);
+        for (int i = 0; i < 2; ++i) {
+            launch_count_nonfinite(src[i], nullptr, N, ctx->partials, nb, ctx->s);
+            launch_finalize(ctx->partials, nb, 1.0, ctx->dscal + i, ctx->s);
+        }
+    });
+    const double *bad = read_scalars(ctx, 2);
+    if (bad[0] > 0 || bad[1] > 0) return fail(ctx, CL_ERR_NONFINITE, "image contains NaN or Inf");
+    run(ctx, CL_K_VEC, [&] {
+        for (int i = 0; i < 2; ++i) launch_convert(ctx->dts, dst[i], src[i], N, ctx->s);
     });
     ctx->images = true;
     ctx->state = false;
@@ -1246,8 +1234,17 @@ int cl_set_velocity(cl_ctx *ctx, const float *v)
     NEED_CTX();
     if (!v) return fail(ctx, CL_ERR_ARG, "NULL velocity pointer");
     API_BEGIN
-    if (count_nonfinite(ctx, v, 3 * ctx->N) > 0) return fail(ctx, CL_ERR_NONFINITE, "velocity contains NaN or Inf");
-    load_velocity(ctx, v);
+    // checked and copied in one pass, into the line search's vector: a velocity
+    // that is refused leaves the current one as it is
+    const size_t n = 3 * ctx->N;
+    run(ctx, CL_K_VEC, [&] {
+        launch_count_nonfinite(v, ctx->vtrial, n, ctx->partials, ctx->nparts, ctx->s);
+        launch_finalize(ctx->partials, ctx->nparts, 1.0, ctx->dscal, ctx->s);
+    });
+    if (read_scalars(ctx, 1)[0] > 0) return fail(ctx, CL_ERR_NONFINITE, "velocity contains NaN or Inf");
+    std::swap(ctx->v, ctx->vtrial);
+    ctx->vel = true;
+    ctx->feet_f = ctx->feet_b = ctx->state = ctx->av = false;
     return CL_OK;
     API_END
 }
@@ -1593,12 +1590,8 @@ int cl_dot(cl_ctx *ctx, const float *a, const float *b, size_t n, double *out)
     NEED_CTX();
     if (!a || !b || !out) return fail(ctx, CL_ERR_ARG, "NULL pointer");
     API_BEGIN
-    const int nb = std::min(ctx->nparts, reduce_blocks(n));
-    run(ctx, CL_K_VEC, [&] {
-        launch_dot(a, b, n, ctx->partials, nb, ctx->s);
-        launch_finalize(ctx->partials, nb, ctx->hv, ctx->dscal, ctx->s);
-    });
-    *out = read_scalar(ctx);
+    dot_to(ctx, a, b, n, ctx->hv, ctx->dscal);
+    *out = *read_scalars(ctx, 1);
     return CL_OK;
     API_END
 }

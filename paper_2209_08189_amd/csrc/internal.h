@@ -195,13 +195,14 @@ void launch_sq_diff(const Grid &g, int dt_m, const void *a, const void *b, doubl
 int reduce_blocks(size_t n);
 void launch_dot(const float *a, const float *b, size_t n, double *partials, int nblocks, hipStream_t s);
 void launch_finalize(const double *partials, int nblocks, double scale, double *out, hipStream_t s);
-void launch_count_nonfinite(const float *a, size_t n, double *partials, int nblocks, hipStream_t s);
+// per-block counts of values that are not finite; copy (may be NULL) receives a
+void launch_count_nonfinite(const float *a, float *copy, size_t n, double *partials, int nblocks, hipStream_t s);
 // x += alpha p; r -= alpha Hp; partials of r.r
 // Fused PCG: FP64 device scalars sc[PCG_*]
 // (PCG_INNER: a second block with the same slots for the inner solve of the
 // zero-velocity preconditioner)
 enum { PCG_RR = 0, PCG_SUMR = 1, PCG_PHP = 4, PCG_RZ = 5, PCG_RZNEW = 6, PCG_ALPHA = 7, PCG_BETA = 8, PCG_NEG = 9,
-       PCG_RZOLD = 10, PCG_INNER = 16, PCG_NSCAL = 32 };
+       PCG_RZOLD = 10, PCG_R0 = 11, PCG_INNER = 16, PCG_NSCAL = 32 };
 // flexible beta = (rz_new - rz_old) / rz, then rz = rz_new
 void launch_pcg_beta_flex(double *sc, hipStream_t s);
 // p = z + beta p, q = Lz + beta q (3 n values)

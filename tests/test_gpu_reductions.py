@@ -51,3 +51,23 @@ def test_dot_against_numpy(n):
     hv = (2.0 * math.pi / 32) ** 3
     got = r.dot(a.cuda(), b.cuda())
     assert abs(got - hv * p.sum()) <= 2 * n * 2.0 ** -53 * hv * np.abs(p).sum()
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2])
+def test_velocity_is_checked_and_copied_from_any_element(offset):
+    from paper_2209_08189_amd.claire import ClaireError, Registration
+    shape = (16, 16, 32)
+    n = 3 * 16 * 16 * 32
+    r = Registration(shape)
+    buf = torch.zeros(n + 4, device="cuda")
+    v = buf[offset:offset + n].view((3,) + shape)
+    v.copy_(_velocity(shape, 0.1))
+    r.set_velocity(v)
+    assert torch.equal(r.velocity(), v)
+    good = v.clone()
+    for bad in (float("nan"), float("inf"), -float("inf")):
+        v.copy_(2 * good)
+        v[2, 15, 15, 31] = bad           # the last value
+        with pytest.raises(ClaireError):
+            r.set_velocity(v)
+        assert torch.equal(r.velocity(), good)
