@@ -465,11 +465,24 @@ struct H0Level {
     float *ir, *izi, *ip, *iLp, *ih;
 };
 
-void level_spectral(cl_ctx *ctx, const H0Level &L, int kind, const float *in, float *out)
+// z = P r on one grid and the partials of <r, z>: their buffer and count.  With
+// uncoupled components they are formed in the transform's x1 pass (Parseval),
+// into scratch, which holds 3 N floats (one double per workgroup of that pass is
+// far less); coupled components (beta_w != 0) have no such pass.
+struct DotParts {
+    const double *parts;
+    int count;
+};
+DotParts precond_dot(cl_ctx *ctx, const FFTPlan &fft, size_t N, const float *r, float *z, float *scratch)
 {
+    double *dot = ctx->opt.beta_w == 0.0 ? (double *)scratch : nullptr;
     run(ctx, CL_K_FFT, [&] {
-        spectral_apply(*L.fft, kind, (float)ctx->opt.beta_v, (float)ctx->opt.beta_w, 3, in, out, nullptr, ctx->s);
+        spectral_apply(fft, 1, (float)ctx->opt.beta_v, (float)ctx->opt.beta_w, 3, r, z, nullptr, ctx->s, dot);
     });
+    if (dot) return {dot, spectral_dot_blocks(fft)};
+    const int nb = std::min(ctx->nparts, reduce_blocks(3 * N));
+    run(ctx, CL_K_VEC, [&] { launch_dot(r, z, 3 * N, ctx->partials, nb, ctx->s); });
+    return {ctx->partials, nb};
 }
 
 // z ~ H0^-1 r (zero-velocity Hessian) on grid L by opt.precond_inner CG
@@ -486,31 +499,27 @@ void h0_inner(cl_ctx *ctx, const H0Level &L, const float *r, float *z)
     double *sc = ctx->pscal + PCG_INNER;
     const int nb = std::min(ctx->nparts, reduce_blocks(n));
     HIPCHK(hipMemcpyAsync(L.ir, r, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
-    run(ctx, CL_K_VEC, [&] { launch_fill_f32(z, 0.0f, n, ctx->s); });
-    level_spectral(ctx, L, 1, L.ir, L.izi);
+    DotParts d = precond_dot(ctx, *L.fft, N, L.ir, L.izi, L.ih);
     HIPCHK(hipMemcpyAsync(L.ip, L.izi, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
     HIPCHK(hipMemcpyAsync(L.iLp, L.ir, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
-    run(ctx, CL_K_VEC, [&] {
-        launch_dot(L.ir, L.izi, n, ctx->partials, nb, ctx->s);
-        launch_finalize(ctx->partials, nb, L.hv, sc + PCG_RZ, ctx->s);
-    });
+    run(ctx, CL_K_VEC, [&] { launch_finalize(d.parts, d.count, L.hv, sc + PCG_RZ, ctx->s); });
+    // z takes the step of an iteration in the pass that forms the next direction
     const int inner = ctx->opt.precond_inner;
     for (int it = 0; it < inner; ++it) {
         run(ctx, CL_K_VEC, [&] {
             if (it == 0)
                 launch_h0_apply(L.ip, L.iLp, L.G0, L.ih, N, ctx->partials, nb, ctx->s);
             else
-                launch_h0_direction_apply(L.ip, L.iLp, L.izi, L.ir, L.G0, L.ih, sc, N, ctx->partials, nb, ctx->s);
+                launch_h0_direction_apply(z, it == 1, L.ip, L.iLp, L.izi, L.ir, L.G0, L.ih, sc, N, ctx->partials, nb,
+                                          ctx->s);
             launch_finalize_alpha(ctx->partials, nb, L.hv, sc, ctx->s);
-            launch_h0_update(z, L.ir, L.ip, L.ih, sc, N, ctx->s);
         });
         if (it == inner - 1) break;
-        level_spectral(ctx, L, 1, L.ir, L.izi);
-        run(ctx, CL_K_VEC, [&] {
-            launch_dot(L.ir, L.izi, n, ctx->partials, nb, ctx->s);
-            launch_finalize_beta(ctx->partials, nb, L.hv, sc, ctx->s);
-        });
+        run(ctx, CL_K_VEC, [&] { launch_h0_residual(L.ir, L.ih, sc, N, ctx->s); });
+        d = precond_dot(ctx, *L.fft, N, L.ir, L.izi, L.ih);
+        run(ctx, CL_K_VEC, [&] { launch_finalize_beta(d.parts, d.count, L.hv, sc, ctx->s); });
     }
+    run(ctx, CL_K_VEC, [&] { launch_h0_step(z, inner == 1, L.ip, sc, N, ctx->s); });
 }
 
 // Full resolution: grad_h m0 is the stored G^0; ctx->ilz receives L z (one
@@ -576,16 +585,21 @@ int pcg(cl_ctx *ctx, int max_pcg, double eta, int forced, int *iters)
     const size_t n = 3 * ctx->N;
     double *sc = ctx->pscal;
     const int nbc = reduce_blocks(ctx->N);
+    const bool h0 = ctx->opt.precond == CL_PRECOND_H0 || ctx->opt.precond == CL_PRECOND_H0_2LEVEL;
     run(ctx, CL_K_VEC, [&] { launch_fill_f32(ctx->px, 0.0f, n, ctx->s); });
-    precond(ctx, ctx->pr, ctx->pz);
+    if (h0) {
+        precond(ctx, ctx->pr, ctx->pz);
+        dot_to(ctx, ctx->pr, ctx->pz, n, ctx->hv, sc + PCG_RZ);
+    } else {
+        const DotParts d = precond_dot(ctx, ctx->fft, ctx->N, ctx->pr, ctx->pz, ctx->pHp);
+        run(ctx, CL_K_VEC, [&] { launch_finalize(d.parts, d.count, ctx->hv, sc + PCG_RZ, ctx->s); });
+    }
     HIPCHK(hipMemcpyAsync(ctx->pp, ctx->pz, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
-    dot_to(ctx, ctx->pr, ctx->pz, n, ctx->hv, sc + PCG_RZ);
     dot_to(ctx, ctx->pr, ctx->pr, n, ctx->hv, sc + PCG_R0);   // read with the first iteration's scalars
     // beta A p by recurrence: p = z + b p and beta A z = r - mean(r) (A has
     // no k = 0 mode, the preconditioner maps it by 1/beta), so the matvecs
     // inside PCG need no FFT pair of their own.  With the zero-velocity
     // preconditioner L z comes from its inner solve.
-    const bool h0 = ctx->opt.precond == CL_PRECOND_H0 || ctx->opt.precond == CL_PRECOND_H0_2LEVEL;
     float *pAp = ctx->tmp3;
     if (h0) {
         HIPCHK(hipMemcpyAsync(pAp, ctx->ilz, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
@@ -628,10 +642,9 @@ int pcg(cl_ctx *ctx, int max_pcg, double eta, int forced, int *iters)
             });
             continue;
         }
-        precond(ctx, ctx->pr, ctx->pz);
+        const DotParts d = precond_dot(ctx, ctx->fft, ctx->N, ctx->pr, ctx->pz, ctx->pHp);
         run(ctx, CL_K_VEC, [&] {
-            launch_dot(ctx->pr, ctx->pz, n, ctx->partials, ctx->nparts, ctx->s);
-            launch_finalize_beta(ctx->partials, ctx->nparts, ctx->hv, sc, ctx->s);
+            launch_finalize_beta(d.parts, d.count, ctx->hv, sc, ctx->s);
             launch_pcg_direction(ctx->pp, pAp, ctx->pz, ctx->pr, sc, ctx->N, ctx->s);
         });
     }

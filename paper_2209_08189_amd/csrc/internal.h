@@ -208,14 +208,15 @@ void launch_pcg_beta_flex(double *sc, hipStream_t s);
 // p = z + beta p, q = Lz + beta q (3 n values)
 void launch_pcg_direction_lz(float *p, float *q, const float *z, const float *Lz, const double *sc, size_t n,
                              hipStream_t s);
-// y += sc[PCG_ALPHA] x over 3 n values
-void launch_axpy_sc(float *y, const float *x, const double *sc, size_t n, hipStream_t s);
-// p = z + beta p, q = r + beta q, out = q + (G . p) G (beta = sc[PCG_BETA]),
-// per-block partials of p . out
-void launch_h0_direction_apply(float *p, float *q, const float *z, const float *r, const float *G, float *out,
-                               const double *sc, size_t n, double *partials, int nblocks, hipStream_t s);
-// z += alpha p, r -= alpha H (alpha = sc[PCG_ALPHA]) over 3 n values
-void launch_h0_update(float *z, float *r, const float *p, const float *H, const double *sc, size_t n, hipStream_t s);
+// x += alpha p (x = alpha p if first) with the p of the step before, then p = z
+// + beta p, q = r + beta q, out = q + (G . p) G (alpha, beta from sc), per-block
+// partials of p . out
+void launch_h0_direction_apply(float *x, bool first, float *p, float *q, const float *z, const float *r, const float *G,
+                               float *out, const double *sc, size_t n, double *partials, int nblocks, hipStream_t s);
+// r -= alpha H (alpha = sc[PCG_ALPHA]) over 3 n values
+void launch_h0_residual(float *r, const float *H, const double *sc, size_t n, hipStream_t s);
+// x += alpha p (x = alpha p if first) over 3 n values
+void launch_h0_step(float *x, bool first, const float *p, const double *sc, size_t n, hipStream_t s);
 // y_c += scale * sums[c] (3 components of n values)
 void launch_add_sums3(float *y, const double *sums, double scale, size_t n, hipStream_t s);
 // out = Lp + (G . p) G per node (3 components n apart), per-block partials
@@ -268,8 +269,11 @@ size_t fft_spec_bytes(int n1, int n2, int n3, int ncomp);
 // out_c = F^-1[ mult(k) F[in_c] ] (+ add_c), c < ncomp; kind as cl_spectral.
 // With beta_w != 0 and ncomp = 3, kinds 0, 1 and 3 couple the components per
 // mode (regularisation Hessian L, its inverse, K); in may equal out.
+// dot (may be NULL; only for ncomp = ncomp_max components, not coupled): takes
+// spectral_dot_blocks(P) partials whose sum is <in, out>.
+int spectral_dot_blocks(const FFTPlan &P);
 void spectral_apply(const FFTPlan &P, int kind, float beta, float beta_w, int ncomp, const float *in, float *out,
-                    const float *add, hipStream_t s);
+                    const float *add, hipStream_t s, double *dot = nullptr);
 // out (grid B) = spectral resampling of in (grid A): modes with |k_d| <
 // min(n_a, n_b)/2 kept, others zero, scaled so band-limited fields are
 // reproduced; both plans' spectra are used as work space

@@ -421,6 +421,23 @@ __global__ __launch_bounds__(NTP) void k_fft_plane(const float *__restrict__ in,
     }
 }
 
+// <in, out> of a spectral operation from its x1 pass (Parseval): the sum of w
+// |X|^2 sym over the half spectrum, w = 2 off the planes k3 = 0 and k3 = n3 / 2,
+// in FP64, one partial per workgroup (sym carries the transform's 1 / N).  A dot
+// product of the two fields reads both again: 402 MB, 102 us at 256^3, against 1.5 us
+// more in this pass (75.0 -> 76.5).
+__device__ __forceinline__ double dot_term(float2 x, float sym, bool edge)
+{
+    const double m = (double)x.x * x.x + (double)x.y * x.y;
+    return (edge ? 1.0 : 2.0) * (double)sym * m;
+}
+__device__ __forceinline__ void dot_store(double acc, double *__restrict__ partials)
+{
+    acc = block_sum(acc);
+    if (threadIdx.x == 0)
+        partials[((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = acc;
+}
+
 // Pruned column passes (spectral resampling): of the La-point lines of a source
 // spectrum only the rows |k| < m are read, as the rows |k| < m of lines of L
 // points, the others are zero; and only the planes |k| < mp are visited.  A
@@ -531,7 +548,8 @@ __global__ __launch_bounds__(NT) void k_fft_x2(float2 *spec, const float2 *__res
 template <int NT, bool PR>
 __global__ __launch_bounds__(NT) void k_fft_x1_mult(float2 *spec, const float2 *__restrict__ tw1,
                                                      int logn1, int n1, int n2, int nh, int np, int logC, int kind,
-                                                     float beta, float scale, size_t spec_cs, int mode, ColSrc from)
+                                                     float beta, float scale, size_t spec_cs, int mode, ColSrc from,
+                                                     double *__restrict__ dot)
 {
     extern __shared__ float2 sm[];
     const int C = 1 << logC, P = C + 1;
@@ -556,6 +574,7 @@ __global__ __launch_bounds__(NT) void k_fft_x1_mult(float2 *spec, const float2 *
     }
     const float k2 = (float)(i2 < (n2 >> 1) ? i2 : i2 - n2);
     const int tot = C << logn1;
+    double acc = 0.0;
     for (int e = threadIdx.x; e < tot; e += NT) {
         const int l = e & (C - 1), q = e >> logC;
         const float k1 = (float)(q < (n1 >> 1) ? q : q - n1);
@@ -567,9 +586,11 @@ __global__ __launch_bounds__(NT) void k_fft_x1_mult(float2 *spec, const float2 *
         else sym = 1.0f;
         sym *= scale;
         float2 &x = lds[q * P + l];
+        if (dot && l < cw) acc += dot_term(x, sym, c0 + l == 0 || c0 + l == nh - 1);
         x.x *= sym;
         x.y *= sym;
     }
+    if (dot) dot_store(acc, dot);
     __syncthreads();
     fft_lines<true, NT>(lds, P, logC, logn1, tw);
     store_cols<NT>(lds, base, rs, logC, logn1, cw, P);
@@ -599,10 +620,11 @@ __device__ __forceinline__ void cols_load_b(float2 (&v)[16], const float2 *__res
     for (int a = 0; a < 16; ++a) v[a] = ok ? base[(size_t)(R2 * a + b) * rs + l] : make_float2(0.f, 0.f);
 }
 
-template <int R2, int MODE, bool PR>
+template <int R2, int MODE, bool PR, bool DOT>
 __global__ __launch_bounds__(TPB) void k_fft_cols(float2 *spec, const float2 *__restrict__ twL,
                                                   int nh, size_t plane_stride, size_t rs, size_t spec_cs, int kind,
-                                                  float beta, float scale, int n1, int n2, ColSrc from)
+                                                  float beta, float scale, int n1, int n2, ColSrc from,
+                                                  double *__restrict__ dot)
 {
     constexpr int L = 16 * R2, C = 256 / R2, P2 = C / 16;   // P2: (l, c) pairs per thread
     __shared__ float2 tw[L];
@@ -653,6 +675,8 @@ __global__ __launch_bounds__(TPB) void k_fft_cols(float2 *spec, const float2 *__
         // symbol of the x1 pass: k1 = c + 16 d, k2 = plane, k3 = c0 + l
         const float k2 = (float)(pl < (n2 >> 1) ? pl : pl - n2);
         const float k3 = (float)(c0 + l);
+        const bool edge = c0 + l == 0 || c0 + l == nh - 1;
+        double acc = 0.0;
 #pragma unroll
         for (int u = 0; u < P2; ++u) {
             const int c = r + (256 / C) * u;
@@ -666,10 +690,12 @@ __global__ __launch_bounds__(TPB) void k_fft_cols(float2 *spec, const float2 *__
                 else if (kind == 1) sym = 1.0f / (beta * fmaxf(ksq, 1.0f));
                 else sym = 1.0f;
                 sym *= scale;
+                if (DOT) acc += dot_term(v[u * R2 + d], sym, edge);   // zero past the last column
                 v[u * R2 + d].x *= sym;
                 v[u * R2 + d].y *= sym;
             }
         }
+        if (DOT) dot_store(acc, dot);
         __syncthreads();                                      // exchange buffer free again
     } else {
         // inverse only: c layout loads X[c + 16 d]
@@ -745,10 +771,11 @@ template <int E, bool INV, int S = 1> __device__ __forceinline__ void cross_dft(
     bfly(INV ? 2 : 1);
 }
 
-template <int E, int MODE, bool PR>
+template <int E, int MODE, bool PR, bool DOT>
 __global__ __launch_bounds__(NTX, 4) void k_fft_colsx(float2 *spec, const float2 *__restrict__ twL,
                                                       int nh, size_t plane_stride, size_t rs, size_t spec_cs, int kind,
-                                                      float beta, float scale, int n1, int n2, ColSrc from)
+                                                      float beta, float scale, int n1, int n2, ColSrc from,
+                                                      double *__restrict__ dot)
 {
     constexpr int R2 = 16 * E, L = 16 * R2, C = NTX / R2, LOGC = C == 16 ? 4 : 3, LOGE = E == 2 ? 1 : 2;
     constexpr int CS = R2 * C + 16;   // exchange pitch per c
@@ -796,6 +823,8 @@ __global__ __launch_bounds__(NTX, 4) void k_fft_colsx(float2 *spec, const float2
         // symbol of the x1 pass: k1 = c + 16 d' + 256 m, k2 = plane, k3 = c0 + lc
         const float k2 = (float)(pl < (n2 >> 1) ? pl : pl - n2);
         const float k3 = (float)(c0 + lc);
+        const bool edge = c0 + lc == 0 || c0 + lc == nh - 1;
+        double acc = 0.0;
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             const int q = c + 16 * k + 256 * m;
@@ -806,9 +835,11 @@ __global__ __launch_bounds__(NTX, 4) void k_fft_colsx(float2 *spec, const float2
             else if (kind == 1) sym = 1.0f / (beta * fmaxf(ksq, 1.0f));
             else sym = 1.0f;
             sym *= scale;
+            if (DOT) acc += dot_term(v[k], sym, edge);        // zero past the last column
             v[k].x *= sym;
             v[k].y *= sym;
         }
+        if (DOT) dot_store(acc, dot);
         __syncthreads();                                      // exchange buffer free again
     } else {
 #pragma unroll
@@ -1153,23 +1184,26 @@ int cols_width(int L) { return L <= 256 ? 4096 / L : 8192 / L; }
 // from: pruned source (NULL: the spectrum itself, in full)
 template <int MODE>
 void launch_cols(int L, dim3 grid, float2 *spec, const float2 *tw, int nh, size_t plane_stride, size_t rs,
-                 size_t spec_cs, int kind, float beta, float scale, int n1, int n2, const ColSrc *from, hipStream_t s)
+                 size_t spec_cs, int kind, float beta, float scale, int n1, int n2, const ColSrc *from, double *dot,
+                 hipStream_t s)
 {
     auto go = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, spec, tw, nh, plane_stride, rs, spec_cs, kind, beta,
-                           scale, n1, n2, from ? *from : ColSrc{});
+                           scale, n1, n2, from ? *from : ColSrc{}, dot);
     };
-    auto size = [&](auto pruned) {
-        constexpr bool PR = decltype(pruned)::value;
-        if (L == 1024) go(k_fft_colsx<4, MODE, PR>, NTX);
-        else if (L == 512) go(k_fft_colsx<2, MODE, PR>, NTX);
-        else if (L == 256) go(k_fft_cols<16, MODE, PR>, TPB);
-        else go(k_fft_cols<8, MODE, PR>, TPB);
+    auto size = [&](auto pruned, auto dotted) {
+        constexpr bool PR = decltype(pruned)::value, DOT = decltype(dotted)::value;
+        if (L == 1024) go(k_fft_colsx<4, MODE, PR, DOT>, NTX);
+        else if (L == 512) go(k_fft_colsx<2, MODE, PR, DOT>, NTX);
+        else if (L == 256) go(k_fft_cols<16, MODE, PR, DOT>, TPB);
+        else go(k_fft_cols<8, MODE, PR, DOT>, TPB);
     };
-    if constexpr (MODE != 0) {
-        if (from) return size(std::true_type{});
+    if constexpr (MODE == 0) {
+        if (dot) return size(std::false_type{}, std::true_type{});
+    } else {
+        if (from) return size(std::true_type{}, std::false_type{});
     }
-    size(std::false_type{});
+    size(std::false_type{}, std::false_type{});
 }
 
 bool rows_ok(int n3) { return n3 == 128 || n3 == 256 || n3 == 512 || n3 == 1024; }
@@ -1269,8 +1303,10 @@ void pass_x2(const FFTPlan &P, bool inv, int nc, size_t spec_cs, int kmax, const
     if (cols_ok(P.n2)) {
         const int C = cols_width(P.n2);
         const dim3 grid((kmax + C - 1) / C, P.n1, nc);
-        if (inv) launch_cols<2>(P.n2, grid, P.spec, P.tw2, kmax, ps, P.np, spec_cs, 2, 0.f, 1.f, P.n1, P.n2, from, s);
-        else launch_cols<1>(P.n2, grid, P.spec, P.tw2, kmax, ps, P.np, spec_cs, 2, 0.f, 1.f, P.n1, P.n2, nullptr, s);
+        if (inv) launch_cols<2>(P.n2, grid, P.spec, P.tw2, kmax, ps, P.np, spec_cs, 2, 0.f, 1.f, P.n1, P.n2, from,
+                                nullptr, s);
+        else launch_cols<1>(P.n2, grid, P.spec, P.tw2, kmax, ps, P.np, spec_cs, 2, 0.f, 1.f, P.n1, P.n2, nullptr,
+                            nullptr, s);
         return;
     }
     const ColGeom cg = col_geom(P.n2);
@@ -1287,18 +1323,18 @@ void pass_x2(const FFTPlan &P, bool inv, int nc, size_t spec_cs, int kmax, const
 
 // x1 pass over every x2 plane: mode 0 forward, symbol, inverse; 1 forward; 2
 // inverse.  kmax, from: the columns k3 < kmax of the planes that from keeps
-// (modes 1 and 2), read through it.
+// (modes 1 and 2), read through it; dot (mode 0, may be NULL): partials of <in, out>.
 void pass_x1(const FFTPlan &P, int mode, int kind, float beta, float scale, int nc, size_t spec_cs, int kmax,
-             const ColSrc *from, hipStream_t s)
+             const ColSrc *from, double *dot, hipStream_t s)
 {
     const int planes = from ? P.n2 - from->skip : P.n2;
     if (cols_ok(P.n1)) {
         const int C = cols_width(P.n1);
         const dim3 grid((kmax + C - 1) / C, planes, nc);
         const size_t rs = (size_t)P.n2 * P.np;
-        if (mode == 0) launch_cols<0>(P.n1, grid, P.spec, P.tw1, kmax, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, nullptr, s);
-        else if (mode == 1) launch_cols<1>(P.n1, grid, P.spec, P.tw1, kmax, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, from, s);
-        else launch_cols<2>(P.n1, grid, P.spec, P.tw1, kmax, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, from, s);
+        if (mode == 0) launch_cols<0>(P.n1, grid, P.spec, P.tw1, kmax, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, nullptr, dot, s);
+        else if (mode == 1) launch_cols<1>(P.n1, grid, P.spec, P.tw1, kmax, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, from, nullptr, s);
+        else launch_cols<2>(P.n1, grid, P.spec, P.tw1, kmax, P.np, rs, spec_cs, kind, beta, scale, P.n1, P.n2, from, nullptr, s);
         return;
     }
     const ColGeom cg = col_geom(P.n1);
@@ -1306,7 +1342,7 @@ void pass_x1(const FFTPlan &P, int mode, int kind, float beta, float scale, int 
     const dim3 grid((kmax + C1 - 1) / C1, planes, nc);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(TPB), cg.lds, s, P.spec, P.tw1, ilog2(P.n1), P.n1, P.n2, kmax, P.np,
-                           cg.logC, kind, beta, scale, spec_cs, mode, from ? *from : ColSrc{});
+                           cg.logC, kind, beta, scale, spec_cs, mode, from ? *from : ColSrc{}, dot);
     };
     if (from) go(k_fft_x1_mult<TPB, true>);
     else go(k_fft_x1_mult<TPB, false>);
@@ -1314,8 +1350,14 @@ void pass_x1(const FFTPlan &P, int mode, int kind, float beta, float scale, int 
 
 } // namespace
 
+int spectral_dot_blocks(const FFTPlan &P)
+{
+    const int C = cols_ok(P.n1) ? cols_width(P.n1) : 1 << col_geom(P.n1).logC;
+    return (P.nh + C - 1) / C * P.n2 * P.ncomp_max;
+}
+
 void spectral_apply(const FFTPlan &P, int kind, float beta, float beta_w, int ncomp, const float *in, float *out,
-                    const float *add, hipStream_t s)
+                    const float *add, hipStream_t s, double *dot)
 {
     if (beta_w != 0.f && ncomp == 3 && kind != 2) {
         // the three components are coupled per mode: forward transforms,
@@ -1343,13 +1385,13 @@ void spectral_apply(const FFTPlan &P, int kind, float beta, float beta_w, int nc
         const float *addc = add ? add + c0 * N : nullptr;
         if (planes_ok(P)) {
             launch_planes<false>(P, inc, nullptr, nullptr, nc, spec_cs, P.nh, P.n2, s);
-            pass_x1(P, 0, kind, beta, scale, nc, spec_cs, P.nh, nullptr, s);
+            pass_x1(P, 0, kind, beta, scale, nc, spec_cs, P.nh, nullptr, dot, s);
             launch_planes<true>(P, nullptr, outc, addc, nc, spec_cs, P.nh, P.n2, s);
             continue;
         }
         pass_r2c(P, inc, nc, logM, lognl3, lds3, spec_cs, s);
         pass_x2(P, false, nc, spec_cs, P.nh, nullptr, s);
-        pass_x1(P, 0, kind, beta, scale, nc, spec_cs, P.nh, nullptr, s);
+        pass_x1(P, 0, kind, beta, scale, nc, spec_cs, P.nh, nullptr, dot, s);
         pass_x2(P, true, nc, spec_cs, P.nh, nullptr, s);
         pass_c2r(P, outc, addc, nc, logM, lognl3, lds3, spec_cs, P.nh, s);
     }
@@ -1398,19 +1440,19 @@ void forward3(const FFTPlan &P, const PassGeom &G, int nc, const float *in, cons
         pass_x2(P, false, nc, G.spec_cs, k.kmax, nullptr, s);
     }
     if (k.m2 >= P.n2) {
-        pass_x1(P, 1, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, nullptr, s);
+        pass_x1(P, 1, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, nullptr, nullptr, s);
     } else {
         ColSrc c = whole(P, G, P.spec, P.np, (size_t)P.n2 * P.np);
         c.mp = k.m2;
         c.skip = P.n2 - (2 * k.m2 - 1);
-        pass_x1(P, 1, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, &c, s);
+        pass_x1(P, 1, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, &c, nullptr, s);
     }
 }
 
 // from: source of the x1 pass (NULL: this plan's spectrum, in full)
 void inverse3(const FFTPlan &P, const PassGeom &G, int nc, float *out, const Keep &k, const ColSrc *from, hipStream_t s)
 {
-    pass_x1(P, 2, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, from, s);
+    pass_x1(P, 2, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, from, nullptr, s);
     if (planes_ok(P)) {
         launch_planes<true>(P, nullptr, out, nullptr, nc, G.spec_cs, k.kmax, k.m2, s);
         return;

@@ -1,0 +1,38 @@
+"""<r, P r> of the inner CG as the transform's x1 pass forms it (Parseval over the
+half spectrum).  On a constant template the zero-velocity Hessian is L_0, and one
+inner step gives z = (<r, P r> / <P r, L_0 P r>) P r with L_0 P r = r: the
+denominator is summed over the nodes, so z / P r is the ratio of the two sums, 1
+but for rounding.  White noise fills every mode (a wrong weight on the planes k3 =
+0 or n3 / 2, or a column past the last one, moves the ratio by over 1e-3); three
+transforms of relative error <= 4 log2(N) eps enter, the first one squared."""
+import math
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+@pytest.mark.parametrize("shape", [(16, 16, 16), (64, 32, 128), (128, 16, 32), (256, 32, 16), (512, 16, 32),
+                                   (1024, 16, 16)])
+def test_parseval_sum_is_that_over_the_nodes(shape):
+    from paper_2209_08189_amd.claire import Registration
+    g = torch.Generator().manual_seed(sum(shape))
+    x = torch.randn((3,) + shape, generator=g).cuda()
+    flat = torch.full(shape, 0.5, device="cuda")
+    z = []
+    for kw in ({"precond": "h0", "precond_inner": 1}, {}):
+        r = Registration(shape, **kw)
+        r.set_images(flat, flat)
+        r.set_velocity(torch.zeros((3,) + shape, device="cuda"))
+        z.append(r.precond(x).double().cpu())
+        r.close()
+    ratio = float((z[0] * z[1]).sum() / (z[1] * z[1]).sum())
+    print("%s: ratio - 1 = %.2e" % (shape, ratio - 1))
+    assert abs(ratio - 1) <= 16 * 2.0 ** -24 * math.log2(shape[0] * shape[1] * shape[2])
