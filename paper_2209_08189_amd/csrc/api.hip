@@ -468,16 +468,26 @@ struct H0Level {
 // z = P r on one grid and the partials of <r, z>: their buffer and count.  With
 // uncoupled components they are formed in the transform's x1 pass (Parseval),
 // into scratch, which holds 3 N floats (one double per workgroup of that pass is
-// far less); coupled components (beta_w != 0) have no such pass.
+// far less); coupled components (beta_w != 0) have no such pass.  With H, r is
+// first replaced by r - sc[PCG_ALPHA] H, stored to rout: by the row pass as it
+// reads (12 fields moved against 15) where the transform has one that can.
 struct DotParts {
     const double *parts;
     int count;
 };
-DotParts precond_dot(cl_ctx *ctx, const FFTPlan &fft, size_t N, const float *r, float *z, float *scratch)
+DotParts precond_dot(cl_ctx *ctx, const FFTPlan &fft, size_t N, const float *r, float *z, float *scratch,
+                     const float *H = nullptr, const double *sc = nullptr, float *rout = nullptr)
 {
     double *dot = ctx->opt.beta_w == 0.0 ? (double *)scratch : nullptr;
+    const bool fused = H && dot && spectral_takes_update(fft);
+    const SpecUpdate upd{r, H, sc ? sc + PCG_ALPHA : nullptr, rout};
+    if (H && !fused) {
+        run(ctx, CL_K_VEC, [&] { launch_h0_residual(r, H, sc, rout, N, ctx->s); });
+        r = rout;
+    }
     run(ctx, CL_K_FFT, [&] {
-        spectral_apply(fft, 1, (float)ctx->opt.beta_v, (float)ctx->opt.beta_w, 3, r, z, nullptr, ctx->s, dot);
+        spectral_apply(fft, 1, (float)ctx->opt.beta_v, (float)ctx->opt.beta_w, 3, r, z, nullptr, ctx->s, dot,
+                       fused ? &upd : nullptr);
     });
     if (dot) return {dot, spectral_dot_blocks(fft)};
     const int nb = std::min(ctx->nparts, reduce_blocks(3 * N));
@@ -498,25 +508,21 @@ void h0_inner(cl_ctx *ctx, const H0Level &L, const float *r, float *z)
     const size_t N = L.N, n = 3 * N;
     double *sc = ctx->pscal + PCG_INNER;
     const int nb = std::min(ctx->nparts, reduce_blocks(n));
-    HIPCHK(hipMemcpyAsync(L.ir, r, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
-    DotParts d = precond_dot(ctx, *L.fft, N, L.ir, L.izi, L.ih);
-    HIPCHK(hipMemcpyAsync(L.ip, L.izi, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
-    HIPCHK(hipMemcpyAsync(L.iLp, L.ir, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
+    DotParts d = precond_dot(ctx, *L.fft, N, r, L.izi, L.ih);
     run(ctx, CL_K_VEC, [&] { launch_finalize(d.parts, d.count, L.hv, sc + PCG_RZ, ctx->s); });
     // z takes the step of an iteration in the pass that forms the next direction
     const int inner = ctx->opt.precond_inner;
     for (int it = 0; it < inner; ++it) {
         run(ctx, CL_K_VEC, [&] {
             if (it == 0)
-                launch_h0_apply(L.ip, L.iLp, L.G0, L.ih, N, ctx->partials, nb, ctx->s);
+                launch_h0_apply(L.ip, L.iLp, L.izi, r, L.G0, L.ih, N, ctx->partials, nb, ctx->s);
             else
                 launch_h0_direction_apply(z, it == 1, L.ip, L.iLp, L.izi, L.ir, L.G0, L.ih, sc, N, ctx->partials, nb,
                                           ctx->s);
             launch_finalize_alpha(ctx->partials, nb, L.hv, sc, ctx->s);
         });
         if (it == inner - 1) break;
-        run(ctx, CL_K_VEC, [&] { launch_h0_residual(L.ir, L.ih, sc, N, ctx->s); });
-        d = precond_dot(ctx, *L.fft, N, L.ir, L.izi, L.ih);
+        d = precond_dot(ctx, *L.fft, N, it == 0 ? r : L.ir, L.izi, L.ih, L.ih, sc, L.ir);
         run(ctx, CL_K_VEC, [&] { launch_finalize_beta(d.parts, d.count, L.hv, sc, ctx->s); });
     }
     run(ctx, CL_K_VEC, [&] { launch_h0_step(z, inner == 1, L.ip, sc, N, ctx->s); });

@@ -213,16 +213,14 @@ void launch_pcg_direction_lz(float *p, float *q, const float *z, const float *Lz
 // partials of p . out
 void launch_h0_direction_apply(float *x, bool first, float *p, float *q, const float *z, const float *r, const float *G,
                                float *out, const double *sc, size_t n, double *partials, int nblocks, hipStream_t s);
-// r -= alpha H (alpha = sc[PCG_ALPHA]) over 3 n values
-void launch_h0_residual(float *r, const float *H, const double *sc, size_t n, hipStream_t s);
+// out = r - alpha H (alpha = sc[PCG_ALPHA]) over 3 n values; out may be r
+void launch_h0_residual(const float *r, const float *H, const double *sc, float *out, size_t n, hipStream_t s);
 // x += alpha p (x = alpha p if first) over 3 n values
 void launch_h0_step(float *x, bool first, const float *p, const double *sc, size_t n, hipStream_t s);
-// y_c += scale * sums[c] (3 components of n values)
-void launch_add_sums3(float *y, const double *sums, double scale, size_t n, hipStream_t s);
-// out = Lp + (G . p) G per node (3 components n apart), per-block partials
-// of p . out in partials[0 .. nblocks)
-void launch_h0_apply(const float *p, const float *Lp, const float *G, float *out, size_t n, double *partials,
-                     int nblocks, hipStream_t s);
+// p = z, q = r, out = q + (G . p) G per node (3 components n apart), per-block
+// partials of p . out
+void launch_h0_apply(float *p, float *q, const float *z, const float *r, const float *G, float *out, size_t n,
+                     double *partials, int nblocks, hipStream_t s);
 // sc[PCG_PHP] = scale * (sum of the partials), then alpha and the curvature flag
 void launch_finalize_alpha(const double *partials, int nblocks, double scale, double *sc, hipStream_t s);
 // sc[PCG_RZNEW] = scale * (sum of the partials), then beta, and rz = rz_new
@@ -235,8 +233,6 @@ void launch_pcg_update3(float *x, float *r, const float *p, const float *Hp, dou
 // p = z + beta p, q = (r - mean r) + beta q (beta, means from sc)
 void launch_pcg_direction(float *p, float *q, const float *z, const float *r, const double *sc, size_t n,
                           hipStream_t s);
-void launch_pcg_update(float *x, float *r, const float *p, const float *Hp, float alpha, size_t n,
-                       double *partials, int nblocks, hipStream_t s);
 // y = a + alpha * b   (y may alias a)
 void launch_axpy(float *y, const float *a, const float *b, float alpha, size_t n, hipStream_t s);
 // sums_out[c] = sum of component c of a 3-field vector (device, FP64);
@@ -271,9 +267,19 @@ size_t fft_spec_bytes(int n1, int n2, int n3, int ncomp);
 // mode (regularisation Hessian L, its inverse, K); in may equal out.
 // dot (may be NULL; only for ncomp = ncomp_max components, not coupled): takes
 // spectral_dot_blocks(P) partials whose sum is <in, out>.
+// upd (may be NULL; not with coupled components, and only where
+// spectral_takes_update): the input is r - alpha H in place of in, also stored to
+// out (may be r).
+struct SpecUpdate {
+    const float *r;
+    const float *H;
+    const double *alpha;
+    float *out;
+};
 int spectral_dot_blocks(const FFTPlan &P);
+bool spectral_takes_update(const FFTPlan &P);
 void spectral_apply(const FFTPlan &P, int kind, float beta, float beta_w, int ncomp, const float *in, float *out,
-                    const float *add, hipStream_t s, double *dot = nullptr);
+                    const float *add, hipStream_t s, double *dot = nullptr, const SpecUpdate *upd = nullptr);
 // out (grid B) = spectral resampling of in (grid A): modes with |k_d| <
 // min(n_a, n_b)/2 kept, others zero, scaled so band-limited fields are
 // reproduced; both plans' spectra are used as work space

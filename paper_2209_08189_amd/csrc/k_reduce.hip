@@ -42,19 +42,24 @@ __global__ __launch_bounds__(TPB) void k_count_nonfinite(const float *__restrict
 }
 
 // Sum of nb partials in a fixed order, valid in thread 0 of the one
-// workgroup that runs it: thread t adds the partials t, t + 256, ... (so a
-// wavefront reads consecutive values), then block_sum.  Every finalize below
+// workgroup that runs it: thread t adds the partials t, t + T, ... of T threads
+// (so a wavefront reads consecutive values), then block_sum.  Every finalize below
 // is a launch of one small workgroup between two dependent kernels, bound by
 // its latency: with a serial sum of 256 thread values it took 3.0 us at
 // nb = 192 and 5 us at nb = 2048.
 __device__ __forceinline__ double sum_partials(const double *__restrict__ partials, int nb)
 {
     double acc = 0.0;
-    for (int q = threadIdx.x; q < nb; q += TPB) acc += partials[q];
+    for (int q = threadIdx.x; q < nb; q += blockDim.x) acc += partials[q];
     return block_sum(acc);
 }
 
-__global__ __launch_bounds__(TPB) void k_finalize(const double *__restrict__ partials, int nb, double scale,
+// threads for nb partials of the sums that a transform's workgroups leave behind
+// (6912 at 256^3: 13.0 us with 256 threads, 5.5 us with 1024)
+constexpr int FIN = 1024;
+int finalize_threads(int nb) { return nb > 2048 ? FIN : TPB; }
+
+__global__ __launch_bounds__(FIN) void k_finalize(const double *__restrict__ partials, int nb, double scale,
                                                   double *__restrict__ out)
 {
     const double t = sum_partials(partials, nb);
@@ -139,22 +144,6 @@ __global__ __launch_bounds__(TPB) void k_minmax_final(const double *__restrict__
     }
 }
 
-__global__ __launch_bounds__(TPB) void k_pcg_update(float *__restrict__ x, float *__restrict__ r,
-                                                    const float *__restrict__ p, const float *__restrict__ Hp,
-                                                    float alpha, size_t n, double *__restrict__ partials)
-{
-    double acc = 0.0;
-    const size_t stride = (size_t)gridDim.x * TPB;
-    for (size_t q = (size_t)blockIdx.x * TPB + threadIdx.x; q < n; q += stride) {
-        x[q] = fmaf(alpha, p[q], x[q]);
-        const float rq = fmaf(-alpha, Hp[q], r[q]);
-        r[q] = rq;
-        acc += (double)rq * (double)rq;
-    }
-    acc = block_sum(acc);
-    if (threadIdx.x == 0) partials[blockIdx.x] = acc;
-}
-
 __global__ __launch_bounds__(TPB) void k_axpy(float *y, const float *a, const float *b, float alpha,
                                               size_t n)
 {
@@ -212,7 +201,7 @@ __global__ __launch_bounds__(TPB) void k_finalize_alpha(const double *__restrict
 }
 
 // rz_new = scale * (sum of the partials), beta = rz_new / rz, then rz = rz_new
-__global__ __launch_bounds__(TPB) void k_finalize_beta(const double *__restrict__ partials, int nb, double scale,
+__global__ __launch_bounds__(FIN) void k_finalize_beta(const double *__restrict__ partials, int nb, double scale,
                                                        double *__restrict__ sc)
 {
     const double t = sum_partials(partials, nb);
@@ -282,31 +271,33 @@ __global__ __launch_bounds__(TPB) void k_pcg_direction_lz(float *__restrict__ p,
     }
 }
 
-// y_c += scale * sums[c] on the 3 components of n values
-__global__ __launch_bounds__(TPB) void k_add_sums3(float *__restrict__ y, const double *__restrict__ sums, double scale,
-                                                   size_t n)
-{
-    const size_t stride = (size_t)gridDim.x * TPB;
-    for (size_t e = (size_t)blockIdx.x * TPB + threadIdx.x; e < 3 * n; e += stride)
-        y[e] += (float)(scale * sums[e / n]);
-}
-
-// Zero-velocity Hessian: out = Lp + (G . p) G, and p . out per block
-__global__ __launch_bounds__(TPB) void k_h0_apply(const float *__restrict__ p, const float *__restrict__ Lp,
+// First inner step of the zero-velocity preconditioner: p = z, q = r (q = L_0 p),
+// out = q + (G . p) G, and p . out per block
+__global__ __launch_bounds__(TPB) void k_h0_apply(float *__restrict__ p, float *__restrict__ q,
+                                                  const float *__restrict__ z, const float *__restrict__ r,
                                                   const float *__restrict__ G, float *__restrict__ out, size_t n,
                                                   double *__restrict__ partials)
 {
     double acc = 0.0;
     const size_t stride = (size_t)gridDim.x * TPB;
-    for (size_t q = (size_t)blockIdx.x * TPB + threadIdx.x; q < n; q += stride) {
-        const float g0 = G[q], g1 = G[n + q], g2 = G[2 * n + q];
-        const float p0 = p[q], p1 = p[n + q], p2 = p[2 * n + q];
-        const float gp = g0 * p0 + g1 * p1 + g2 * p2;
-        const float o0 = fmaf(gp, g0, Lp[q]), o1 = fmaf(gp, g1, Lp[n + q]), o2 = fmaf(gp, g2, Lp[2 * n + q]);
-        out[q] = o0;
-        out[n + q] = o1;
-        out[2 * n + q] = o2;
-        acc += (double)p0 * o0 + (double)p1 * o1 + (double)p2 * o2;
+    for (size_t e = (size_t)blockIdx.x * TPB + threadIdx.x; e < n; e += stride) {
+        float pn[3], qn[3], g[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const size_t i = c * n + e;
+            pn[c] = z[i];
+            qn[c] = r[i];
+            g[c] = G[i];
+            p[i] = pn[c];
+            q[i] = qn[c];
+        }
+        const float gp = g[0] * pn[0] + g[1] * pn[1] + g[2] * pn[2];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float o = fmaf(gp, g[c], qn[c]);
+            out[c * n + e] = o;
+            acc += (double)pn[c] * o;
+        }
     }
     acc = block_sum(acc);
     if (threadIdx.x == 0) partials[blockIdx.x] = acc;
@@ -353,13 +344,14 @@ __global__ __launch_bounds__(TPB) void k_h0_direction_apply(float *__restrict__ 
     if (threadIdx.x == 0) partials[blockIdx.x] = acc;
 }
 
-// r -= alpha H over 3 n values (alpha = sc[PCG_ALPHA]; no reductions)
-__global__ __launch_bounds__(TPB) void k_h0_residual(float *__restrict__ r, const float *__restrict__ H,
-                                                     const double *__restrict__ sc, size_t n3)
+// out = r - alpha H over 3 n values (alpha = sc[PCG_ALPHA]; no reductions), where
+// the transform that follows does not form it while it reads
+__global__ __launch_bounds__(TPB) void k_h0_residual(const float *r, const float *__restrict__ H,
+                                                     const double *__restrict__ sc, float *out, size_t n3)
 {
     const float alpha = (float)sc[PCG_ALPHA];
     const size_t stride = (size_t)gridDim.x * TPB;
-    for (size_t e = (size_t)blockIdx.x * TPB + threadIdx.x; e < n3; e += stride) r[e] = fmaf(-alpha, H[e], r[e]);
+    for (size_t e = (size_t)blockIdx.x * TPB + threadIdx.x; e < n3; e += stride) out[e] = fmaf(-alpha, H[e], r[e]);
 }
 
 // x += alpha p, or x = alpha p, over 3 n values
@@ -461,13 +453,7 @@ void launch_minmax(const float *a, size_t n, double *partials, int nblocks, doub
 
 void launch_finalize(const double *partials, int nblocks, double scale, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(TPB), 0, s, partials, nblocks, scale, out);
-}
-
-void launch_pcg_update(float *x, float *r, const float *p, const float *Hp, float alpha, size_t n,
-                       double *partials, int nblocks, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_pcg_update, dim3(nblocks), dim3(TPB), 0, s, x, r, p, Hp, alpha, n, partials);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(finalize_threads(nblocks)), 0, s, partials, nblocks, scale, out);
 }
 
 void launch_axpy(float *y, const float *a, const float *b, float alpha, size_t n, hipStream_t s)
@@ -498,7 +484,7 @@ void launch_finalize_alpha(const double *partials, int nblocks, double scale, do
 
 void launch_finalize_beta(const double *partials, int nblocks, double scale, double *sc, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_finalize_beta, dim3(1), dim3(TPB), 0, s, partials, nblocks, scale, sc);
+    hipLaunchKernelGGL(k_finalize_beta, dim3(1), dim3(finalize_threads(nblocks)), 0, s, partials, nblocks, scale, sc);
 }
 
 void launch_pcg_update3(float *x, float *r, const float *p, const float *Hp, double *sc, size_t n, double *partials,
@@ -519,11 +505,6 @@ void launch_pcg_direction_lz(float *p, float *q, const float *z, const float *Lz
     hipLaunchKernelGGL(k_pcg_direction_lz, stream_grid(3 * n), dim3(TPB), 0, s, p, q, z, Lz, sc, 3 * n);
 }
 
-void launch_add_sums3(float *y, const double *sums, double scale, size_t n, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_add_sums3, stream_grid(3 * n), dim3(TPB), 0, s, y, sums, scale, n);
-}
-
 void launch_h0_direction_apply(float *x, bool first, float *p, float *q, const float *z, const float *r, const float *G,
                                float *out, const double *sc, size_t n, double *partials, int nblocks, hipStream_t s)
 {
@@ -535,9 +516,9 @@ void launch_h0_direction_apply(float *x, bool first, float *p, float *q, const f
                            partials);
 }
 
-void launch_h0_residual(float *r, const float *H, const double *sc, size_t n, hipStream_t s)
+void launch_h0_residual(const float *r, const float *H, const double *sc, float *out, size_t n, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_h0_residual, stream_grid(3 * n), dim3(TPB), 0, s, r, H, sc, 3 * n);
+    hipLaunchKernelGGL(k_h0_residual, stream_grid(3 * n), dim3(TPB), 0, s, r, H, sc, out, 3 * n);
 }
 
 void launch_h0_step(float *x, bool first, const float *p, const double *sc, size_t n, hipStream_t s)
@@ -546,10 +527,10 @@ void launch_h0_step(float *x, bool first, const float *p, const double *sc, size
     else hipLaunchKernelGGL(k_h0_step<false>, stream_grid(3 * n), dim3(TPB), 0, s, x, p, sc, 3 * n);
 }
 
-void launch_h0_apply(const float *p, const float *Lp, const float *G, float *out, size_t n, double *partials,
-                     int nblocks, hipStream_t s)
+void launch_h0_apply(float *p, float *q, const float *z, const float *r, const float *G, float *out, size_t n,
+                     double *partials, int nblocks, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_h0_apply, dim3(nblocks), dim3(TPB), 0, s, p, Lp, G, out, n, partials);
+    hipLaunchKernelGGL(k_h0_apply, dim3(nblocks), dim3(TPB), 0, s, p, q, z, r, G, out, n, partials);
 }
 
 void launch_pcg_direction(float *p, float *q, const float *z, const float *r, const double *sc, size_t n,
