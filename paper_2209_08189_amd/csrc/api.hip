@@ -354,7 +354,10 @@ double gradient(cl_ctx *ctx, double *J, double *mis_out, double *reg_out)
     const QuadArgs qa = quad_args(ctx);
     const size_t n3 = 3 * ctx->N;
     if (ctx->opt.beta_w == 0.0) {
-        run(ctx, CL_K_QUAD, [&] { launch_quadrature(ctx->g, ctx->dta, qa, ctx->Av, ctx->grad, ctx->s); });
+        run(ctx, CL_K_QUAD, [&] {
+            launch_quadrature_dot(ctx->g, ctx->dta, qa, ctx->Av, ctx->grad, nullptr, ctx->qparts, ctx->s);
+            launch_finalize(ctx->qparts, quadrature_blocks(ctx->g, qa), ctx->hv, ctx->dscal + SC_GN2, ctx->s);
+        });
     } else {
         // b into the PCG z vector (free outside PCG), L v + b into ctx->grad, and the
         // reduced gradient beta_v A v + K b in z, each term formed directly
@@ -363,9 +366,8 @@ double gradient(cl_ctx *ctx, double *J, double *mis_out, double *reg_out)
         spectral(ctx, 3, 3, ctx->pz, ctx->pz, nullptr);
         spectral_scalar(ctx, 0, 3, ctx->v, ctx->tmp3);
         run(ctx, CL_K_VEC, [&] { launch_axpy(ctx->pz, ctx->pz, ctx->tmp3, 1.0f, n3, ctx->s); });
+        dot_to(ctx, ctx->pz, ctx->pz, n3, ctx->hv, ctx->dscal + SC_GN2);
     }
-    const float *g = ctx->opt.beta_w != 0.0 ? ctx->pz : ctx->grad;
-    dot_to(ctx, g, g, n3, ctx->hv, ctx->dscal + SC_GN2);
     const double *sc = read_scalars(ctx, SC_GN2 + 1);
     if (mis_out) *mis_out = sc[SC_MIS];
     if (reg_out) *reg_out = sc[SC_REG];

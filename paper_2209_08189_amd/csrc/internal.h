@@ -177,7 +177,8 @@ void launch_inc_sources_march(const Grid &g, int dt_m, const QuadArgs &qa, const
                               int dt_q, void *q0, float *S, hipStream_t s);
 // out3 = addend3 (may be NULL) + sum_j w_j lam^j G^j
 void launch_quadrature(const Grid &g, int dt_lam, const QuadArgs &qa, const float *addend3, float *out3, hipStream_t s);
-// same, and per-block FP64 partial sums of dp . out3 in partials[0 .. quadrature_blocks(g, qa))
+// same, and per-block FP64 partial sums of dp . out3 (of out3 . out3 with dp = NULL) in
+// partials[0 .. quadrature_blocks(g, qa))
 int quadrature_blocks(const Grid &g, const QuadArgs &qa);
 // largest block count any quadrature launch on g uses (partials buffer size)
 int quadrature_blocks_max(const Grid &g);

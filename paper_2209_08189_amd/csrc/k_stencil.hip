@@ -103,8 +103,9 @@ template <typename T> __device__ __forceinline__ float4 ld4(const T *p)
 template <> __device__ __forceinline__ float4 ld4<float>(const float *p) { return *(const float4 *)p; }
 
 // out3 = add3 + sum_j w_j lam^j G^j, four nodes per thread (streaming).
-// With dp != NULL also the per-block FP64 partial sums of dp . out3 (from
-// the FP32 values stored), one per block in partials[blockIdx.x].
+// With partials also the per-block FP64 partial sums of dp . out3 (from the FP32
+// values stored; of out3 . out3 with dp = NULL), one per block in
+// partials[blockIdx.x].
 template <typename Tl>
 __global__ __launch_bounds__(TPB) void k_quadrature(Grid g, QuadArgs qa, const float *__restrict__ add,
                                                     float *__restrict__ out, const float *__restrict__ dp,
@@ -136,15 +137,19 @@ __global__ __launch_bounds__(TPB) void k_quadrature(Grid g, QuadArgs qa, const f
         *(float4 *)(out + p) = b0;
         *(float4 *)(out + N + p) = b1;
         *(float4 *)(out + 2 * N + p) = b2;
-        if (dp) {
-            const float4 d0 = *(const float4 *)(dp + p), d1 = *(const float4 *)(dp + N + p),
-                         d2 = *(const float4 *)(dp + 2 * N + p);
+        if (partials) {
+            float4 d0 = b0, d1 = b1, d2 = b2;
+            if (dp) {
+                d0 = *(const float4 *)(dp + p);
+                d1 = *(const float4 *)(dp + N + p);
+                d2 = *(const float4 *)(dp + 2 * N + p);
+            }
             acc = (double)d0.x * b0.x + (double)d0.y * b0.y + (double)d0.z * b0.z + (double)d0.w * b0.w;
             acc += (double)d1.x * b1.x + (double)d1.y * b1.y + (double)d1.z * b1.z + (double)d1.w * b1.w;
             acc += (double)d2.x * b2.x + (double)d2.y * b2.y + (double)d2.z * b2.z + (double)d2.w * b2.w;
         }
     }
-    if (dp) {
+    if (partials) {
         acc = block_sum(acc);
         if (threadIdx.x == 0) partials[blockIdx.x] = acc;
     }
@@ -181,10 +186,13 @@ __global__ __launch_bounds__(TPB) void k_quadrature_fd(Grid g, QuadArgs qa, cons
             out[p] = b0;
             out[N + p] = b1;
             out[2 * N + p] = b2;
-            if (dp) acc += (double)dp[p] * b0 + (double)dp[N + p] * b1 + (double)dp[2 * N + p] * b2;
+            if (partials) {
+                const float d0 = dp ? dp[p] : b0, d1 = dp ? dp[N + p] : b1, d2 = dp ? dp[2 * N + p] : b2;
+                acc += (double)d0 * b0 + (double)d1 * b1 + (double)d2 * b2;
+            }
         }
     }
-    if (dp) {
+    if (partials) {
         acc = block_sum(acc);
         if (threadIdx.x == 0) partials[blockIdx.x] = acc;
     }
@@ -242,7 +250,8 @@ __device__ __forceinline__ float fd8_lds(const float *c, int st, float ih)   // 
 }
 
 // MODE 0: out3 = add + sum_t w_t lam^t grad_h m^t (NL = qa.count levels),
-//         optional FP64 partials of dp . out3 per block.
+//         optional FP64 partials of dp . out3 per block (of out3 . out3 with
+//         dp = NULL: a pass of its own for them takes 58 us at 256^3).
 // MODE 1: out1 = scale * (-vt . grad_h m^0) (NL = 1).
 // MODE 2: the incremental sources of every level at once, s^t = -vt .
 //         grad_h m^t: out1 = scale * s^0, out3[(t - 1) N ..] = s^t, t >= 1.
@@ -389,8 +398,15 @@ __global__ __launch_bounds__(TPB_M) void k_fd_march(Grid g, MarchGeom mg, QuadAr
             at(out3, p) = b0;
             at(out3 + N, p) = b1;
             at(out3 + 2 * (size_t)N, p) = b2;
-            if (dp)
-                acc += (double)at(dp, p) * b0 + (double)at(dp + N, p) * b1 + (double)at(dp + 2 * (size_t)N, p) * b2;
+            if (partials) {
+                float f0 = b0, f1 = b1, f2 = b2;
+                if (dp) {
+                    f0 = at(dp, p);
+                    f1 = at(dp + N, p);
+                    f2 = at(dp + 2 * (size_t)N, p);
+                }
+                acc += (double)f0 * b0 + (double)f1 * b1 + (double)f2 * b2;
+            }
         } else {
             stf(&at(out1, p), scale * -(e0 * b0 + e1 * b1 + e2 * b2));
         }
@@ -399,7 +415,7 @@ __global__ __launch_bounds__(TPB_M) void k_fd_march(Grid g, MarchGeom mg, QuadAr
 #pragma unroll
             for (int s = 0; s < 8; ++s) ring[t][s] = ring[t][s + 1];
     }
-    if (MODE == 0 && dp) {
+    if (MODE == 0 && partials) {
         acc = block_sum(acc);
         if (threadIdx.x == 0) partials[blockIdx.x] = acc;
     }
