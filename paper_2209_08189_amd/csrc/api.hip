@@ -613,9 +613,8 @@ int pcg(cl_ctx *ctx, int max_pcg, double eta, int forced, int *iters)
         HIPCHK(hipMemcpyAsync(pAp, ctx->ilz, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
     } else {
         run(ctx, CL_K_VEC, [&] {
-            launch_fill_f32(pAp, 0.0f, n, ctx->s);
             launch_comp_sums3(ctx->pr, ctx->N, ctx->partials, ctx->nparts / 3, sc + PCG_SUMR, ctx->s);
-            launch_mean_free_axpy(pAp, ctx->pr, sc + PCG_SUMR, 0.0f, ctx->N, ctx->s);
+            launch_mean_free(pAp, ctx->pr, sc + PCG_SUMR, ctx->N, ctx->s);
         });
     }
     const int limit = forced >= 0 ? forced : max_pcg;
