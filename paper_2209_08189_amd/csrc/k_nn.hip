@@ -149,11 +149,15 @@ __device__ __forceinline__ void store4(float *o, f4 v, int wide)
 // straight to LDS with three or four workgroups per CU and no prefetch: 65 and
 // 167 us; three workgroups per CU with the prefetch: 17-60 spilled registers,
 // 67 and 195 us.
+// IN2: in holds the first two of 16 channels, the others are zero (the network's
+// two images; vs = 2): they are filled in as the halo is staged, so the first
+// layer reads 4 bytes a voxel instead of 32.  128^3: 55 -> 54 us (bound by
+// its LDS reads), and the pass that packs the images 19 -> 7.6 us.
 // Off: unsigned where a brick's halo spans less than 4 GiB of the input (each
 // access is then a wave-uniform base plus a 32-bit offset), else size_t.
 __device__ const u4 conv_zero = {0u, 0u, 0u, 0u};
 
-template <int MT, int NTS, typename To, typename Off, bool MASK>
+template <int MT, int NTS, typename To, typename Off, bool MASK, bool IN2>
 __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restrict__ in, const u4 *__restrict__ wp,
                                                   const float *__restrict__ bias, To *__restrict__ out,
                                                   const unsigned short *__restrict__ mask, NNLayout li, NNLayout lo,
@@ -188,7 +192,7 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
     for (int ch = 0; ch < NCH; ++ch) {
         const int q = ch * TPB + tid, v = q >> 1, xt = v % XS, r = v / XS;
         const int yt = r % YS, zt = r / YS;
-        rel[ch] = ((((Off)zt * H + yt) * W + xt) * li.vs + (q & 1) * 8) * 2;
+        rel[ch] = ((((Off)zt * H + yt) * W + xt) * li.vs + (IN2 ? 0 : (q & 1) * 8)) * 2;
         const unsigned e = (xt == 0) | (xt == XS - 1) << 1 | (yt == 0) << 2 | (yt == YS - 1) << 3 | (zt == 0) << 4 |
                            (zt == ZS - 1) << 5 | (q >= NQ) << 6;
         edge[ch >> 2] |= e << (8 * (ch & 3));
@@ -226,8 +230,13 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
             }
         }
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch)
-            st[ch] = *(const u4 *)((ok >> ch) & 1 ? org + rel[ch] : (const char *)&conv_zero);
+        for (int ch = 0; ch < NCH; ++ch) {
+            if constexpr (IN2)   // the other half's channels are zero
+                st[ch] = u4{*(const unsigned *)((ok >> ch) & ~tid & 1 ? org + rel[ch] : (const char *)&conv_zero), 0u, 0u,
+                            0u};
+            else
+                st[ch] = *(const u4 *)((ok >> ch) & 1 ? org + rel[ch] : (const char *)&conv_zero);
+        }
     };
     f4 acc[MT][2][NTS];
     u4 bw[NTP][NTS];
@@ -845,6 +854,15 @@ __global__ __launch_bounds__(TPB) void k_pack_input(const float *__restrict__ a,
     out[2 * p + 1] = u4{0u, 0u, 0u, 0u};
 }
 
+// the same as two channels per voxel
+__global__ __launch_bounds__(TPB) void k_pack_two(const float *__restrict__ a, const float *__restrict__ b,
+                                                  unsigned *__restrict__ out, size_t P)
+{
+    const size_t p = (size_t)blockIdx.x * TPB + threadIdx.x;
+    if (p >= P) return;
+    out[p] = (unsigned)f2bf(a[p]) | ((unsigned)f2bf(b[p]) << 16);
+}
+
 inline unsigned nblk(size_t n) { return (unsigned)((n + TPB - 1) / TPB); }
 
 } // namespace
@@ -856,7 +874,7 @@ void nn_pack_weights(const float *w, unsigned short *out, int Ci, int Co, int fl
     hipLaunchKernelGGL(k_pack_w, dim3(nblk(nn_packed_weight_elems(Ci, Co))), dim3(TPB), 0, s, w, out, Ci, Co, flip);
 }
 
-template <int MT, int NTS, typename To, typename Off = unsigned>
+template <int MT, int NTS, typename To, typename Off = unsigned, bool IN2 = false>
 static void conv3_launch(const unsigned short *in, const void *wp, const float *bias, To *out, const unsigned short *mask, NNLayout li, NNLayout lo, int D, int H, int W,
                          int Ci, int NT, int act, float slope, hipStream_t s)
 {
@@ -869,31 +887,31 @@ static void conv3_launch(const unsigned short *in, const void *wp, const float *
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(TPB), 0, s, in, (const u4 *)wp, bias, out, mask, li, lo, D, H, W,
                            Ci, act, slope, nbx, nby, ntile, NT, wide);
     };
-    if constexpr (sizeof(To) == 2) {
-        if (mask) return go(k_conv3<MT, NTS, To, Off, true>);
+    if constexpr (sizeof(To) == 2 && !IN2) {
+        if (mask) return go(k_conv3<MT, NTS, To, Off, true, false>);
     }
-    go(k_conv3<MT, NTS, To, Off, false>);
+    go(k_conv3<MT, NTS, To, Off, false, IN2>);
 }
 
 // The largest brick and output split that still give two workgroups per CU;
 // below that, the smallest (the halo of a brick is staged once per output
 // group, so fewer groups where the bricks alone fill the chip).
-template <typename To>
+template <typename To, bool IN2 = false>
 static void conv3_dispatch(const unsigned short *in, const void *wp, const float *bias, To *out, const unsigned short *mask, NNLayout li, NNLayout lo, int D, int H, int W,
                            int Ci, int Co, int act, float slope, hipStream_t s)
 {
     const int NT = Co / 16;
     auto tiles = [&](int mt, int nts) { return ((W + 15) / 16) * ((H + 7) / 8) * ((D + mt - 1) / mt) * (NT / nts); };
     if ((6.0 * H + 10.0) * W * li.vs * 2.0 >= 4294967296.0)
-        conv3_launch<1, 1, To, size_t>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
-    else if (NT % 2 == 0 && tiles(2, 2) >= 512)
+        conv3_launch<1, 1, To, size_t, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
+    else if (!IN2 && NT % 2 == 0 && tiles(2, 2) >= 512)
         conv3_launch<2, 2, To>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
     else if (tiles(4, 1) >= 512)
-        conv3_launch<4, 1, To>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<4, 1, To, unsigned, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
     else if (tiles(2, 1) >= 512)
-        conv3_launch<2, 1, To>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<2, 1, To, unsigned, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
     else
-        conv3_launch<1, 1, To>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
+        conv3_launch<1, 1, To, unsigned, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
 }
 
 void nn_conv3(const unsigned short *in, const void *wp, const float *bias, void *out, int out_f32,
@@ -901,6 +919,12 @@ void nn_conv3(const unsigned short *in, const void *wp, const float *bias, void 
 {
     if (out_f32) conv3_dispatch(in, wp, bias, (float *)out, mask, li, lo, D, H, W, Ci, Co, act, slope, s);
     else conv3_dispatch(in, wp, bias, (unsigned short *)out, mask, li, lo, D, H, W, Ci, Co, act, slope, s);
+}
+
+void nn_conv3_two(const unsigned short *in, const void *wp, const float *bias, unsigned short *out, NNLayout lo, int D,
+                  int H, int W, int Co, int act, float slope, hipStream_t s)
+{
+    conv3_dispatch<unsigned short, true>(in, wp, bias, out, nullptr, NNLayout{2, 0}, lo, D, H, W, 16, Co, act, slope, s);
 }
 
 // weight-gradient work split: the (input chunk, output tile) pairs times runs
@@ -995,6 +1019,11 @@ void nn_adam(float *p, const float *g, float *m, float *v, size_t n, float lr, f
 void nn_pack_input(const float *a, const float *b, unsigned short *out, size_t P, hipStream_t s)
 {
     hipLaunchKernelGGL(k_pack_input, dim3(nblk(P)), dim3(TPB), 0, s, a, b, (u4 *)out, P);
+}
+
+void nn_pack_two(const float *a, const float *b, unsigned short *out, size_t P, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_pack_two, dim3(nblk(P)), dim3(TPB), 0, s, a, b, (unsigned *)out, P);
 }
 
 } // namespace clh

@@ -173,12 +173,21 @@ void pack_all(cl_net *net)
     }
 }
 
-void forward(cl_net *net, const float *m0, const float *m1)
+// keep: a backward follows (the weight gradient of the first layer reads its
+// input with all 16 channels)
+void forward(cl_net *net, const float *m0, const float *m1, bool keep)
 {
     hipStream_t s = net->s;
     auto &C = net->conv;
-    nn_pack_input(m0, m1, net->x0.p, vox(net, 0), s);
-    conv_fwd(net, C[0], net->x0, net->a1);
+    if (keep) {
+        nn_pack_input(m0, m1, net->x0.p, vox(net, 0), s);
+        conv_fwd(net, C[0], net->x0, net->a1);
+    } else {
+        const int d = net->dims[0];
+        nn_pack_two(m0, m1, net->x0.p, vox(net, 0), s);
+        nn_conv3_two(net->x0.p, C[0].wpf, net->param + C[0].bo, net->a1.p, nn_chunked(vox(net, 0)), d, d, d, C[0].Co, 1,
+                     net->opt.slope, s);
+    }
     conv_fwd(net, C[1], net->a1, net->e1);
     pool(net, net->e1, net->p1);
     conv_fwd(net, C[2], net->p1, net->a2);
@@ -414,7 +423,7 @@ int cl_net_forward(cl_net *net, const float *m0, const float *m1, float *v_out)
 {
     if (!net || !m0 || !m1 || !v_out) return CL_ERR_ARG;
     try {
-        forward(net, m0, m1);
+        forward(net, m0, m1, false);
         NCHK(hipMemcpyAsync(v_out, net->vout, 3 * vox(net, 0) * sizeof(float), hipMemcpyDeviceToDevice, net->s));
     } catch (const NFail &f) { return f.code; }
     return CL_OK;
@@ -425,7 +434,7 @@ int cl_net_loss_grad(cl_net *net, const float *m0, const float *m1, const float 
 {
     if (!net || !m0 || !m1 || !v_label) return CL_ERR_ARG;
     try {
-        forward(net, m0, m1);
+        forward(net, m0, m1, true);
         const double L = loss_and_grad(net, v_label);
         backward(net);
         if (grad_out)
@@ -444,7 +453,7 @@ int cl_net_train_step(cl_net *net, const float *m0, const float *m1, const float
         double Ls = 0.0;
         NCHK(hipMemsetAsync(net->gacc, 0, net->nparam * sizeof(float), net->s));
         for (int b = 0; b < batch; ++b) {
-            forward(net, m0 + (size_t)b * P, m1 + (size_t)b * P);
+            forward(net, m0 + (size_t)b * P, m1 + (size_t)b * P, true);
             Ls += loss_and_grad(net, v_label + (size_t)b * 3 * P);
             backward(net);
             hipLaunchKernelGGL(k_axpy_f, dim3((unsigned)((net->nparam + 255) / 256)), dim3(256), 0, net->s, net->gacc,
@@ -549,7 +558,7 @@ int cl_warm_start(cl_ctx *ctx, cl_net *net, int *used, double *J_pred, double *J
         ctx_images_f32(ctx, net->full_buf, net->full_buf + N);
         spectral_resample(net->down->A, net->down->B, 1, net->full_buf, net->in0, net->s);
         spectral_resample(net->down->A, net->down->B, 1, net->full_buf + N, net->in1, net->s);
-        forward(net, net->in0, net->in1);
+        forward(net, net->in0, net->in1, false);
         spectral_resample(net->up->A, net->up->B, 3, net->vout, net->full_buf, net->s);
         NCHK(hipGetLastError());
     } catch (const NFail &f) {

@@ -22,6 +22,9 @@ void nn_pack_weights(const float *w, unsigned short *out, int Ci, int Co, int fl
 void nn_conv3(const unsigned short *in, const void *wp, const float *bias, void *out, int out_f32,
               const unsigned short *mask, NNLayout li, NNLayout lo, int D, int H, int W, int Ci, int Co, int act,
               float slope, hipStream_t s);
+// 16 -> Co, the input as two channels per voxel (nn_pack_two), the others zero
+void nn_conv3_two(const unsigned short *in, const void *wp, const float *bias, unsigned short *out, NNLayout lo, int D,
+                  int H, int W, int Co, int act, float slope, hipStream_t s);
 size_t nn_packed_weight_elems(int Ci, int Co);
 size_t nn_dw_workspace_floats(int D, int H, int W, int Ci, int Co);
 void nn_conv3_dw(const unsigned short *X, const unsigned short *dZ, float *partial, float *gw, float *gb, NNLayout lx,
@@ -43,5 +46,6 @@ void nn_mse(const float *pred, const float *label, size_t n, float inv, float *g
 void nn_adam(float *p, const float *g, float *m, float *v, size_t n, float lr, float b1, float b2, float eps, float c1,
              float c2, hipStream_t s);
 void nn_pack_input(const float *a, const float *b, unsigned short *out, size_t P, hipStream_t s);
+void nn_pack_two(const float *a, const float *b, unsigned short *out, size_t P, hipStream_t s);
 
 } // namespace clh
