@@ -14,8 +14,8 @@
 //   x2 C2C    inverse;
 //   x3 C2R    Hermitian merge, inverse FFT of length M, unpack to reals,
 //             optional fused add.
-// Lines of 128 ... 1024 points take register-resident passes (below); the
-// generic passes for shorter lines work on LDS tiles: a workgroup owns a
+// Columns of 64 ... 1024 and rows of 128 ... 1024 points take register-resident
+// passes (below); the generic passes for shorter lines work on LDS tiles: a workgroup owns a
 // tile of nl lines x L points (nl L <= 2048 complex, 16 KB), coalesced
 // batched loads into LDS, then Stockham stages of radix 8 (and one of
 // radix 2/4 for the remainder) with every group's R values in registers,
@@ -25,7 +25,8 @@
 // a pass lasts as long as one tile: radix 16 on tiles of 4096 values left half
 // the threads of a stage idle behind the other half's longer chains.  Planes of
 // at most 64 x 64 points do their x3 and x2 passes in one kernel (k_fft_plane),
-// three passes in all: a 64^3 vector 49 -> 29 us, 32^3 35 -> 18 us.
+// three passes in all: a 64^3 vector 49 -> 29 us (26 with the x1
+// pass in registers), 32^3 35 -> 18 us.
 #include "internal.h"
 
 #include <algorithm>
@@ -597,8 +598,12 @@ __global__ __launch_bounds__(NT) void k_fft_x1_mult(float2 *spec, const float2 *
 }
 
 // --- register-resident column passes for lines of L = 16 R2 points (R2 =
-// 8 or 16, i.e. L = 128 or 256; 512 and 1024 below) in tiles of C = 256 / R2
-// columns.  With
+// 4, 8 or 16, i.e. L = 64, 128 or 256; 512 and 1024 below) in tiles of C = 256 /
+// R2 columns.  On small grids a pass lasts as long as one tile: lines of 64 points
+// cross LDS twice here, eight times in the Stockham pass, 11.2 -> 8.3 us at 64^3
+// with the sum of <x, P x>, and an operation on 64 x 256 x 256 116 -> 100 us; lines
+// of 32 took 5.8 us either way and stay there
+// (tiles of 128 columns, of which a 32^3 row fills 17).  With
 // n = R2 a + b and k = c + 16 d,
 //   X[c + 16 d] = sum_b W_R2^{bd} W_L^{bc} sum_a x[R2 a + b] W_16^{ac},
 // so each thread holds 16 (or 2 x R2) values in registers: the length-16
@@ -1191,7 +1196,7 @@ void coupled3(const FFTPlan &P, int kind, float beta_v, float beta_w, const floa
 
 namespace {
 
-bool cols_ok(int L) { return L == 128 || L == 256 || L == 512 || L == 1024; }
+bool cols_ok(int L) { return L == 64 || L == 128 || L == 256 || L == 512 || L == 1024; }
 
 // columns per tile of the register-resident column passes
 int cols_width(int L) { return L <= 256 ? 4096 / L : 8192 / L; }
@@ -1211,7 +1216,8 @@ void launch_cols(int L, dim3 grid, float2 *spec, const float2 *tw, int nh, size_
         if (L == 1024) go(k_fft_colsx<4, MODE, PR, DOT>, NTX);
         else if (L == 512) go(k_fft_colsx<2, MODE, PR, DOT>, NTX);
         else if (L == 256) go(k_fft_cols<16, MODE, PR, DOT>, TPB);
-        else go(k_fft_cols<8, MODE, PR, DOT>, TPB);
+        else if (L == 128) go(k_fft_cols<8, MODE, PR, DOT>, TPB);
+        else go(k_fft_cols<4, MODE, PR, DOT>, TPB);
     };
     if constexpr (MODE == 0) {
         if (dot) return size(std::false_type{}, std::true_type{});
@@ -1299,7 +1305,7 @@ void launch_planes(const FFTPlan &P, const float *in, float *out, const float *a
                        kmax, m2);
 }
 
-// Stockham column passes (lines of 16 ... 64 points; 128 ... 1024 take the
+// Stockham column passes (lines of 16 and 32 points; longer ones take the
 // register-resident passes): a 256-thread tile of at most 2048 values holds 32
 // columns.
 struct ColGeom {

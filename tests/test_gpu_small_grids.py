@@ -57,7 +57,7 @@ def test_grouped_sources_equal_single_levels(shape, nt):
 # times the mean symbol: 1e-5 like the other operators.
 @pytest.mark.parametrize("kind", [0, 1, 2])
 @pytest.mark.parametrize("shape", [(16, 16, 16), (16, 64, 16), (256, 16, 64), (64, 64, 64), (32, 128, 64),
-                                   (64, 32, 128), (16, 32, 1024)])
+                                   (64, 32, 128), (16, 32, 1024), (64, 64, 128)])
 def test_spectral_operators_on_short_lines(shape, kind):
     from paper_2209_08189_amd.claire import Registration
     beta = 5e-4
@@ -76,7 +76,8 @@ def test_spectral_operators_on_short_lines(shape, kind):
 
 # resampling through pruned passes: up, down and mixed, every kind of line
 @pytest.mark.parametrize("ncomp", [1, 3])
-@pytest.mark.parametrize("a,b", [((16, 16, 16), (32, 64, 16)), ((64, 32, 128), (64, 32, 128)),
+@pytest.mark.parametrize("a,b", [((16, 16, 16), (32, 64, 16)), ((64, 64, 128), (128, 64, 16)),
+                                 ((128, 32, 64), (64, 64, 128)), ((64, 32, 128), (64, 32, 128)),
                                  ((128, 64, 32), (16, 256, 256)), ((16, 32, 1024), (512, 16, 64)),
                                  ((1024, 16, 32), (32, 64, 512)), ((32, 512, 64), (128, 1024, 16))])
 def test_resampling_keeps_the_common_modes(a, b, ncomp):
