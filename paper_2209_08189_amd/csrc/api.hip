@@ -761,8 +761,12 @@ int grad_levels(int n1, int n2, int n3, const cl_options &o, bool lean)
     return o.precond == CL_PRECOND_H0 ? 1 : 0;
 }
 
+// The size counts every level with nt > 4, where the sources used to be taken from
+// stored gradients: a cap selects (and refuses) the layouts that it did, and such a
+// context allocates less than its size.
 size_t workspace_bytes(int n1, int n2, int n3, const cl_options &o, bool lean)
 {
+    const int levels = !lean && o.nt > 4 ? o.nt + 1 : grad_levels(n1, n2, n3, o, lean);
     const size_t N = (size_t)n1 * n2 * n3;
     const size_t es = dtype_size(o.storage_state), ea = dtype_size(o.storage_adjoint);
     size_t b = 0;
@@ -770,7 +774,7 @@ size_t workspace_bytes(int n1, int n2, int n3, const cl_options &o, bool lean)
     b += (size_t)(o.nt + 1) * N * es;        // m^j
     b += (size_t)(o.nt + 1) * N * ea;        // lam^j / lam~^j
     b += 2 * N * ea;                         // q ping-pong
-    b += (size_t)grad_levels(n1, n2, n3, o, lean) * 3 * N * sizeof(float);   // grad_h m^j
+    b += (size_t)levels * 3 * N * sizeof(float);   // grad_h m^j
     b += (size_t)(lean ? 1 : o.nt) * N * sizeof(float);   // incremental sources s^j
     b += 3 * (N / 2048 + 1) * 8 * sizeof(int);  // tile stencil boxes
     b += 2 * N * sizeof(float);              // c, div v
