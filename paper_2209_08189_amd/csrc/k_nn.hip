@@ -13,6 +13,8 @@
 #include "internal.h"
 #include "nn.h"
 
+#include <algorithm>
+
 namespace clh {
 
 namespace {
@@ -927,6 +929,19 @@ void nn_conv3_two(const unsigned short *in, const void *wp, const float *bias, u
     conv3_dispatch<unsigned short, true>(in, wp, bias, out, nullptr, NNLayout{2, 0}, lo, D, H, W, 16, Co, act, slope, s);
 }
 
+// Runs of voxel tiles that the workspace has room for.  Its size is a result of the
+// ABI, and callers keep workspaces: it counts three resident workgroups per CU (one
+// with output tiles by four) and tiles of 16 x 4 x 2 voxels, whatever the kernel's
+// own split, which never takes more.
+static int dw_room(int D, int H, int W, int Ci, int Co)
+{
+    const int nt = Co / 16, ng = nt % 4 == 0 ? 4 : nt % 3 == 0 ? 3 : nt, per = (Ci / 16) * (nt / ng);
+    const int ntiles = ((W + 15) / 16) * ((H + 3) / 4) * ((D + 1) / 2);
+    const int want = std::max(1, std::min(ntiles, ((ng == 4 ? 1 : 3) * 256 + per - 1) / per));
+    const int tpc = (ntiles + want - 1) / want;
+    return (ntiles + tpc - 1) / tpc;
+}
+
 // weight-gradient work split: the (input chunk, output tile) pairs times runs
 // of tpc voxel tiles, at most the 512 workgroups that are resident at once (two
 // per CU): 171 runs of three pairs, 513 workgroups, took twice the time of 170
@@ -941,9 +956,7 @@ static DwPlan dw_plan(int D, int H, int W, int Ci, int Co)
     p.ntx = (W + 15) / 16;
     p.nty = (H + 3) / 4;
     p.ntiles = p.ntx * p.nty * ((D + 3) / 4);
-    int want = 512 / p.npair;
-    if (want > p.ntiles) want = p.ntiles;
-    if (want < 1) want = 1;
+    const int want = std::max(1, std::min({512 / p.npair, p.ntiles, dw_room(D, H, W, Ci, Co)}));
     p.tpc = (p.ntiles + want - 1) / want;
     p.nchunk = (p.ntiles + p.tpc - 1) / p.tpc;
     return p;
@@ -951,8 +964,7 @@ static DwPlan dw_plan(int D, int H, int W, int Ci, int Co)
 
 size_t nn_dw_workspace_floats(int D, int H, int W, int Ci, int Co)
 {
-    const DwPlan p = dw_plan(D, H, W, Ci, Co);
-    return (size_t)p.nchunk * (27 * (size_t)Ci * Co + Co);
+    return (size_t)dw_room(D, H, W, Ci, Co) * (27 * (size_t)Ci * Co + Co);
 }
 
 void nn_conv3_dw(const unsigned short *X, const unsigned short *dZ, float *partial, float *gw, float *gb, NNLayout lx,
