@@ -510,6 +510,10 @@ void h0_inner(cl_ctx *ctx, const H0Level &L, const float *r, float *z)
     const size_t N = L.N, n = 3 * N;
     double *sc = ctx->pscal + PCG_INNER;
     const int nb = std::min(ctx->nparts, reduce_blocks(n));
+    if ((uintptr_t)r & 7) {   // the transform reads its rows in pairs of values
+        HIPCHK(hipMemcpyAsync(L.ir, r, n * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
+        r = L.ir;
+    }
     DotParts d = precond_dot(ctx, *L.fft, N, r, L.izi, L.ih);
     run(ctx, CL_K_VEC, [&] { launch_finalize(d.parts, d.count, L.hv, sc + PCG_RZ, ctx->s); });
     // z takes the step of an iteration in the pass that forms the next direction

@@ -64,3 +64,19 @@ def test_residual_formed_by_the_row_pass(shape):
     print("%s: rel %.2e" % (shape, e))
     assert e < 1e-4
     assert torch.equal(xd.cpu(), torch.from_numpy(x))
+
+
+@pytest.mark.parametrize("shape", [(16, 16, 32), (16, 16, 128)])
+def test_residual_at_any_alignment(shape):
+    """A residual that starts at an odd element gives what an aligned copy gives."""
+    from paper_2209_08189_amd import synth
+    from paper_2209_08189_amd.claire import Registration
+    m = torch.from_numpy(np.float32(synth.trig_template(shape))).cuda()
+    n = 3 * shape[0] * shape[1] * shape[2]
+    buf = torch.randn(n + 1, generator=torch.Generator().manual_seed(3)).cuda()
+    x = buf[1:].view((3,) + shape)
+    r = Registration(shape, precond="h0", precond_inner=3)
+    r.set_images(m, m)
+    r.set_velocity(torch.zeros((3,) + shape, device="cuda"))
+    assert torch.equal(r.precond(x), r.precond(x.clone()))
+    r.close()
