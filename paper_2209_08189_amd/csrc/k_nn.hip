@@ -431,6 +431,9 @@ __device__ __forceinline__ bf8 frag_tr(unsigned a)
     return __builtin_bit_cast(bf8, f);
 }
 
+// DMA: X and dZ on 16-byte boundaries, which the loads straight to LDS need; else
+// through registers.
+template <bool DMA>
 __global__ __launch_bounds__(TPB, 2) void k_conv3_dw(const unsigned short *__restrict__ X,
                                                      const unsigned short *__restrict__ dZ, float *__restrict__ part,
                                                      NNLayout lx, NNLayout lz, int D, int H, int W, int Ci, int Co,
@@ -491,8 +494,14 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3_dw(const unsigned short *__res
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
             const char *src = (ch * TPB + tid < XQ ? xo : zo) + rel[ch];
-            __builtin_amdgcn_global_load_lds((const void *)((ok >> ch) & 1 ? src : (const char *)&conv_zero),
-                                             (lds_void *)(tile + buf * BUF + ch * TPB + wv * 64), 16, 0, 0);
+            const void *from = (ok >> ch) & 1 ? src : (const char *)&conv_zero;
+            if constexpr (DMA) {
+                __builtin_amdgcn_global_load_lds(from, (lds_void *)(tile + buf * BUF + ch * TPB + wv * 64), 16, 0, 0);
+            } else {
+                u4 v;
+                __builtin_memcpy(&v, from, sizeof(v));
+                tile[buf * BUF + ch * TPB + tid] = v;
+            }
         }
     };
     f4 acc[27], accb = f4{0.f, 0.f, 0.f, 0.f};
@@ -971,8 +980,12 @@ void nn_conv3_dw(const unsigned short *X, const unsigned short *dZ, float *parti
                  NNLayout lz, int D, int H, int W, int Ci, int Co, hipStream_t s)
 {
     const DwPlan p = dw_plan(D, H, W, Ci, Co);
-    hipLaunchKernelGGL(k_conv3_dw, dim3(p.nchunk * p.npair), dim3(TPB), 0, s, X, dZ, partial, lx, lz, D, H, W, Ci, Co,
-                       p.ntx, p.nty, p.ntiles, p.tpc);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(p.nchunk * p.npair), dim3(TPB), 0, s, X, dZ, partial, lx, lz, D, H, W, Ci, Co,
+                           p.ntx, p.nty, p.ntiles, p.tpc);
+    };
+    if ((((uintptr_t)X | (uintptr_t)dZ) & 15) == 0) go(k_conv3_dw<true>);
+    else go(k_conv3_dw<false>);
     const int nw = 27 * Ci * Co;
     hipLaunchKernelGGL(k_sum_partials, dim3((nw + Co + 63) / 64), dim3(64 * SUM_WAVES), 0, s, partial, p.nchunk, nw, Co,
                        gw, gb);
