@@ -147,3 +147,21 @@ def test_two_channel_input(n):
     want = 0.5 / v.numel() * float((v.double() ** 2).sum())
     assert want > 0
     assert abs(loss - want) <= 2 * v.numel() * 2.0 ** -53 * want
+
+
+def test_label_at_any_element():
+    """The loss and the gradient of a label that starts at an odd element are those of
+    an aligned copy (the loss up to its order of summation in FP64)."""
+    from paper_2209_08189_amd.claire import Net
+    n = 32
+    g = torch.Generator().manual_seed(5)
+    net = Net(in_n=n)
+    net.set_params(torch.cat([0.1 * torch.randn(27 * ci * co + co, generator=g) for ci, co in LAYERS]
+                             + [0.3 * torch.randn(51, generator=g)]).cuda())
+    m0, m1 = (torch.rand((n, n, n), generator=g).cuda() for _ in range(2))
+    buf = torch.randn(3 * n ** 3 + 1, generator=g).cuda()
+    label = buf[1:].view(3, n, n, n)
+    a, ga = net.loss_grad(m0, m1, label)
+    b, gb = net.loss_grad(m0, m1, label.clone())
+    assert torch.equal(ga, gb)
+    assert abs(a - b) <= 2 * label.numel() * 2.0 ** -53 * b
