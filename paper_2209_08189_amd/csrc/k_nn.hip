@@ -576,15 +576,46 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3_dw(const unsigned short *__res
     if (do_bias && g == 0) dst[27 * (size_t)Ci * Co + ct * 16 + ln] = accb[0];
 }
 
+// Element (tap t, channels i, o) of a chunk's weight gradient as plain sums of
+// the products inside the grid.  k_conv3_dw stages zeros outside the grid, and
+// zero times a value that is not finite is NaN in taps that do not see it.
+struct DwOperands {
+    const unsigned short *X, *dZ;
+    NNLayout lx, lz;
+    int D, H, W, Ci, Co, ntx, nty, ntiles, tpc;
+};
+__device__ float dw_element(const DwOperands &a, int chunk, int t, int i, int o)
+{
+    const unsigned short *x = a.X + (size_t)(i >> 4) * a.lx.cs + (i & 15);
+    const unsigned short *dz = a.dZ + (size_t)(o >> 4) * a.lz.cs + (o & 15);
+    const int sx = t % 3 - 1, sy = t / 3 % 3 - 1, sz = t / 9 - 1, t1 = min(a.ntiles, (chunk + 1) * a.tpc);
+    double s = 0.0;
+    for (int tI = chunk * a.tpc; tI < t1; ++tI) {
+        const int x0 = tI % a.ntx * 16, y0 = tI / a.ntx % a.nty * 4, z0 = tI / (a.ntx * a.nty) * 4;
+        // the tiles are those of X along x, of dZ along y and z
+        for (int z = max(z0, -sz); z < min(z0 + 4, min(a.D, a.D - sz)); ++z)
+            for (int y = max(y0, -sy); y < min(y0 + 4, min(a.H, a.H - sy)); ++y) {
+                for (int v = max(x0, sx); v < min(x0 + 16, min(a.W, a.W + sx)); ++v)
+                    s += (double)bf2f(x[(((size_t)(z + sz) * a.H + y + sy) * a.W + v) * a.lx.vs]) *
+                         bf2f(dz[(((size_t)z * a.H + y) * a.W + v - sx) * a.lz.vs]);
+                if (isnan(s)) return NAN;
+            }
+    }
+    return (float)s;
+}
+
 // Fixed-order sum of the chunk partials: row c of partial holds nw weight
 // values then nb bias values (row stride nw + nb).  A workgroup owns 64
 // consecutive outputs; wave w of 16 sums the chunks c = w (mod 16) in order,
 // eight loads in flight, then the wave sums are added in order.  The 16 -> 16
 // layers have 27 KB rows and 512 chunks: few outputs, so the rows are split
-// over many waves (4 waves with one load in flight: 48 us).
+// over many waves (4 waves with one load in flight: 48 us).  A sum that is not
+// finite is taken again, with dw_element in place of the weight partials that are
+// not (masked operands in k_conv3_dw would take 5-38 % of its time).
 constexpr int SUM_WAVES = 16;
 __global__ __launch_bounds__(64 * SUM_WAVES) void k_sum_partials(const float *__restrict__ partial, int nchunk, int nw,
-                                                                 int nb, float *__restrict__ gw, float *__restrict__ gb)
+                                                                 int nb, float *__restrict__ gw, float *__restrict__ gb,
+                                                                 DwOperands a)
 {
     __shared__ float red[SUM_WAVES][64];
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -601,6 +632,13 @@ __global__ __launch_bounds__(64 * SUM_WAVES) void k_sum_partials(const float *__
             for (int u = 0; u < 8; ++u) s += v[u];
         }
         for (; c < nchunk; c += SUM_WAVES) s += partial[(size_t)c * rs + e];
+        if (!isfinite(s) && e < nw) {
+            s = 0.f;
+            for (c = w; c < nchunk; c += SUM_WAVES) {
+                const float v = partial[(size_t)c * rs + e];
+                s += isfinite(v) ? v : dw_element(a, c, e / (a.Ci * a.Co), e / a.Co % a.Ci, e % a.Co);
+            }
+        }
     }
     red[w][l] = s;
     __syncthreads();
@@ -994,7 +1032,7 @@ void nn_conv3_dw(const unsigned short *X, const unsigned short *dZ, float *parti
     else go(k_conv3_dw<false>);
     const int nw = 27 * Ci * Co;
     hipLaunchKernelGGL(k_sum_partials, dim3((nw + Co + 63) / 64), dim3(64 * SUM_WAVES), 0, s, partial, p.nchunk, nw, Co,
-                       gw, gb);
+                       gw, gb, DwOperands{X, dZ, lx, lz, D, H, W, Ci, Co, p.ntx, p.nty, p.ntiles, p.tpc});
 }
 
 void nn_pool2(const unsigned short *in, unsigned short *out, int D, int H, int W, hipStream_t s)
