@@ -549,31 +549,32 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3_dw(const unsigned short *__res
             for (int zi = 0; zi < 2; ++zi) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, bz[zi][1], accb, 0, 0, 0);
         }
     }
-    // sum over the wavefronts: 2 and 3 into 0 and 1, then 1 into 0
-    f4 *red = (f4 *)tile;                 // two regions of 28 x 64 values (28 KB each)
-#pragma unroll
-    for (int half = 2; half >= 1; half >>= 1) {
-        __syncthreads();
-        if (wv >= half && wv < 2 * half) {
-#pragma unroll
-            for (int t = 0; t < 27; ++t) red[((wv - half) * 28 + t) * 64 + l] = acc[t];
-            red[((wv - half) * 28 + 27) * 64 + l] = accb;
-        }
-        __syncthreads();
-        if (wv < half) {
-#pragma unroll
-            for (int t = 0; t < 27; ++t) acc[t] += red[(wv * 28 + t) * 64 + l];
-            accb += red[(wv * 28 + 27) * 64 + l];
-        }
-    }
-    if (wv != 0) return;
-    // D[m][n]: m = 4 g + j (input channel), n = ln (output channel)
+    // sum over the wavefronts, half of the 27 taps and the bias at a time: wavefront
+    // w adds and stores the sums w, w + 4, ... (one wavefront adding and storing all of
+    // them: 8.3 -> 7.6 us where a run is one tile)
+    f4 *red = (f4 *)tile;                 // 4 wavefronts x 14 x 64 values
     float *dst = part + (size_t)chunk * (27 * Ci * Co + Co);
 #pragma unroll
-    for (int t = 0; t < 27; ++t)
+    for (int h = 0; h < 28; h += 14) {
+        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) dst[((size_t)t * Ci + kc * 16 + 4 * g + j) * Co + ct * 16 + ln] = acc[t][j];
-    if (do_bias && g == 0) dst[27 * (size_t)Ci * Co + ct * 16 + ln] = accb[0];
+        for (int t = 0; t < 14; ++t) red[(wv * 14 + t) * 64 + l] = h + t < 27 ? acc[h + t < 27 ? h + t : 0] : accb;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int t = wv + 4 * u;
+            if (t >= 14) break;
+            const f4 *r = red + t * 64 + l;
+            const f4 v = (r[0] + r[2 * 14 * 64]) + (r[14 * 64] + r[3 * 14 * 64]);
+            // D[m][n]: m = 4 g + j (input channel), n = ln (output channel)
+            if (h + t < 27) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) dst[((size_t)(h + t) * Ci + kc * 16 + 4 * g + j) * Co + ct * 16 + ln] = v[j];
+            } else if (do_bias && g == 0) {
+                dst[27 * (size_t)Ci * Co + ct * 16 + ln] = v[0];
+            }
+        }
+    }
 }
 
 // Element (tap t, channels i, o) of a chunk's weight gradient as plain sums of
@@ -606,35 +607,38 @@ __device__ float dw_element(const DwOperands &a, int chunk, int t, int i, int o)
 
 // Fixed-order sum of the chunk partials: row c of partial holds nw weight
 // values then nb bias values (row stride nw + nb).  A workgroup owns 64
-// consecutive outputs; wave w of 16 sums the chunks c = w (mod 16) in order,
-// eight loads in flight, then the wave sums are added in order.  The 16 -> 16
-// layers have 27 KB rows and 512 chunks: few outputs, so the rows are split
-// over many waves (4 waves with one load in flight: 48 us).  A sum that is not
+// consecutive outputs; wave w of NW sums the chunks c = w (mod NW) in order,
+// eight loads in flight, then the wave sums are added in order.  16 waves
+// where there are more chunks than 4 waves take in one go, 4 else: the 16 -> 16
+// layers have 27 KB rows and 512 chunks, few outputs whose rows are split
+// over many waves (4 waves with one load in flight: 48 us), the wide layers of
+// small grids have up to 2.6 MB rows and a few chunks (128 -> 128 at 6^3, 4 chunks:
+// 16 waves 14 us, 4 waves 5 us).  A sum that is not
 // finite is taken again, with dw_element in place of the weight partials that are
 // not (masked operands in k_conv3_dw would take 5-38 % of its time).
-constexpr int SUM_WAVES = 16;
-__global__ __launch_bounds__(64 * SUM_WAVES) void k_sum_partials(const float *__restrict__ partial, int nchunk, int nw,
-                                                                 int nb, float *__restrict__ gw, float *__restrict__ gb,
-                                                                 DwOperands a)
+constexpr int SUM_LOADS = 8;
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_sum_partials(const float *__restrict__ partial, int nchunk, int nw, int nb,
+                                                          float *__restrict__ gw, float *__restrict__ gb, DwOperands a)
 {
-    __shared__ float red[SUM_WAVES][64];
+    __shared__ float red[NW][64];
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int e = blockIdx.x * 64 + l;
     const int rs = nw + nb;
     float s = 0.f;
     if (e < rs) {
-        int c = w;
-        for (; c + 7 * SUM_WAVES < nchunk; c += 8 * SUM_WAVES) {
-            float v[8];
+        for (int c = w; c < nchunk; c += SUM_LOADS * NW) {
+            float v[SUM_LOADS];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)(c + u * SUM_WAVES) * rs + e];
+            for (int u = 0; u < SUM_LOADS; ++u)
+                if (c + u * NW < nchunk) v[u] = partial[(size_t)(c + u * NW) * rs + e];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) s += v[u];
+            for (int u = 0; u < SUM_LOADS; ++u)
+                if (c + u * NW < nchunk) s += v[u];
         }
-        for (; c < nchunk; c += SUM_WAVES) s += partial[(size_t)c * rs + e];
         if (!isfinite(s) && e < nw) {
             s = 0.f;
-            for (c = w; c < nchunk; c += SUM_WAVES) {
+            for (int c = w; c < nchunk; c += NW) {
                 const float v = partial[(size_t)c * rs + e];
                 s += isfinite(v) ? v : dw_element(a, c, e / (a.Ci * a.Co), e / a.Co % a.Ci, e % a.Co);
             }
@@ -645,7 +649,7 @@ __global__ __launch_bounds__(64 * SUM_WAVES) void k_sum_partials(const float *__
     if (w == 0 && e < rs) {
         float t = red[0][l];
 #pragma unroll
-        for (int u = 1; u < SUM_WAVES; ++u) t += red[u][l];
+        for (int u = 1; u < NW; ++u) t += red[u][l];
         if (e < nw) gw[e] = t;
         else if (gb) gb[e - nw] = t;
     }
@@ -1031,8 +1035,12 @@ void nn_conv3_dw(const unsigned short *X, const unsigned short *dZ, float *parti
     if ((((uintptr_t)X | (uintptr_t)dZ) & 15) == 0) go(k_conv3_dw<true>);
     else go(k_conv3_dw<false>);
     const int nw = 27 * Ci * Co;
-    hipLaunchKernelGGL(k_sum_partials, dim3((nw + Co + 63) / 64), dim3(64 * SUM_WAVES), 0, s, partial, p.nchunk, nw, Co,
-                       gw, gb, DwOperands{X, dZ, lx, lz, D, H, W, Ci, Co, p.ntx, p.nty, p.ntiles, p.tpc});
+    auto sum = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, dim3((nw + Co + 63) / 64), dim3(64 * waves), 0, s, partial, p.nchunk, nw, Co, gw, gb,
+                           DwOperands{X, dZ, lx, lz, D, H, W, Ci, Co, p.ntx, p.nty, p.ntiles, p.tpc});
+    };
+    if (p.nchunk > 4 * SUM_LOADS) sum(k_sum_partials<16>, 16);
+    else sum(k_sum_partials<4>, 4);
 }
 
 void nn_pool2(const unsigned short *in, unsigned short *out, int D, int H, int W, hipStream_t s)
