@@ -952,22 +952,54 @@ static void conv3_launch(const unsigned short *in, const void *wp, const float *
     go(k_conv3<MT, NTS, To, Off, false, IN2>);
 }
 
-// The largest brick and output split that still give two workgroups per CU;
-// below that, the smallest (the halo of a brick is staged once per output
-// group, so fewer groups where the bricks alone fill the chip).
+// Brick depth and output tiles per workgroup (MT, NTS) by the time of their items:
+// rounds of 512 walkers, two per CU.  Times per item and 16-channel input chunk in
+// 0.1 us, fitted to 340 launches of ragged and whole sizes in each variant (one
+// MI355X): one walker per CU, two, and two in the rounds after the first.  A deep
+// brick reads less halo for its work, a flat one gives more items and less work past
+// the last plane.  On average this is 0.4 % off the best variant; the rule "the
+// largest brick with 512 items" was 4.6 % off: two rounds of flat bricks for one of
+// deeper ones (30^3 64 -> 64 22.6 -> 16.9 us), bricks of four planes for grids of
+// one (1 x 40 x 200 128 -> 192 66 -> 34 us).
+struct ConvBrick {
+    int mt, nts;
+    double alone, paired, later;
+    double time(int items) const
+    {
+        const int last = items % 512;
+        double t = last == 0 ? 0.0 : last <= 256 ? alone : alone + (paired - alone) * (last - 256) / 256.0;
+        if (items >= 512) t += paired + (items / 512 - 1) * later;
+        return t;
+    }
+};
+static ConvBrick conv3_brick(int D, int H, int W, int NT, bool two)
+{
+    constexpr ConvBrick bricks[] = {{2, 2, 31., 47., 48.}, {4, 1, 31., 50., 50.}, {2, 1, 19., 28., 31.}, {1, 1, 15., 18., 24.}};
+    ConvBrick best{};
+    double tbest = 0.0;
+    for (const ConvBrick &b : bricks) {
+        if (b.nts == 2 && (two || NT % 2)) continue;
+        const double t = b.time(((W + 15) / 16) * ((H + 7) / 8) * ((D + b.mt - 1) / b.mt) * (NT / b.nts));
+        if (best.mt && t >= tbest) continue;
+        best = b;
+        tbest = t;
+    }
+    return best;
+}
+
 template <typename To, bool IN2 = false>
 static void conv3_dispatch(const unsigned short *in, const void *wp, const float *bias, To *out, const unsigned short *mask, NNLayout li, NNLayout lo, int D, int H, int W,
                            int Ci, int Co, int act, float slope, hipStream_t s)
 {
     const int NT = Co / 16;
-    auto tiles = [&](int mt, int nts) { return ((W + 15) / 16) * ((H + 7) / 8) * ((D + mt - 1) / mt) * (NT / nts); };
+    const ConvBrick b = conv3_brick(D, H, W, NT, IN2);
     if ((6.0 * H + 10.0) * W * li.vs * 2.0 >= 4294967296.0)
         conv3_launch<1, 1, To, size_t, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
-    else if (!IN2 && NT % 2 == 0 && tiles(2, 2) >= 512)
+    else if (!IN2 && b.nts == 2)
         conv3_launch<2, 2, To>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
-    else if (tiles(4, 1) >= 512)
+    else if (b.mt == 4)
         conv3_launch<4, 1, To, unsigned, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
-    else if (tiles(2, 1) >= 512)
+    else if (b.mt == 2)
         conv3_launch<2, 1, To, unsigned, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
     else
         conv3_launch<1, 1, To, unsigned, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
