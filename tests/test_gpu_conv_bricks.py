@@ -14,11 +14,13 @@ def _gpu():
         pytest.skip("no GPU")
 
 
-# bricks of 2 x 2, 4 x 1, 2 x 1 and 1 x 1 (planes x output tiles) for the whole grid;
-# three planes take 1 x 1
+# bricks of 2 x 2, 4 x 1, 2 x 1 and 1 x 1 (planes x output tiles) of 8 rows, then 4 x 1,
+# 2 x 2, 2 x 1 and 1 x 1 of 4 rows for the whole grid; three planes take 1 x 1 of 8
 @pytest.mark.parametrize("f32,transpose", [(True, False), (False, False), (False, True)])
 @pytest.mark.parametrize("shape,ci,co", [((22, 50, 100), 32, 32), ((36, 70, 130), 16, 16), ((30, 30, 30), 64, 64),
-                                         ((5, 33, 90), 64, 64), ((17, 23, 30), 64, 64)])
+                                         ((5, 33, 90), 64, 64), ((17, 23, 30), 64, 64),
+                                         ((45, 17, 130), 16, 16), ((41, 9, 119), 32, 32), ((39, 25, 17), 64, 64),
+                                         ((49, 25, 35), 16, 16), ((44, 11, 17), 64, 64), ((41, 3, 18), 64, 64)])
 def test_planes_alone(shape, ci, co, f32, transpose):
     from paper_2209_08189_amd.claire import nn_conv3
     g = torch.Generator().manual_seed(sum(shape))
