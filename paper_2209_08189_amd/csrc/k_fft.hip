@@ -24,7 +24,7 @@
 // column-wise accesses are conflict-free.  Grids of such lines are small and
 // a pass lasts as long as one tile: radix 16 on tiles of 4096 values left half
 // the threads of a stage idle behind the other half's longer chains.  Planes of
-// at most 64 x 64 points do their x3 and x2 passes in one kernel (k_fft_plane),
+// at most 64 x 64 points, up to 2048 of them, do their x3 and x2 passes in one kernel (k_fft_plane),
 // three passes in all: a 64^3 vector 49 -> 29 us (26 with the x1
 // pass in registers), 32^3 35 -> 18 us.
 #include "internal.h"
@@ -1291,8 +1291,12 @@ void pass_c2r(const FFTPlan &P, float *out, const float *add, int nc, int logM, 
                        logM, lognl3, nrows, N, spec_cs, P.np, kmax);
 }
 
-// x3 and x2 passes of small planes in one kernel
-bool planes_ok(const FFTPlan &P) { return P.n2 <= 64 && P.n3 <= 64; }
+// x3 and x2 passes of small planes (of nc components) in one kernel, one workgroup a
+// plane.  With 3072 of them, 1024 planes of three components, the workgroups come in
+// rounds and the separate passes' full tiles take less: 1024 x 16 x 32 77 -> 60 us,
+// 1024 x 64 x 64 172 -> 148 us.  At 1536 the two are within 10 % of each other either
+// way, below one kernel takes 0.5-0.9 of the time.
+bool planes_ok(const FFTPlan &P, int nc) { return P.n2 <= 64 && P.n3 <= 64 && P.n1 * nc <= 2048; }
 
 template <bool INV>
 void launch_planes(const FFTPlan &P, const float *in, float *out, const float *add, int nc, size_t spec_cs, int kmax,
@@ -1384,7 +1388,8 @@ int spectral_dot_blocks(const FFTPlan &P)
     return (P.nh + C - 1) / C * P.n2 * P.ncomp_max;
 }
 
-bool spectral_takes_update(const FFTPlan &P) { return !planes_ok(P) && rows_fit(P); }
+// (the rows that can are longer than those of a plane)
+bool spectral_takes_update(const FFTPlan &P) { return rows_fit(P); }
 
 void spectral_apply(const FFTPlan &P, int kind, float beta, float beta_w, int ncomp, const float *in, float *out,
                     const float *add, hipStream_t s, double *dot, const SpecUpdate *upd)
@@ -1413,7 +1418,7 @@ void spectral_apply(const FFTPlan &P, int kind, float beta, float beta_w, int nc
         const float *inc = in + c0 * N;
         float *outc = out + c0 * N;
         const float *addc = add ? add + c0 * N : nullptr;
-        if (planes_ok(P)) {
+        if (planes_ok(P, nc)) {
             launch_planes<false>(P, inc, nullptr, nullptr, nc, spec_cs, P.nh, P.n2, s);
             pass_x1(P, 0, kind, beta, scale, nc, spec_cs, P.nh, nullptr, dot, s);
             launch_planes<true>(P, nullptr, outc, addc, nc, spec_cs, P.nh, P.n2, s);
@@ -1464,7 +1469,7 @@ ColSrc whole(const FFTPlan &P, const PassGeom &G, const float2 *src, size_t ps, 
 
 void forward3(const FFTPlan &P, const PassGeom &G, int nc, const float *in, const Keep &k, hipStream_t s)
 {
-    if (planes_ok(P)) {
+    if (planes_ok(P, nc)) {
         launch_planes<false>(P, in, nullptr, nullptr, nc, G.spec_cs, P.nh, P.n2, s);
     } else {
         pass_r2c(P, in, nc, G.logM, G.lognl3, G.lds3, G.spec_cs, nullptr, s);
@@ -1484,7 +1489,7 @@ void forward3(const FFTPlan &P, const PassGeom &G, int nc, const float *in, cons
 void inverse3(const FFTPlan &P, const PassGeom &G, int nc, float *out, const Keep &k, const ColSrc *from, hipStream_t s)
 {
     pass_x1(P, 2, 2, 0.f, 1.f, nc, G.spec_cs, k.kmax, from, nullptr, s);
-    if (planes_ok(P)) {
+    if (planes_ok(P, nc)) {
         launch_planes<true>(P, nullptr, out, nullptr, nc, G.spec_cs, k.kmax, k.m2, s);
         return;
     }
