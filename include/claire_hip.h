@@ -137,7 +137,9 @@ typedef struct {
 void cl_default_options(cl_options *opt);
 
 /* Device bytes cl_create would allocate for this grid and options (host-only query; with
- * workspace_cap_bytes = 0 it reports the full layout). */
+ * workspace_cap_bytes = 0 it reports the full layout).  An upper bound: with nt > 4 it counts the state
+ * gradients of every level, which the full layout stores on some grids only (cl_layout).  A cap is
+ * compared with this size; without one the layout is chosen by what it allocates and the free memory. */
 int cl_query_workspace(int n1, int n2, int n3, const cl_options *opt, unsigned long long *bytes);
 
 /* Create a context on the current HIP device; allocates all workspace. */
@@ -146,8 +148,7 @@ int cl_create(cl_ctx **out, int n1, int n2, int n3, const cl_options *opt);
 /* Memory layout of a context: 0 = full (every incremental source field is kept; the state gradients
  * grad_h m^j are stored once per velocity where a kernel reads them: all nt+1 levels, (nt+1) x 3 FP32
  * fields, on grids with n3 < 64 or n2 < 8, level 0 for CL_PRECOND_H0, none otherwise, since the marching
- * kernels take the stencil of m^j on the fly; cl_query_workspace and the choice of the layout count all
- * levels with nt > 4, an upper bound),
+ * kernels take the stencil of m^j on the fly),
  * 1 = lean (no stored gradients and one source field, computed level by level: slower).  Same results
  * up to FP32 rounding order.  Negative: error code (NULL context). */
 int cl_layout(const cl_ctx *ctx);

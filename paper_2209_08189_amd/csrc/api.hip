@@ -765,12 +765,10 @@ int grad_levels(int n1, int n2, int n3, const cl_options &o, bool lean)
     return o.precond == CL_PRECOND_H0 ? 1 : 0;
 }
 
-// The size counts every level with nt > 4, where the sources used to be taken from
-// stored gradients: a cap selects (and refuses) the layouts that it did, and such a
-// context allocates less than its size.
-size_t workspace_bytes(int n1, int n2, int n3, const cl_options &o, bool lean)
+// Bytes of a context that stores levels gradients (cl_create's allocations; tables,
+// partial sums and boxes at their largest).
+size_t context_bytes(int n1, int n2, int n3, const cl_options &o, bool lean, int levels)
 {
-    const int levels = !lean && o.nt > 4 ? o.nt + 1 : grad_levels(n1, n2, n3, o, lean);
     const size_t N = (size_t)n1 * n2 * n3;
     const size_t es = dtype_size(o.storage_state), ea = dtype_size(o.storage_adjoint);
     size_t b = 0;
@@ -794,6 +792,15 @@ size_t workspace_bytes(int n1, int n2, int n3, const cl_options &o, bool lean)
     b += 4 * 1025 * sizeof(float2) + 4096 * sizeof(double) + 256;   // FFT tables, reduction partials, scalars
     b += (std::max<size_t>((N / 4 + 255) / 256, 6 * (size_t)reduce_blocks(N)) + PCG_NSCAL) * sizeof(double);
     return b;
+}
+
+// The size that cl_query_workspace reports and caps are compared with.  It counts
+// every level with nt > 4, where the sources used to be taken from stored gradients:
+// a cap selects (and refuses) the layouts that it did, and such a context allocates
+// less than its size.
+size_t workspace_bytes(int n1, int n2, int n3, const cl_options &o, bool lean)
+{
+    return context_bytes(n1, n2, n3, o, lean, !lean && o.nt > 4 ? o.nt + 1 : grad_levels(n1, n2, n3, o, lean));
 }
 
 // J = det grad y at the current v: min and max, and the field (N floats,
@@ -1093,15 +1100,17 @@ int cl_create(cl_ctx **out, int n1, int n2, int n3, const cl_options *opt)
     int st = check_options(opt, nullptr);
     if (st) return st;
     if (!pow2_ok(n1) || !pow2_ok(n2) || !pow2_ok(n3)) return CL_ERR_SHAPE;
-    // layout: the full one when it fits the cap (or, without a cap, the free
-    // device memory), else the lean one; CL_ERR_OOM if neither fits the cap
-    const size_t full = workspace_bytes(n1, n2, n3, *opt, false);
-    size_t limit = opt->workspace_cap_bytes;
-    if (!limit) {
+    // layout: the full one when its size fits the cap or, without a cap, when what it
+    // allocates fits the free device memory, else the lean one; CL_ERR_OOM if neither
+    // fits the cap
+    bool lean = false;
+    if (opt->workspace_cap_bytes) {
+        lean = workspace_bytes(n1, n2, n3, *opt, false) > opt->workspace_cap_bytes;
+    } else {
         size_t fr = 0, tot = 0;
-        if (hipMemGetInfo(&fr, &tot) == hipSuccess) limit = fr - fr / 16;
+        if (hipMemGetInfo(&fr, &tot) == hipSuccess && fr)
+            lean = context_bytes(n1, n2, n3, *opt, false, grad_levels(n1, n2, n3, *opt, false)) > fr - fr / 16;
     }
-    const bool lean = limit && full > limit;
     if (lean && opt->precond != CL_PRECOND_SPECTRAL) return CL_ERR_UNSUPPORTED;
     if (opt->precond == CL_PRECOND_H0_2LEVEL && (n1 < 32 || n2 < 32 || n3 < 32)) return CL_ERR_SHAPE;
     if (lean && opt->workspace_cap_bytes && workspace_bytes(n1, n2, n3, *opt, true) > opt->workspace_cap_bytes)
