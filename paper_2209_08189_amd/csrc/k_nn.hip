@@ -1022,10 +1022,12 @@ static void conv3_dispatch(const unsigned short *in, const void *wp, const float
         else
             conv3_launch<1, 1, YR, To, unsigned, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
     };
-    if ((6.0 * H + 10.0) * voxel >= 4294967296.0)
-        return conv3_launch<1, 1, 8, To, size_t, IN2>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
-    if constexpr (!IN2)
+    // (the network's grids, the only ones of two channels, are far below 4 GiB)
+    if constexpr (!IN2) {
+        if ((6.0 * H + 10.0) * voxel >= 4294967296.0)
+            return conv3_launch<1, 1, 8, To, size_t>(in, wp, bias, out, mask, li, lo, D, H, W, Ci, NT, act, slope, s);
         if (b.rows == 4) return go(std::integral_constant<int, 4>{});
+    }
     go(std::integral_constant<int, 8>{});
 }
 
