@@ -238,10 +238,11 @@ __global__ __launch_bounds__(TPB) void k_fft_x3_c2r(const float2 *__restrict__ s
     // stage the half-spectrum rows (nh values each) at lds[k * P + r], k <= M
     // (row M of the tile doubles as the Nyquist slot; the tile has M + 1 rows).
     // nl * nh = TILE + nl <= TILE + TILE / 8 values (M >= 8), i.e. at most
-    // EPT + 2 per thread.
+    // EPT + EPT / 8 = EPT + 1 per thread, all of them in use at M = 8.
     const int totk = nl * nh;
     {
         constexpr int NB = EPT + EPT / 8;
+        static_assert(NB * TPB >= TILE + TILE / 8, "a thread's buffer holds its share of the widest tile");
         float2 buf[NB];
 #pragma unroll
         for (int it = 0; it < NB; ++it) {
@@ -470,7 +471,8 @@ __device__ __forceinline__ float2 src_row(const ColSrc &c, const float2 *__restr
 // the tile is base[q * rs + l], l < cw valid columns; NT threads.  A thread
 // keeps its column l and steps through the rows q0, q0 + NT / C, ...: the
 // row part of an address is wave-uniform (a scalar base), the thread's part a
-// 32-bit byte offset (below 1/16 of one component's half spectrum).
+// 32-bit byte offset of at most NT / C - 1 = 7 rows, below half of one component's
+// half spectrum (lines of 16 or 32 points: at most 138 MB, 32 x 1024 x 1024).
 template <int NT>
 __device__ __forceinline__ void load_cols(float2 *lds, const float2 *__restrict__ base, size_t rs, int logC, int logL,
                                           int cw, int P)

@@ -3,8 +3,10 @@
 // image pair (restricted to a coarser grid); the registration solve stays
 // the judge of its output.
 //
-// Activations are channels-last BF16 tensors [D][H][W][C] (C a multiple of
-// 16); arithmetic is FP32.  3x3x3 convolutions run on the matrix cores as an
+// Activations are BF16 tensors of C channels (a multiple of 16), by 16-channel
+// chunks [C / 16][D][H][W][16] inside the network and channels last, [D][H][W][C],
+// at the single-layer entry points (NNLayout); arithmetic is FP32.  3x3x3
+// convolutions run on the matrix cores as an
 // implicit GEMM with v_mfma_f32_16x16x32_bf16 (K = two taps x 16 input
 // channels, below).  Weights are packed once per update into fragment order, so
 // a fragment is one 16-byte load per lane.  The transpose needed by the

@@ -778,7 +778,8 @@ __global__ __launch_bounds__(tile_threads(SP), 8) void k_sl_tile(Grid g, const T
 // launches (predictor, boxes, one SL gather per component, corrector, boxes)
 // the intermediate fields made 33 field passes per direction, 560 us at 256^3;
 // in one kernel a direction takes 350 us, bound by the VALU and LDS issue of
-// the three gathers like an SL step.  Trilinear at 128^3: 56 -> 15 us.
+// the three gathers like an SL step.  Trilinear at 128^3: 56 -> 28 us for one
+// direction alone, 46 us for both.
 struct FeetArgs {
     float a[2];          // -dt, +dt
     float *d[2];         // feet out, interleaved
