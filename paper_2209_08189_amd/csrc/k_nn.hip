@@ -417,10 +417,10 @@ __global__ __launch_bounds__(TPB, 2) void k_conv3(const unsigned short *__restri
 // next tile is in flight while the current one is computed.
 // Wavefront w owns two rows of two planes and all 27 taps (108 accumulators):
 // 12 X fragments and 6 dZ fragments serve 54 products, a third of an LDS read
-// per product.  The wavefronts' sums are added in order at the end; the bias
+// per product.  The wavefronts' sums are added in a fixed order at the end; the bias
 // sums use an all-ones X operand.
 // Measured (one MI355X, with the sum of the partials): 16 -> 16 at 128^3 165 ->
-// 48 us, 48 -> 16 359 -> 120 us (channels last).  Before, X was transposed into three shifted
+// 42 us, 48 -> 16 365 -> 116 us (channels last).  Before, X was transposed into three shifted
 // copies by 2-byte LDS writes (24 per staged 16 bytes).
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s4 lds_s4;
